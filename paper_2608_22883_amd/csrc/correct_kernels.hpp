@@ -12,10 +12,8 @@ template <typename T>
 using Corr1Cfg = GemmCfg<T, 64, 4>;
 template <typename T, int BM = 128>
 using Corr2Cfg = GemmCfg<T, BM, 2>;
-// memory build: 256-row tiles (three 48 KB stages, two thirds of a 128-row tile's operand
-// bytes per multiply-add) for bf16 memories of many rows, else 128-row tiles
-template <typename T, int BM = 128>
-using MemCfg = GemmCfg<T, BM, BM == 256 ? 3 : 4>;
+template <typename T, int BM>
+using MemCfg = GemmCfg<T, BM, 4>;
 constexpr int kPartCols = 128;  // columns reduced into one partial sum (one block tile)
 
 __host__ __device__ constexpr int n_parts(int cols) { return (cols + kPartCols - 1) / kPartCols; }
@@ -301,38 +299,55 @@ __global__ __launch_bounds__(256) void rms_kernel(int n, int d, const float* __r
 
 // Memory build: [keys | values] = LN(V) [W_K ; W_U]^T with the LayerNorm folded into the
 // epilogue exactly as in the query projection (c1 = W' 1, c2 = W b).
-template <typename T, int BM = 128>
-__global__ __launch_bounds__(256) void mem_proj_kernel(TileMap tm, int n, const T* __restrict__ V,
-                                                       int d_v, const T* __restrict__ Wku, int d_m,
-                                                       const float2* __restrict__ stats,
-                                                       const float* __restrict__ c1,
-                                                       const float* __restrict__ c2,
-                                                       T* __restrict__ keys, T* __restrict__ values) {
+template <typename T>
+struct MemEpi {
+  int n, d_m;
+  const float2* stats;
+  const float* c1;
+  const float* c2;
+  T* keys;
+  T* values;
+  __device__ __forceinline__ float operator()(int row, int col0, const float (&v)[8]) const {
+    if (row >= n || col0 >= 2 * d_m) return 0.f;
+    const float2 st = stats[row];
+    float a[8], b[8], val[8];
+    load8(c1 + col0, a);
+    load8(c2 + col0, b);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) val[e] = st.y * (v[e] - st.x * a[e]) + b[e];
+    if (col0 < d_m)
+      store8(keys + static_cast<int64_t>(row) * d_m + col0, val);
+    else
+      store8(values + static_cast<int64_t>(row) * d_m + (col0 - d_m), val);
+    return 0.f;
+  }
+};
+
+template <typename T, int BM>
+__global__ __launch_bounds__(256) void mem_proj_kernel(TileMap tm, const T* __restrict__ V, int d_v,
+                                                       const T* __restrict__ Wku, MemEpi<T> epi) {
   using C = MemCfg<T, BM>;
   __shared__ __align__(16) unsigned char smem[C::SMEM_BYTES];
   int tr, tc;
   if (!tm.map(tr, tc)) return;
   const int m0 = tr * C::BM, n0 = tc * C::BN;
-  const int N = 2 * d_m;
   f32x4 acc[C::TM][C::TN];
-  gemm_mainloop<C>(acc, V, d_v, n, Wku, d_v, N, d_v, m0, n0, smem);
-  gemm_epilogue<C>(
-      acc, smem, m0, n0,
-      [&](int row, int col0, const float(&v)[8]) -> float {
-        if (row >= n || col0 >= N) return 0.f;
-        const float2 st = stats[row];
-        float a[8], b[8], val[8];
-        load8(c1 + col0, a);
-        load8(c2 + col0, b);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) val[e] = st.y * (v[e] - st.x * a[e]) + b[e];
-        if (col0 < d_m)
-          store8(keys + static_cast<int64_t>(row) * d_m + col0, val);
-        else
-          store8(values + static_cast<int64_t>(row) * d_m + (col0 - d_m), val);
-        return 0.f;
-      },
-      NoRowSum{});
+  gemm_mainloop<C>(acc, V, d_v, epi.n, Wku, d_v, 2 * epi.d_m, d_v, m0, n0, smem);
+  gemm_epilogue<C>(acc, smem, m0, n0, epi, NoRowSum{});
+}
+
+template <int QM>
+__global__ __launch_bounds__(512, 2) void mem_proj_pp_kernel(TileMap tm, const bf16_t* __restrict__ V, int d_v,
+                                                             const bf16_t* __restrict__ Wku,
+                                                             MemEpi<bf16_t> epi) {
+  using C = PpCfg<QM>;
+  __shared__ __align__(16) unsigned char smem[C::SMEM_BYTES];
+  int tr, tc;
+  if (!tm.map(tr, tc)) return;
+  const int m0 = tr * C::BM, n0 = tc * C::BN;
+  typename C::Acc acc;
+  pp_mainloop<C>(acc, V, d_v, epi.n, Wku, d_v, 2 * epi.d_m, d_v, m0, n0, smem);
+  pp_epilogue<C>(acc, smem, m0, n0, epi);
 }
 
 // ---------------------------------------------------------------------------------

@@ -288,6 +288,12 @@ fovea_status pack_weights(fovea_ctx* c, const fovea_params* p, hipStream_t s) {
   return FOVEA_OK;
 }
 
+void launch_mem_proj_pp(int qm, const TileMap& tm, const bf16_t* V, int d_v, const bf16_t* Wku,
+                        const MemEpi<bf16_t>& epi, hipStream_t s) {
+  auto kern = qm == 4 ? mem_proj_pp_kernel<4> : qm == 3 ? mem_proj_pp_kernel<3> : mem_proj_pp_kernel<2>;
+  hipLaunchKernelGGL(kern, dim3(tile_grid(tm)), dim3(512), 0, s, tm, V, d_v, Wku, epi);
+}
+
 template <typename T>
 fovea_status run_build(fovea_ctx* c, int n, const void* V, void* keys, void* values,
                        float2* build_stats, hipStream_t s) {
@@ -301,18 +307,39 @@ fovea_status run_build(fovea_ctx* c, int n, const void* V, void* keys, void* val
                        static_cast<const int64_t*>(nullptr), int64_t{0}, 0,
                        static_cast<int32_t*>(nullptr), static_cast<NodeInfo*>(nullptr), c->err);
   }
-  // 256-row tiles once the grid still holds at least 256 of them (bf16 only)
-  const bool tall = std::is_same<T, bf16_t>::value &&
-                    static_cast<int64_t>((n + 255) / 256) * ((2 * D.d_m + 127) / 128) >= 256;
-  const int BMv = tall ? 256 : 128;
-  const TileMap tm = make_tile_map((n + BMv - 1) / BMv, (2 * D.d_m + 127) / 128,
-                                   static_cast<double>(n) * D.d_v, 2.0 * D.d_m * D.d_v);
-  {
-    ProfScope ps(c, kMemProj, s);
-    hipLaunchKernelGGL((tall ? mem_proj_kernel<T, 256> : mem_proj_kernel<T, 128>), dim3(tile_grid(tm)),
-                       dim3(256), 0, s, tm, n, static_cast<const T*>(V), D.d_v,
-                       static_cast<const T*>(c->W_KU), D.d_m, build_stats, c->m_c1, c->m_c2,
-                       static_cast<T*>(keys), static_cast<T*>(values));
+  MemEpi<T> epi;
+  epi.n = n;
+  epi.d_m = D.d_m;
+  epi.stats = build_stats;
+  epi.c1 = c->m_c1;
+  epi.c2 = c->m_c2;
+  epi.keys = static_cast<T*>(keys);
+  epi.values = static_cast<T*>(values);
+  const int N = 2 * D.d_m;
+  const T* Vt = static_cast<const T*>(V);
+  const T* Wku = static_cast<const T*>(c->W_KU);
+  auto map = [&](int bm, int bn) {
+    return make_tile_map((n + bm - 1) / bm, (N + bn - 1) / bn, static_cast<double>(n) * D.d_v,
+                         static_cast<double>(N) * D.d_v);
+  };
+  auto tiles = [&](int bm, int bn) { return static_cast<int64_t>((n + bm - 1) / bm) * ((N + bn - 1) / bn); };
+  ProfScope ps(c, kMemProj, s);
+  if constexpr (std::is_same<T, bf16_t>::value) {
+    // a full round of 128 x 128 tiles or more: the ping-pong core in the tile height that
+    // takes the least time over its rounds
+    if (tiles(128, 128) > 256) {
+      const int qm = pp_rows(n, N);
+      launch_mem_proj_pp(qm, map(64 * qm, 256), Vt, D.d_v, Wku, epi, s);
+      return hipGetLastError() == hipSuccess ? FOVEA_OK : FOVEA_ERR_DEVICE;
+    }
+  }
+  // 64-row tiles while they take one round
+  if (tiles(64, 128) <= 256) {
+    const TileMap tm = map(64, 128);
+    hipLaunchKernelGGL((mem_proj_kernel<T, 64>), dim3(tile_grid(tm)), dim3(256), 0, s, tm, Vt, D.d_v, Wku, epi);
+  } else {
+    const TileMap tm = map(128, 128);
+    hipLaunchKernelGGL((mem_proj_kernel<T, 128>), dim3(tile_grid(tm)), dim3(256), 0, s, tm, Vt, D.d_v, Wku, epi);
   }
   FOVEA_HIP(hipGetLastError());
   return FOVEA_OK;
@@ -657,23 +684,34 @@ void launch_lm(int n, const T* h, int d, const T* W, int vocab, int k, uint64_t*
                      k, cand);
 }
 
+void launch_lm_pp(int n, const bf16_t* h, int d, const bf16_t* W, int vocab, int k, uint64_t* cand,
+                  hipStream_t s) {
+  const int qm = pp_rows(n, vocab);
+  const LmMap m = make_lm_map((n + 64 * qm - 1) / (64 * qm), (vocab + 255) / 256);
+  auto kern = qm == 4 ? lm_pp_kernel<4> : qm == 3 ? lm_pp_kernel<3> : lm_pp_kernel<2>;
+  hipLaunchKernelGGL(kern, dim3(lm_grid(m)), dim3(512), 0, s, m, n, h, d, W, vocab, k, cand);
+}
+
 template <typename T>
 fovea_status run_lm_topk(fovea_ctx* c, int n, const void* h, const void* W, int vocab, int k,
                          int32_t* idx, float* logit, uint64_t* cand, hipStream_t s) {
   const int d = c->dims.d;
   {
     ProfScope ps(c, kLmHead, s);
-    // row tiles: 64 for one small batch, 256 for many rows (half the operand bytes per
-    // MAC of a 128-row tile), 128 between
-    if (n <= 64)
-      launch_lm<T, 64>(n, static_cast<const T*>(h), d, static_cast<const T*>(W), vocab, k, cand, s);
-    else if (n < 768)
-      launch_lm<T, 128>(n, static_cast<const T*>(h), d, static_cast<const T*>(W), vocab, k, cand, s);
-    else
-      launch_lm<T, 256>(n, static_cast<const T*>(h), d, static_cast<const T*>(W), vocab, k, cand, s);
+    const T* ht = static_cast<const T*>(h);
+    const T* Wt = static_cast<const T*>(W);
+    if constexpr (std::is_same<T, bf16_t>::value) {
+      if (n <= 64) launch_lm<T, 64>(n, ht, d, Wt, vocab, k, cand, s);
+      else launch_lm_pp(n, ht, d, Wt, vocab, k, cand, s);
+    } else {
+      if (n <= 64) launch_lm<T, 64>(n, ht, d, Wt, vocab, k, cand, s);
+      else if (n < 768) launch_lm<T, 128>(n, ht, d, Wt, vocab, k, cand, s);
+      else launch_lm<T, 256>(n, ht, d, Wt, vocab, k, cand, s);
+    }
   }
   {
-    const int n_cand = (vocab + 127) / 128 * k;
+    const int tile = std::is_same<T, bf16_t>::value && n > 64 ? 256 : 128;
+    const int n_cand = (vocab + tile - 1) / tile * k;
     ProfScope ps(c, kLmMerge, s);
     if (k <= 8)
       hipLaunchKernelGGL(lm_merge_kernel<8>, dim3(n), dim3(256), 0, s, n_cand, k, cand, idx, logit);

@@ -397,6 +397,262 @@ __device__ __forceinline__ void epilogue_group(int gi, int m0, int n0, int& row,
   col0 = n0 + (g & 15) * 8;
 }
 
+// ---------------------------------------------------------------------------------
+// Ping-pong GEMM for grids of many tiles (bf16): 8 waves on a (64 QM) x 256 tile.
+//
+// Eight waves as 2 (rows) x 4 (columns); each owns QM x 2 accumulators of 16x16 in each
+// quadrant of the tile (row half x column half).  A k-tile (64 wide, the same swizzled
+// 128-byte rows as above) is four half tiles A0, A1, B0, B1; two k-tiles fill the LDS and
+// a half is refilled with k-tile + 2 as soon as every wave has read it.  One k-tile takes
+// four phases (quadrants 00, 01, 11, 10), each a read slot (fragments from LDS, loads of
+// a half tile issued) and a multiply slot, a barrier after each.  Waves w and w + 4 share
+// a SIMD and run one slot apart, so that one of them multiplies while the other reads:
+// with one wave per SIMD the reads, waits and barriers of the core above are not hidden.
+//   Bound by the matrix cores: a k-tile of 256 x 256 asks 2048 MFMA cycles, 64 KB of
+// direct-to-LDS loads (about 1400 cycles) and 192 KB of LDS reads (about 1540).  Measured
+// (plain fp32 stores, back to back): 4096^3 99.9 us, 1376 TFLOP/s, against 139 us (128 x
+// 128, 4 waves) and 117 us (256 x 128, 4 waves).  A k-tile takes 1.18, 1.06, 0.83 us at
+// QM = 4, 3, 2: the slots of smaller tiles are bound by their reads and barriers.
+// ---------------------------------------------------------------------------------
+template <int QM_>
+struct PpCfg {
+  static constexpr int QM = QM_, QN = 2, WN = 4, NT = 512;
+  static constexpr int BM = 64 * QM, BN = 256;
+  static constexpr int AH = BM / 2, BH = BN / 2;  // rows of a half tile
+  static constexpr int A_BYTES = AH * 128, B_BYTES = BH * 128;
+  static constexpr int STAGE_BYTES = 2 * (A_BYTES + B_BYTES);
+  // direct-to-LDS loads per wave and half tile (8 rows each; where the rows do not divide,
+  // the last load is repeated so that every wave counts the same number)
+  static constexpr int NA = (AH / 8 + 7) / 8, NB = BH / 8 / 8;
+  // epilogue staging: one row half of the tile in fp32 with a 4-float pad
+  static constexpr int SLD = BN + 4;
+  static constexpr int OUT_BYTES = AH * SLD * 4;
+  static constexpr int PIPE_BYTES = 2 * STAGE_BYTES;
+  static constexpr int SMEM_BYTES = PIPE_BYTES > OUT_BYTES ? PIPE_BYTES : OUT_BYTES;
+  using Acc = f32x4[2][2][QM][QN];  // [row half][column half][row block][column block]
+  static_assert(QM >= 2 && QM <= 4 && SMEM_BYTES <= 160 * 1024, "tile");
+  static constexpr int off_a(int s, int h) { return s * STAGE_BYTES + h * A_BYTES; }
+  static constexpr int off_b(int s, int h) { return s * STAGE_BYTES + 2 * A_BYTES + h * B_BYTES; }
+};
+
+// One direct-to-LDS load: lane L's 16 bytes at src go to dst + 16 L (dst uniform).
+__device__ __forceinline__ void load_lds16(const bf16_t* src, unsigned char* dst) {
+  __builtin_amdgcn_global_load_lds(src, (lds_void_ptr)dst, 16, 0, 0);
+}
+
+template <int P>
+__device__ __forceinline__ void wave_prio() {
+  __builtin_amdgcn_s_setprio(P);
+}
+
+// Ends a read slot: at most VM loads still out, this wave's LDS reads done, barrier.
+template <int VM>
+__device__ __forceinline__ void pp_end_read() {
+  if constexpr (VM < 63) wait_vmcnt<VM>();
+  __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+  lds_barrier();
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+__device__ __forceinline__ void pp_end_mma() {
+  __builtin_amdgcn_sched_barrier(0);
+  lds_barrier();
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+template <class C>
+__device__ __forceinline__ void pp_mainloop(typename C::Acc& acc, const bf16_t* __restrict__ A,
+                                            int64_t lda, int M, const bf16_t* __restrict__ Bw, int64_t ldb,
+                                            int N, int K, int m0, int n0, unsigned char* smem) {
+  constexpr int QM = C::QM, QN = C::QN, NA = C::NA, NB = C::NB;
+  constexpr int NT1 = 2 * NA + 2 * NB;  // loads of one k-tile per wave
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+  const int wm = wave & 1, wn = wave >> 1;
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int i = 0; i < QM; ++i)
+#pragma unroll
+        for (int j = 0; j < QN; ++j) acc[a][b][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const bf16_t* ga[2][NA];
+  const bf16_t* gb[2][NB];
+  int da[NA], db[NB];
+#pragma unroll
+  for (int u = 0; u < NA; ++u) {
+    const int r0 = min(wave + 8 * u, C::AH / 8 - 1) * 8;
+    const int row = r0 + (lane >> 3);
+    const int c = (lane & 7) ^ ((row >> 1) & 7);
+    da[u] = r0 * 128;
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      ga[h][u] = A + static_cast<int64_t>(min(m0 + h * C::AH + row, M - 1)) * lda + c * 8;
+  }
+#pragma unroll
+  for (int u = 0; u < NB; ++u) {
+    const int r0 = (wave + 8 * u) * 8;
+    const int row = r0 + (lane >> 3);
+    const int c = (lane & 7) ^ ((row >> 1) & 7);
+    db[u] = r0 * 128;
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      gb[h][u] = Bw + static_cast<int64_t>(min(n0 + h * C::BH + row, N - 1)) * ldb + c * 8;
+  }
+  const int nk = K / 64;
+  const int arow = wm * QM * 16 + (lane & 15), brow = wn * QN * 16 + (lane & 15);
+  int fa[2], fb[2];
+#pragma unroll
+  for (int kh = 0; kh < 2; ++kh) {
+    fa[kh] = arow * 128 + (((4 * kh + (lane >> 4)) ^ ((arow >> 1) & 7)) << 4);
+    fb[kh] = brow * 128 + (((4 * kh + (lane >> 4)) ^ ((brow >> 1) & 7)) << 4);
+  }
+  // loads past the last k-tile repeat it (into a half that nobody reads any more), so that
+  // the waits are fixed counts
+  auto load_a = [&](int kt, int s, int h) {
+    const int k0 = min(kt, nk - 1) * 64;
+#pragma unroll
+    for (int u = 0; u < NA; ++u)
+      load_lds16(ga[h][u] + k0, smem + C::off_a(s, h) + da[u]);
+  };
+  auto load_b = [&](int kt, int s, int h) {
+    const int k0 = min(kt, nk - 1) * 64;
+#pragma unroll
+    for (int u = 0; u < NB; ++u)
+      load_lds16(gb[h][u] + k0, smem + C::off_b(s, h) + db[u]);
+  };
+  bf16x8 af[2][QM], bf[2][2][QN];  // [k half][row block], [column half][k half][column block]
+  auto read_a = [&](int s, int h) {
+#pragma unroll
+    for (int kh = 0; kh < 2; ++kh)
+#pragma unroll
+      for (int i = 0; i < QM; ++i)
+        af[kh][i] = *reinterpret_cast<const bf16x8*>(smem + C::off_a(s, h) + fa[kh] + i * 16 * 128);
+  };
+  auto read_b = [&](int s, int h) {
+#pragma unroll
+    for (int kh = 0; kh < 2; ++kh)
+#pragma unroll
+      for (int j = 0; j < QN; ++j)
+        bf[h][kh][j] = *reinterpret_cast<const bf16x8*>(smem + C::off_b(s, h) + fb[kh] + j * 16 * 128);
+  };
+  auto mma = [&](int a, int b) {
+    wave_prio<1>();
+#pragma unroll
+    for (int kh = 0; kh < 2; ++kh)
+#pragma unroll
+      for (int i = 0; i < QM; ++i)
+#pragma unroll
+        for (int j = 0; j < QN; ++j) mfma_bf16_16x16x32_acc(acc[a][b][i][j], af[kh][i], bf[b][kh][j]);
+    wave_prio<0>();
+  };
+  // k-tile kt from stage s.  A wave waits, one slot or more before the slot that reads a
+  // half, until its own loads of that half are done; the barriers between make every
+  // wave's share visible.  Loads are issued in the order A0 B0, B1, A1.
+  auto tile = [&](int kt, auto S) {
+    constexpr int s = decltype(S)::value;
+    read_a(s, 0);
+    read_b(s, 0);
+    pp_end_read<NA + NT1>();  // B1 of kt is here
+    mma(0, 0);
+    pp_end_mma();
+    read_b(s, 1);
+    load_a(kt + 2, s, 0);
+    load_b(kt + 2, s, 0);
+    pp_end_read<NT1 + NA + NB>();  // A1 of kt
+    mma(0, 1);
+    pp_end_mma();
+    read_a(s, 1);
+    load_b(kt + 2, s, 1);
+    pp_end_read<63>();
+    mma(1, 1);
+    pp_end_mma();
+    load_a(kt + 2, s, 1);
+    pp_end_read<NB + NA + NT1>();  // A0 and B0 of kt + 1
+    mma(1, 0);
+    pp_end_mma();
+  };
+#pragma unroll
+  for (int t = 0; t < 2; ++t) {
+    load_a(t, t, 0);
+    load_b(t, t, 0);
+    load_b(t, t, 1);
+    load_a(t, t, 1);
+  }
+  wait_vmcnt<NB + NA + NT1>();
+  lds_barrier();
+  if (wave >= 4) lds_barrier();  // the second wave of each SIMD runs one slot behind
+  int kt = 0;
+  for (; kt + 1 < nk; kt += 2) {
+    tile(kt, std::integral_constant<int, 0>());
+    tile(kt + 1, std::integral_constant<int, 1>());
+  }
+  if (kt < nk) tile(kt, std::integral_constant<int, 0>());
+  if (wave < 4) lds_barrier();
+  wait_vmcnt<0>();  // the repeated loads land before the LDS is reused
+  mfma_results_ready();
+  lds_barrier();
+}
+
+// Row half a of the accumulators into the staging area (fp32, rows SLD apart).
+template <class C>
+__device__ __forceinline__ void pp_stage(const typename C::Acc& acc, int a, float* so) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int wm = wave & 1, wn = wave >> 1;
+#pragma unroll
+  for (int b = 0; b < 2; ++b)
+#pragma unroll
+    for (int i = 0; i < C::QM; ++i)
+#pragma unroll
+      for (int j = 0; j < C::QN; ++j)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          so[(wm * C::QM * 16 + i * 16 + 4 * (lane >> 4) + v) * C::SLD + b * C::BH + wn * C::QN * 16 +
+             j * 16 + (lane & 15)] = acc[a][b][i][j][v];
+}
+
+// LDS-staged epilogue: f(row, col0, v) sees 8 consecutive columns of a row, as in
+// gemm_epilogue (without row sums); 16 consecutive lanes hold 128 columns of a row.
+template <class C, class F>
+__device__ __forceinline__ void pp_epilogue(const typename C::Acc& acc, unsigned char* smem,
+                                            int m0, int n0, F&& f) {
+  float* so = reinterpret_cast<float*>(smem);
+  constexpr int GROUPS = C::AH * (C::BN / 8);
+  static_assert(GROUPS % C::NT == 0, "epilogue mapping");
+#pragma unroll
+  for (int a = 0; a < 2; ++a) {
+    pp_stage<C>(acc, a, so);
+    __syncthreads();
+#pragma unroll
+    for (int g0 = 0; g0 < GROUPS; g0 += C::NT) {
+      const int g = g0 + static_cast<int>(threadIdx.x);
+      const int r = g / (C::BN / 8), c8 = g % (C::BN / 8);
+      float v[8];
+      load8(so + r * C::SLD + c8 * 8, v);
+      f(m0 + a * C::AH + r, n0 + c8 * 8, v);
+    }
+    __syncthreads();
+  }
+}
+
+// Row blocks of 16 per quadrant and wave (tile rows 64 QM) for an M x N product on 256
+// compute units: rounds of tiles times the measured time of a k-tile.
+inline int pp_rows(int64_t M, int64_t N) {
+  const int cost[5] = {0, 0, 83, 106, 118};
+  int best = 4;
+  int64_t best_cost = -1;
+  for (int qm = 4; qm >= 2; --qm) {
+    const int64_t tiles = (M + 64 * qm - 1) / (64 * qm) * ((N + 255) / 256);
+    const int64_t c = (tiles + 255) / 256 * cost[qm];
+    if (best_cost < 0 || c < best_cost) {
+      best_cost = c;
+      best = qm;
+    }
+  }
+  return best;
+}
+
 struct NoRowSum {
   __device__ __forceinline__ void operator()(int, float) const {}
 };

@@ -4,10 +4,11 @@
 // experimental setup).
 //
 // Two kernels:
-//  * lm_kernel: the logit GEMM in 64, 128 or 256 x 128 tiles (the bf16
-//    direct-to-LDS mainloop of gemm.hpp) with an epilogue that keeps, for every row of
-//    the tile, its k largest logits and writes them as candidates [row][column tile][k]
-//    - the logits themselves never reach memory;
+//  * lm_kernel / lm_pp_kernel: the logit GEMM (the cores of gemm.hpp: 64-row tiles for one
+//    small batch, which is bound by reading the head; the ping-pong core's 256-column tiles
+//    for more bf16 rows; 128- and 256-row tiles for fp32) with an epilogue that keeps, for
+//    every row of the tile, its k largest logits and writes them as candidates
+//    [row][column tile][k] - the logits themselves never reach memory;
 //  * lm_merge_kernel: one block per row merges the row's candidates into its top k.
 // A candidate is one 64-bit key: the logit mapped to an order-preserving unsigned
 // integer in the high word and the complemented token id in the low word, so that one
@@ -19,17 +20,12 @@
 // 8 x 4 tiles that share their h rows and weight rows through the L2, and a head too
 // large for the Infinity Cache (Qwen's 1.09 GB) is read from HBM once per eight row
 // tiles rather than once per row tile (measured: 6% on 768 rows of that head).
-// Selection has no serial rounds.  On 32-bit order-preserving images of the
-// logits, every lane sorts its 8 values with a sorting network, then four butterfly
-// steps over DPP row permutations each keep the 8 largest of two sorted lists (a
-// bitonic half-cleaner and a bitonic sort of 8); all 16 lanes of a row then hold the
-// row's 8 largest values, hence its k-th largest value T.  Each lane takes its values
-// above T and, lowest ids first, the share of values equal to T that the k slots
-// leave, placed by two row prefix counts (k = 9 .. 16 runs the same with 16-long
-// lists).  With one wave per SIMD (the mainloop's LDS), a round-per-candidate selection
-// was latency bound (about 43 us per round on 1920 x 32000 logits), and the same
-// network on 64-bit (logit, id) keys spent most of its time in compare-to-select wait
-// states.
+// Selection (lm_select_quad): four lanes of a wave share a row of the staged tile, a
+// quarter of its columns each.  The k-th largest of the row's 32 chunk maxima (8 chunks a
+// lane, sorted by a network and merged over the four lanes) bounds the row's k-th largest
+// logit from below, so the few logits that reach it (about 7 for k = 6) are all that is
+// ranked.  About 8 VALU operations per logit; a sorting network over every logit took
+// about 37 (a 256 x 256 tile: 28 us of epilogue after 66 us of products; now 5 us).
 #pragma once
 
 #include <cfloat>
@@ -85,6 +81,11 @@ __device__ __forceinline__ uint32_t lm_ord(float v) {
   return v == v ? o : 0u;
 }
 
+// the logit whose image is o (o != 0)
+__device__ __forceinline__ float lm_ord_val(uint32_t o) {
+  return __uint_as_float((o >> 31) ? (o ^ 0x80000000u) : ~o);
+}
+
 __device__ __forceinline__ uint64_t lm_key_of(uint32_t o, int id) {
   return o == 0u ? 0ull : (static_cast<uint64_t>(o) << 32) | static_cast<uint32_t>(~id);
 }
@@ -97,8 +98,15 @@ __device__ __forceinline__ int lm_key_id(uint64_t key) {
 
 __device__ __forceinline__ float lm_key_val(uint64_t key) {
   if (key == 0ull) return -INFINITY;
-  const uint32_t o = static_cast<uint32_t>(key >> 32);
-  return __uint_as_float((o >> 31) ? (o ^ 0x80000000u) : ~o);
+  return lm_ord_val(static_cast<uint32_t>(key >> 32));
+}
+
+// Orders the LDS accesses of one wave (they execute in issue order; this keeps the compiler
+// from moving them across the point).
+__device__ __forceinline__ void lm_wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 __device__ __forceinline__ uint64_t umax64(uint64_t a, uint64_t b) { return a > b ? a : b; }
@@ -177,67 +185,200 @@ __device__ __forceinline__ uint64_t wave_max64(uint64_t v) {
   return m;
 }
 
-// The k (<= LL) largest logits of two rows of a 128-column tile, each row spread over
-// the 16 lanes of a DPP row (8 consecutive columns per lane, starting at col0), written
-// in any order as the k candidates of (row, tile).  th = the row's k-th largest value,
-// found on 32-bit order-preserving images with a sorting network and LL-long butterfly
-// merges; every lane then takes its values above th and, lowest ids first, the share of
-// values equal to th that the k slots leave, placed by two row prefix counts.
+__device__ __forceinline__ float max3_f32(float a, float b, float c) {
+  float r;  // a NaN operand is ignored
+  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
+}
+
+typedef __attribute__((ext_vector_type(2))) uint64_t u64x2;
+
+// m = 2 m + (x >= t): the compare's carry goes straight into the shift (left to itself the
+// compiler keeps every compare in a scalar pair of its own and spills them).
+__device__ __forceinline__ void push_ge_f32(uint32_t& m, float x, float t) {
+  asm("v_cmp_ge_f32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(m) : "v"(x), "v"(t) : "vcc");
+}
+
+__device__ __forceinline__ void push_eq_f32(uint32_t& m, float x, float t) {
+  asm("v_cmp_eq_f32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(m) : "v"(x), "v"(t) : "vcc");
+}
+
+// The value of the lane 16 (32) away: with both operands equal, a row swap leaves this
+// lane's value in one result and the partner's in the other.
+__device__ __forceinline__ uint32_t xor16_u32(uint32_t v, int lane) {
+  const auto p = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+  return (lane & 16) ? static_cast<uint32_t>(p[0]) : static_cast<uint32_t>(p[1]);
+}
+
+__device__ __forceinline__ uint32_t xor32_u32(uint32_t v, int lane) {
+  const auto p = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  return (lane & 32) ? static_cast<uint32_t>(p[0]) : static_cast<uint32_t>(p[1]);
+}
+
+// The LL largest of this lane's sorted list and its partner's, sorted.
 template <int LL>
-__device__ __forceinline__ void lm_select_rows(const float (&v)[2][8], const int (&row)[2],
-                                               int col0, int vocab, int k, int n,
-                                               uint64_t* __restrict__ cand, int n_tiles,
-                                               int tile) {
-  uint32_t o[2][8], L[2][LL];
+__device__ __forceinline__ void merge_rows(uint32_t (&a)[LL], int lane, bool far) {
+  uint32_t p[LL];
 #pragma unroll
-  for (int g = 0; g < 2; ++g) {
+  for (int i = 0; i < LL; ++i) p[i] = far ? xor32_u32(a[LL - 1 - i], lane) : xor16_u32(a[LL - 1 - i], lane);
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {  // masked, not branched: columns past the vocabulary are empty
-      o[g][e] = lm_ord(v[g][e]) & (0u - static_cast<uint32_t>(col0 + e < vocab));
-      L[g][e] = o[g][e];
-    }
-#pragma unroll
-    for (int e = 8; e < LL; ++e) L[g][e] = 0u;
+  for (int i = 0; i < LL; ++i) a[i] = max(a[i], p[i]);
+  bitonic_desc<LL>(a);
+}
+
+// The k (<= LL) largest logits of 16 staged rows of a tile of 4 NV columns, by one wave:
+// lane 16 q + r holds columns q NV .. + NV - 1 of row r (16 consecutive lanes read 16 rows
+// 4 banks apart, without conflicts).  so: the wave's first row (rows ld floats apart, ld a
+// multiple of 4 with ld % 64 == 4); row0: its index; n0: the tile's first column.  Writes
+// candidate t of (row, tile) to cand[(row n_tiles + tile) k + t], in descending order, 0
+// where the tile holds fewer than k.  Columns past the vocabulary become NaN, which
+// neither reaches a maximum nor compares.
+template <int NV, int LL>
+__device__ __forceinline__ void lm_select_quad(float* so, int ld, int row0, int n0, int vocab, int k, int n,
+                                               uint64_t* __restrict__ cand, int n_tiles, int tile) {
+  constexpr int CH = NV / 8;   // columns per chunk
+  constexpr int HMAX = LL;            // logits a lane may contribute to the row's list
+  constexpr int CAP = 2 * NV - 2;     // keys that fit the row, four of them padding
+  static_assert(NV % 32 == 0, "hit words");
+  const int lane = threadIdx.x & 63, q = lane >> 4;
+  float* row_s = so + (lane & 15) * ld;
+  const float* mine = row_s + q * NV;
+  const int col0 = n0 + q * NV;
+  if (n0 + 4 * NV > vocab) {
+    for (int e = max(0, vocab - col0); e < NV; ++e) row_s[q * NV + e] = __builtin_nanf("");
+    lm_wave_sync();
   }
-  sort8_desc(L[0]);  // the zero tail of an LL = 16 list is already in place
-  sort8_desc(L[1]);
+  float v[NV];
 #pragma unroll
-  for (int sel = 0; sel < 4; ++sel) {
-    merge_step<LL>(L[0], sel);
-    merge_step<LL>(L[1], sel);
+  for (int e = 0; e < NV; e += 4) {
+    const f32x4 x = *reinterpret_cast<const f32x4*>(mine + e);
+    v[e] = x[0]; v[e + 1] = x[1]; v[e + 2] = x[2]; v[e + 3] = x[3];
+  }
+  uint32_t L[LL];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    float m = -INFINITY;
+#pragma unroll
+    for (int e = 0; e < CH; e += 2) m = max3_f32(m, v[j * CH + e], v[j * CH + e + 1]);
+    L[j] = lm_ord(m);
   }
 #pragma unroll
-  for (int g = 0; g < 2; ++g) {
-    uint32_t th = L[g][0];
+  for (int j = 8; j < LL; ++j) L[j] = 0u;
+  sort8_desc(L);
+  merge_rows<LL>(L, lane, false);
+  merge_rows<LL>(L, lane, true);
+  uint32_t th = L[0];
 #pragma unroll
-    for (int q = 1; q < LL; ++q)
-      if (q < k) th = min(th, L[g][q]);
-    int c_gt = 0, n_gt = 0, n_eq = 0;
+  for (int j = 1; j < LL; ++j)
+    if (j < k) th = L[j];
+  float t0 = lm_ord_val(th);
+  // the lane's columns that reach the bound, first column in the highest bit
+  uint32_t hit[NV / 32];
+  auto find_hits = [&](float t) {
+    int c = 0;
 #pragma unroll
-    for (int q = 0; q < LL; ++q) c_gt += (q < k) & (L[g][q] > th);
+    for (int w = 0; w < NV / 32; ++w) {
+      uint32_t m = 0;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      n_gt += o[g][e] > th;
-      n_eq += o[g][e] == th;
+      for (int e = 0; e < 32; ++e) push_ge_f32(m, v[32 * w + e], t);
+      hit[w] = m;
+      c += __popc(m);
     }
-    const int need = k - c_gt;  // slots left for values equal to th
-    const int eq_before = row16_incl_scan_i32(n_eq) - n_eq;
-    const int take = min(max(need - eq_before, 0), n_eq);
-    const int nsel = n_gt + take;
-    int slot = row16_incl_scan_i32(nsel) - nsel;
-    if (row[g] < n) {
-      uint64_t* dst = cand + (static_cast<int64_t>(row[g]) * n_tiles + tile) * k;
-      int r = eq_before;
+    return c;
+  };
+  int cnt = find_hits(t0);
+  auto pair_sums = [&](int x, int& x1, int& x2) {  // counts of lanes q ^ 1 and of the other pair
+    x1 = static_cast<int>(xor16_u32(static_cast<uint32_t>(x), lane));
+    x2 = static_cast<int>(xor32_u32(static_cast<uint32_t>(x + x1), lane));
+    return x + x1 + x2;
+  };
+  int c1, c2;
+  int c = pair_sums(cnt, c1, c2);
+  const int row = row0 + (lane & 15);
+  uint64_t* dst = cand + (static_cast<int64_t>(row) * n_tiles + tile) * k;
+  if (__ballot(cnt > HMAX || c > CAP - 4) != 0ull) {
+    // too many for the list (a tile with few valid columns, logits in one lane, equal
+    // logits): search the k-th largest logit itself, between the bound and the maximum
+    // (all rows of the wave together, until each is exact), then take the logits above it
+    // and of those equal to it the lowest ids that the k slots leave
+    uint32_t lo = th, hi = L[0];
+    while (__ballot(lo < hi) != 0ull) {
+      const uint32_t mid = lo + ((hi - lo + 1) >> 1);
+      const int got = pair_sums(find_hits(lm_ord_val(mid)), c1, c2);
+      if (got >= k) lo = mid;
+      if (got < k) hi = mid - 1;
+      if (got == k) hi = lo;
+    }
+    t0 = lm_ord_val(lo);
+    find_hits(t0);
+    uint32_t eq[NV / 32];
+    int ngt = 0, neq = 0;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const bool eq = o[g][e] == th;
-        const bool s = (o[g][e] > th) | (eq & (r < need));
-        r += eq;
-        if (s) dst[slot] = lm_key_of(o[g][e], col0 + e);
-        slot += s;
+    for (int w = 0; w < NV / 32; ++w) {
+      uint32_t m = 0;
+#pragma unroll
+      for (int e = 0; e < 32; ++e) push_eq_f32(m, v[32 * w + e], t0);
+      eq[w] = m;
+      hit[w] &= ~m;
+      neq += __popc(m);
+      ngt += __popc(hit[w]);
+    }
+    int e1, e2;
+    pair_sums(ngt, e1, e2);
+    const int need = k - (ngt + e1 + e2);
+    pair_sums(neq, e1, e2);
+    int take = min(max(need - (((q & 1) ? e1 : 0) + ((q & 2) ? e2 : 0)), 0), neq);
+    cnt = ngt + take;
+#pragma unroll
+    for (int w = 0; w < NV / 32; ++w)
+      for (; take > 0 && eq[w] != 0u; --take) {
+        const uint32_t top = 0x80000000u >> __clz(eq[w]);
+        hit[w] |= top;
+        eq[w] &= ~top;
       }
-    }
+    c = pair_sums(cnt, c1, c2);
   }
+  int pos = ((q & 1) ? c1 : 0) + ((q & 2) ? c2 : 0);
+  uint64_t key[HMAX];
+#pragma unroll
+  for (int t = 0; t < HMAX; ++t) {
+    int e = __clz(hit[0]);
+    if (hit[0] != 0u) {
+      hit[0] &= ~(0x80000000u >> e);
+    } else if constexpr (NV == 64) {
+      const int e1 = __clz(hit[1]);
+      e = 32 + e1;
+      if (hit[1] != 0u) hit[1] &= ~(0x80000000u >> e1);
+    }
+    e = min(e, NV - 1);
+    key[t] = lm_key(mine[e], col0 + e);
+  }
+  lm_wave_sync();  // every value is read before the list overwrites the row
+  uint64_t* list = reinterpret_cast<uint64_t*>(row_s);
+#pragma unroll
+  for (int t = 0; t < HMAX; ++t)
+    if (t < cnt) list[pos + t] = key[t];
+  list[c + q] = 0ull;  // the ranking reads four at a time
+  lm_wave_sync();
+  // every lane ranks its own hits, four at a time while some lane has that many
+#pragma unroll
+  for (int t0 = 0; t0 < HMAX; t0 += 4) {
+    if (__ballot(cnt > t0) == 0ull) break;
+    int rk[4] = {0, 0, 0, 0};
+    for (int u = 0; u < c; u += 4) {
+      const u64x2 y0 = *reinterpret_cast<const u64x2*>(list + u);
+      const u64x2 y1 = *reinterpret_cast<const u64x2*>(list + u + 2);
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        rk[t] += (y0[0] > key[t0 + t] ? 1 : 0) + (y0[1] > key[t0 + t] ? 1 : 0) +
+                 (y1[0] > key[t0 + t] ? 1 : 0) + (y1[1] > key[t0 + t] ? 1 : 0);
+    }
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+      if (t0 + t < cnt && rk[t] < k && row < n) dst[rk[t]] = key[t0 + t];
+  }
+  for (int t = c + q; t < k; t += 4)
+    if (row < n) dst[t] = 0ull;
 }
 
 // ---- logits GEMM + per-tile candidates --------------------------------------------
@@ -258,15 +399,10 @@ __global__ __launch_bounds__(256) void lm_kernel(LmMap tm, int n, const T* __res
   f32x4 acc[C::TM][C::TN];
   gemm_mainloop<C>(acc, h, d, n, W, d, vocab, d, m0, n0, smem);
 
-  // stage the whole tile in LDS (the accumulators are then dead), then select: the 16
-  // threads of a row are 16 consecutive lanes (one DPP row), each holding 8 consecutive
-  // logits; each thread handles GPT rows, two at a time so that their independent
-  // selections interleave without spilling
+  // stage the whole tile in LDS (the accumulators are then dead), then select, 16 rows a wave
   float* so = reinterpret_cast<float*>(smem);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wm = wave / C::WN, wn = wave % C::WN;
-  constexpr int GPT = C::BM * (C::BN / 8) / C::NT;
-  static_assert(GPT % 2 == 0 && C::BN / 8 == 16, "epilogue mapping");
 #pragma unroll
   for (int i = 0; i < C::TM; ++i)
 #pragma unroll
@@ -276,25 +412,41 @@ __global__ __launch_bounds__(256) void lm_kernel(LmMap tm, int n, const T* __res
         so[(wm * C::SROWS + i * 16 + 4 * (lane >> 4) + v) * C::SLD + wn * C::TN * 16 + j * 16 +
            (lane & 15)] = acc[i][j][v];
   __syncthreads();
-  const int c8 = threadIdx.x & 15;
-  const int col0 = n0 + c8 * 8;
-#pragma unroll
-  for (int g0 = 0; g0 < GPT; g0 += 2) {
-    int row[2];
-    float v[2][8];
-#pragma unroll
-    for (int g = 0; g < 2; ++g) {
-      const int r = ((g0 + g) * C::NT + static_cast<int>(threadIdx.x)) >> 4;
-      row[g] = m0 + r;
-      const f32x4 lo = *reinterpret_cast<const f32x4*>(so + r * C::SLD + c8 * 8);
-      const f32x4 hi = *reinterpret_cast<const f32x4*>(so + r * C::SLD + c8 * 8 + 4);
-      v[g][0] = lo[0]; v[g][1] = lo[1]; v[g][2] = lo[2]; v[g][3] = lo[3];
-      v[g][4] = hi[0]; v[g][5] = hi[1]; v[g][6] = hi[2]; v[g][7] = hi[3];
-    }
+  for (int r0 = 16 * wave; r0 < C::BM; r0 += 64) {
     if (k <= 8)
-      lm_select_rows<8>(v, row, col0, vocab, k, n, cand, tm.cb, tc);
+      lm_select_quad<32, 8>(so + r0 * C::SLD, C::SLD, m0 + r0, n0, vocab, k, n, cand, tm.cb, tc);
     else
-      lm_select_rows<16>(v, row, col0, vocab, k, n, cand, tm.cb, tc);
+      lm_select_quad<32, 16>(so + r0 * C::SLD, C::SLD, m0 + r0, n0, vocab, k, n, cand, tm.cb, tc);
+  }
+}
+
+// The same in the ping-pong core's tiles (64 QM rows x 256 columns, bf16), one row half of
+// the tile staged at a time; k candidates per row and 256 columns.
+template <int QM>
+__global__ __launch_bounds__(512, 2) void lm_pp_kernel(LmMap tm, int n, const bf16_t* __restrict__ h, int d,
+                                                       const bf16_t* __restrict__ W, int vocab, int k,
+                                                       uint64_t* __restrict__ cand) {
+  using C = PpCfg<QM>;
+  __shared__ __align__(16) unsigned char smem[C::SMEM_BYTES];
+  int tr, tc;
+  if (!tm.map(tr, tc)) return;
+  const int m0 = tr * C::BM, n0 = tc * C::BN;
+  typename C::Acc acc;
+  pp_mainloop<C>(acc, h, d, n, W, d, vocab, d, m0, n0, smem);
+  float* so = reinterpret_cast<float*>(smem);
+  const int r0 = 16 * static_cast<int>(threadIdx.x >> 6);  // AH <= 128: at most 16 rows a wave
+#pragma unroll
+  for (int a = 0; a < 2; ++a) {
+    pp_stage<C>(acc, a, so);
+    __syncthreads();
+    const int m1 = m0 + a * C::AH + r0;
+    if (r0 < C::AH && m1 < n) {  // uniform over the wave
+      if (k <= 8)
+        lm_select_quad<64, 8>(so + r0 * C::SLD, C::SLD, m1, n0, vocab, k, n, cand, tm.cb, tc);
+      else
+        lm_select_quad<64, 16>(so + r0 * C::SLD, C::SLD, m1, n0, vocab, k, n, cand, tm.cb, tc);
+    }
+    __syncthreads();
   }
 }
 

@@ -174,3 +174,23 @@ def test_lm_topk_host_errors(lib):
     assert e.value.status == lib.FOVEA_ERR_INVALID_ARG
     assert lib.fovea_lm_topk_workspace(fv.ctx, 4, 300, 17) == 0
     f(fv.ctx, 0, h, W, 300, 6, idx, None, ws)   # no rows: nothing to do
+
+
+@pytest.mark.parametrize("n,vocab,k", [
+    (65, 256, 1), (128, 257, 8), (129, 320, 9), (192, 511, 16), (193, 776, 6), (257, 513, 10), (300, 264, 16)])
+def test_lm_topk_wide_tiles(lib, n, vocab, k):
+    """Edges of the 128-, 192- and 256-row, 256-column tiles, last tiles of 1 to 255 columns
+    (fewer than k among them), rows of equal logits (zero states: the lowest ids) and rows whose
+    large logits are neighbours (one lane's columns)."""
+    h, W = make_lm_case(n, 128, vocab, "bf16", seed=n * 31 + k)
+    h[1] = 0.0
+    h[n - 1] = 0.0
+    W[64:128] += h[3] * 0.125   # row 3: 64 consecutive columns above all others
+    W = W.astype(np.float32).astype(np.float64)
+    W = torch.from_numpy(W).to(torch.bfloat16).double().numpy()
+    idx, val = _run(lib, h, W, k, "bf16")
+    z = oracle.lm_logits(h, W)
+    for r in (1, n - 1):
+        assert idx[r].tolist() == list(range(k)) and np.all(val[r] == 0.0)
+    keep = [r for r in range(n) if r not in (1, n - 1)]
+    assert check_topk(idx[keep], val[keep], z[keep], k) > 0.9

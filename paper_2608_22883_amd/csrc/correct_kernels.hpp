@@ -9,11 +9,11 @@
 namespace fovea {
 
 template <typename T>
-using Corr1Cfg = GemmCfg<T, 64, 4>;
+using Corr1Cfg = FwdCfg<T, 64>;
 template <typename T, int BM = 128>
-using Corr2Cfg = GemmCfg<T, BM, 2>;
+using Corr2Cfg = FwdCfg<T, BM, 2>;
 template <typename T, int BM>
-using MemCfg = GemmCfg<T, BM, 4>;
+using MemCfg = FwdCfg<T, BM>;
 constexpr int kPartCols = 128;  // columns reduced into one partial sum (one block tile)
 
 __host__ __device__ constexpr int n_parts(int cols) { return (cols + kPartCols - 1) / kPartCols; }
@@ -73,7 +73,7 @@ struct RowPart {  // part[row][tile] = sum (rows past n dropped)
 // corr1_combine_kernel with the same epilogue.
 template <typename T>
 __global__ __launch_bounds__(256) void corr1_kernel(TileMap tm, const T* __restrict__ rT, int d_m,
-                                                    const T* __restrict__ W1r, Corr1Epi<T> epi,
+                                                    const bf16_t* __restrict__ W1r, Corr1Epi<T> epi,
                                                     float* __restrict__ gate_part, int ks,
                                                     float* __restrict__ part) {
   using C = Corr1Cfg<T>;
@@ -82,7 +82,7 @@ __global__ __launch_bounds__(256) void corr1_kernel(TileMap tm, const T* __restr
   if (!tm.map(tr, tc)) return;
   const int m0 = tr * C::BM, n0 = tc * C::BN;
   if (ks > 1) {
-    gemm_splitk_partial<C>(rT, d_m, epi.n, W1r, d_m, epi.N, d_m, ks, m0, n0, part, smem);
+    gemm_splitk_partial<C>(rT, epi.n, W1r, epi.N, d_m, ks, m0, n0, part, smem);
     return;
   }
   // each thread's P for the epilogue (8 fp32 per epilogue group, rows and columns clamped
@@ -99,7 +99,7 @@ __global__ __launch_bounds__(256) void corr1_kernel(TileMap tm, const T* __restr
     ppre[gi][1] = *reinterpret_cast<const f32x4*>(pp + 4);
   }
   f32x4 acc[C::TM][C::TN];
-  gemm_mainloop<C>(acc, rT, d_m, epi.n, W1r, d_m, epi.N, d_m, m0, n0, smem);
+  fwd_mainloop<C>(acc, rT, epi.n, W1r, epi.N, d_m, 0, d_m, m0, n0, smem);
   gemm_epilogue<C>(
       acc, smem, m0, n0,
       [&](int row, int col0, const float(&v)[8], int gi) -> float {
@@ -175,7 +175,7 @@ __device__ __forceinline__ void stage_gates(const Corr2Args& ca, int n, int m0, 
 
 template <typename T, int BM = 128>
 __global__ __launch_bounds__(256) void corr2_kernel(TileMap tm, const T* __restrict__ a_c,
-                                                    const T* __restrict__ Wc2, Corr2Epi<T> epi,
+                                                    const bf16_t* __restrict__ Wc2, Corr2Epi<T> epi,
                                                     Corr2Args ca, int ks, float* __restrict__ part) {
   using C = Corr2Cfg<T, BM>;
   static_assert(C::SMEM_BYTES >= C::OUT_BYTES + C::BM * 4, "gate staging");
@@ -184,11 +184,11 @@ __global__ __launch_bounds__(256) void corr2_kernel(TileMap tm, const T* __restr
   if (!tm.map(tr, tc)) return;
   const int m0 = tr * C::BM, n0 = tc * C::BN;
   if (ks > 1) {
-    gemm_splitk_partial<C>(a_c, ca.d_c, epi.n, Wc2, ca.d_c, epi.d, ca.d_c, ks, m0, n0, part, smem);
+    gemm_splitk_partial<C>(a_c, epi.n, Wc2, epi.d, ca.d_c, ks, m0, n0, part, smem);
     return;
   }
   f32x4 acc[C::TM][C::TN];
-  gemm_mainloop<C>(acc, a_c, ca.d_c, epi.n, Wc2, ca.d_c, epi.d, ca.d_c, m0, n0, smem);
+  fwd_mainloop<C>(acc, a_c, epi.n, Wc2, epi.d, ca.d_c, 0, ca.d_c, m0, n0, smem);
   // gate of each row of the tile, next to the epilogue's staging area
   float* sg = reinterpret_cast<float*>(smem + C::OUT_BYTES);
   stage_gates(ca, epi.n, m0, C::BM, tc == 0, sg);
@@ -325,14 +325,14 @@ struct MemEpi {
 
 template <typename T, int BM>
 __global__ __launch_bounds__(256) void mem_proj_kernel(TileMap tm, const T* __restrict__ V, int d_v,
-                                                       const T* __restrict__ Wku, MemEpi<T> epi) {
+                                                       const bf16_t* __restrict__ Wku, MemEpi<T> epi) {
   using C = MemCfg<T, BM>;
   __shared__ __align__(16) unsigned char smem[C::SMEM_BYTES];
   int tr, tc;
   if (!tm.map(tr, tc)) return;
   const int m0 = tr * C::BM, n0 = tc * C::BN;
   f32x4 acc[C::TM][C::TN];
-  gemm_mainloop<C>(acc, V, d_v, epi.n, Wku, d_v, 2 * epi.d_m, d_v, m0, n0, smem);
+  fwd_mainloop<C>(acc, V, epi.n, Wku, 2 * epi.d_m, d_v, 0, d_v, m0, n0, smem);
   gemm_epilogue<C>(acc, smem, m0, n0, epi, NoRowSum{});
 }
 
@@ -354,22 +354,41 @@ __global__ __launch_bounds__(512, 2) void mem_proj_pp_kernel(TileMap tm, const b
 // context packing
 // ---------------------------------------------------------------------------------
 
-// out[i][j] = W[i][j] * g[j], rounded once to the storage dtype (the product of two
-// bf16 values is exact in fp32).
+// Packed GEMM operand rows: out[i][j] = W[i ldw + j] (* g[j] if given), rounded once to the
+// storage dtype (the product of two bf16 values is exact in fp32); bf16 rows cols apart,
+// fp32 as three bf16 planes, rows 3 cols apart.  cols a multiple of 64.
 template <typename T>
-__global__ void fold_gain_kernel(const T* __restrict__ W, const T* __restrict__ g, int64_t rows,
-                                 int cols, T* __restrict__ out) {
-  const int64_t total = rows * cols;
+__global__ void pack_rows_kernel(const T* __restrict__ W, int64_t ldw, const T* __restrict__ g, int64_t rows,
+                                 int cols, bf16_t* __restrict__ out) {
+  const int64_t total = rows * (cols / 8);
+  const bool aligned = ((reinterpret_cast<uintptr_t>(W) | static_cast<uintptr_t>(ldw * sizeof(T))) & 15u) == 0;
   for (int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; i < total;
-       i += static_cast<int64_t>(gridDim.x) * blockDim.x)
-    st_f32(out, i, Elem<T>::to_f32(W[i]) * Elem<T>::to_f32(g[i % cols]));
+       i += static_cast<int64_t>(gridDim.x) * blockDim.x) {
+    const int64_t r = i / (cols / 8);
+    const int j = static_cast<int>(i % (cols / 8)) * 8;
+    float x[8];
+    if (aligned)
+      load8(W + r * ldw + j, x);
+    else
+#pragma unroll
+      for (int e = 0; e < 8; ++e) x[e] = Elem<T>::to_f32(W[r * ldw + j + e]);
+    if (g != nullptr)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) x[e] *= Elem<T>::to_f32(g[j + e]);
+    if constexpr (std::is_same<T, bf16_t>::value)
+      store8(out + r * cols + j, x);
+    else
+      store_planes8<3>(out + r * 3 * cols, j, x);
+  }
 }
 
-// out[l][i] = sum_j W[i][j] * (b[j] + (E ? E[l][j] : 0)), or sum_j W[i][j] when b is
-// null; fp64 accumulation, one wave per (l, i).
+// out[l][i] = sum_j W[i][j] * (b[j] + (E ? E[l][j] : 0)), or sum_j W[i][j] g[j] (the product
+// rounded to the storage dtype, as packed) when b is null; fp64 accumulation, one wave per
+// (l, i).
 template <typename T>
 __global__ void row_dot_kernel(const T* __restrict__ W, int rows, int cols, const T* __restrict__ b,
-                               const T* __restrict__ E, int n_l, float* __restrict__ out) {
+                               const T* __restrict__ E, const T* __restrict__ g, int n_l,
+                               float* __restrict__ out) {
   const int lane = threadIdx.x & 63;
   const int item = blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6);
   if (item >= rows * n_l) return;
@@ -377,11 +396,13 @@ __global__ void row_dot_kernel(const T* __restrict__ W, int rows, int cols, cons
   const T* wr = W + static_cast<int64_t>(i) * cols;
   double s = 0.0;
   for (int j = lane; j < cols; j += 64) {
-    double x = 1.0;
-    if (b != nullptr) {
-      x = static_cast<double>(Elem<T>::to_f32(b[j]));
-      if (E != nullptr) x += static_cast<double>(Elem<T>::to_f32(E[static_cast<int64_t>(l) * cols + j]));
+    if (b == nullptr) {
+      const T w = Elem<T>::from_f32(Elem<T>::to_f32(wr[j]) * Elem<T>::to_f32(g[j]));
+      s += static_cast<double>(Elem<T>::to_f32(w));
+      continue;
     }
+    double x = static_cast<double>(Elem<T>::to_f32(b[j]));
+    if (E != nullptr) x += static_cast<double>(Elem<T>::to_f32(E[static_cast<int64_t>(l) * cols + j]));
     s += static_cast<double>(Elem<T>::to_f32(wr[j])) * x;
   }
   s = wave_sum(s);

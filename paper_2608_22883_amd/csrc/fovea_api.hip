@@ -34,6 +34,7 @@ struct fovea_ctx {
   void* block;  // one allocation holding every packed array below
   float* q_c1;  // [d_m] row sums of the folded W_Q
   float* q_c2;  // [n_depth, d_m] W_Q (q_ln_b + E_dep[l])
+  // GEMM weights: bf16, or for fp32 three bf16 planes (gemm.hpp)
   void* W_KU;   // [2 d_m, d_v] [W_K ; W_U] diag(mem_ln_g)
   float* m_c1;  // [2 d_m]
   float* m_c2;  // [2 d_m] [W_K ; W_U] mem_ln_b
@@ -243,41 +244,33 @@ fovea_status pack_weights(fovea_ctx* c, const fovea_params* p, hipStream_t s) {
   const fovea_dims& D = c->dims;
   const int d = D.d, d_v = D.d_v, d_m = D.d_m, d_c = D.d_c;
   auto T_ = [](const void* x) { return static_cast<const T*>(x); };
-  // folded projections
-  hipLaunchKernelGGL(fold_gain_kernel<T>, dim3(1024), dim3(256), 0, s, T_(p->W_Q), T_(p->q_ln_g),
-                     static_cast<int64_t>(d_m), d, static_cast<T*>(c->W_hq));
-  hipLaunchKernelGGL(fold_gain_kernel<T>, dim3(1024), dim3(256), 0, s, T_(p->W_K), T_(p->mem_ln_g),
-                     static_cast<int64_t>(d_m), d_v, static_cast<T*>(c->W_KU));
-  hipLaunchKernelGGL(fold_gain_kernel<T>, dim3(1024), dim3(256), 0, s, T_(p->W_U), T_(p->mem_ln_g),
-                     static_cast<int64_t>(d_m), d_v, static_cast<T*>(c->W_KU) + static_cast<int64_t>(d_m) * d_v);
+  // GEMM operands: the folded projections, and the first layer of both nets split by input:
+  // the h half joins W_Q in the hidden-state GEMM, the r half is its own GEMM
+  const int64_t pl = std::is_same<T, bf16_t>::value ? 1 : 3;  // stored bf16 planes per weight
+  auto pack = [&](const void* W, int64_t ldw, const void* g, int64_t rows, int cols, void* out, int64_t row0) {
+    hipLaunchKernelGGL(pack_rows_kernel<T>, dim3(1024), dim3(256), 0, s, T_(W), ldw, T_(g), rows, cols,
+                       static_cast<bf16_t*>(out) + row0 * cols * pl);
+  };
+  pack(p->W_Q, d, p->q_ln_g, d_m, d, c->W_hq, 0);
+  pack(p->W_c1, d + d_m, nullptr, d_c, d, c->W_hq, d_m);
+  pack(p->W_g1, d + d_m, nullptr, d_c, d, c->W_hq, static_cast<int64_t>(d_m) + d_c);
+  pack(p->W_K, d_v, p->mem_ln_g, d_m, d_v, c->W_KU, 0);
+  pack(p->W_U, d_v, p->mem_ln_g, d_m, d_v, c->W_KU, d_m);
+  pack(T_(p->W_c1) + d, d + d_m, nullptr, d_c, d_m, c->W1r, 0);
+  pack(T_(p->W_g1) + d, d + d_m, nullptr, d_c, d_m, c->W1r, d_c);
+  pack(p->W_c2, d_c, nullptr, d, d_c, c->W_c2, 0);
   // row sums of the folded weights and the bias / depth terms
-  auto rows = [](int items) { return dim3((items + 3) / 4); };
-  hipLaunchKernelGGL(row_dot_kernel<T>, rows(d_m), dim3(256), 0, s, static_cast<const T*>(c->W_hq),
-                     d_m, d, static_cast<const T*>(nullptr), static_cast<const T*>(nullptr), 1, c->q_c1);
-  hipLaunchKernelGGL(row_dot_kernel<T>, rows(d_m * D.n_depth), dim3(256), 0, s, T_(p->W_Q), d_m, d,
-                     T_(p->q_ln_b), T_(p->E_dep), D.n_depth, c->q_c2);
-  hipLaunchKernelGGL(row_dot_kernel<T>, rows(2 * d_m), dim3(256), 0, s, static_cast<const T*>(c->W_KU),
-                     2 * d_m, d_v, static_cast<const T*>(nullptr), static_cast<const T*>(nullptr), 1, c->m_c1);
-  hipLaunchKernelGGL(row_dot_kernel<T>, rows(d_m), dim3(256), 0, s, T_(p->W_K), d_m, d_v,
-                     T_(p->mem_ln_b), static_cast<const T*>(nullptr), 1, c->m_c2);
-  hipLaunchKernelGGL(row_dot_kernel<T>, rows(d_m), dim3(256), 0, s, T_(p->W_U), d_m, d_v,
-                     T_(p->mem_ln_b), static_cast<const T*>(nullptr), 1, c->m_c2 + d_m);
-  // correction / gate nets
-  const size_t es = sizeof(T);
-  // first layer of both nets split by input: the h half joins W_Q in the hidden-state
-  // GEMM, the r half is its own GEMM
-  const size_t src_pitch = static_cast<size_t>(d + d_m) * es;
-  char* hq_rows = static_cast<char*>(c->W_hq) + static_cast<size_t>(d_m) * d * es;
-  FOVEA_HIP(hipMemcpy2DAsync(hq_rows, d * es, p->W_c1, src_pitch, d * es, d_c, hipMemcpyDeviceToDevice, s));
-  FOVEA_HIP(hipMemcpy2DAsync(hq_rows + static_cast<size_t>(d_c) * d * es, d * es, p->W_g1, src_pitch,
-                             d * es, d_c, hipMemcpyDeviceToDevice, s));
-  FOVEA_HIP(hipMemcpy2DAsync(c->W1r, d_m * es, static_cast<const char*>(p->W_c1) + d * es, src_pitch,
-                             d_m * es, d_c, hipMemcpyDeviceToDevice, s));
-  FOVEA_HIP(hipMemcpy2DAsync(static_cast<char*>(c->W1r) + static_cast<size_t>(d_c) * d_m * es,
-                             d_m * es, static_cast<const char*>(p->W_g1) + d * es, src_pitch,
-                             d_m * es, d_c, hipMemcpyDeviceToDevice, s));
-  FOVEA_HIP(hipMemcpyAsync(c->W_c2, p->W_c2, static_cast<size_t>(d) * d_c * es,
-                           hipMemcpyDeviceToDevice, s));
+  auto dots = [&](const void* W, int rows, int cols, const void* b, const void* E, const void* g, int n_l,
+                  float* out) {
+    hipLaunchKernelGGL(row_dot_kernel<T>, dim3((rows * n_l + 3) / 4), dim3(256), 0, s, T_(W), rows, cols, T_(b),
+                       T_(E), T_(g), n_l, out);
+  };
+  dots(p->W_Q, d_m, d, nullptr, nullptr, p->q_ln_g, 1, c->q_c1);
+  dots(p->W_Q, d_m, d, p->q_ln_b, p->E_dep, nullptr, D.n_depth, c->q_c2);
+  dots(p->W_K, d_m, d_v, nullptr, nullptr, p->mem_ln_g, 1, c->m_c1);
+  dots(p->W_U, d_m, d_v, nullptr, nullptr, p->mem_ln_g, 1, c->m_c1 + d_m);
+  dots(p->W_K, d_m, d_v, p->mem_ln_b, nullptr, nullptr, 1, c->m_c2);
+  dots(p->W_U, d_m, d_v, p->mem_ln_b, nullptr, nullptr, 1, c->m_c2 + d_m);
   hipLaunchKernelGGL(to_f32_kernel<T>, dim3(8), dim3(256), 0, s, T_(p->b_c1), d_c, c->b1);
   hipLaunchKernelGGL(to_f32_kernel<T>, dim3(8), dim3(256), 0, s, T_(p->b_g1), d_c, c->b1 + d_c);
   hipLaunchKernelGGL(to_f32_kernel<T>, dim3(64), dim3(256), 0, s, T_(p->b_c2), d, c->b_c2);
@@ -317,7 +310,7 @@ fovea_status run_build(fovea_ctx* c, int n, const void* V, void* keys, void* val
   epi.values = static_cast<T*>(values);
   const int N = 2 * D.d_m;
   const T* Vt = static_cast<const T*>(V);
-  const T* Wku = static_cast<const T*>(c->W_KU);
+  const bf16_t* Wku = static_cast<const bf16_t*>(c->W_KU);
   auto map = [&](int bm, int bn) {
     return make_tile_map((n + bm - 1) / bm, (N + bn - 1) / bn, static_cast<double>(n) * D.d_v,
                          static_cast<double>(N) * D.d_v);
@@ -506,7 +499,7 @@ fovea_status run_retrieve_fuse(fovea_ctx* c, const RFArgs& a, hipStream_t s) {
       nm.err = c->err;
     }
     hipLaunchKernelGGL((a.n <= 64 ? hq_kernel<T, 64> : hq_kernel<T>), dim3(tile_grid(tm), ks),
-                       dim3(C::NT), 0, s, tm, a.n, h, D.d, static_cast<const T*>(c->W_hq), epi, ks, splitk,
+                       dim3(C::NT), 0, s, tm, a.n, h, D.d, static_cast<const bf16_t*>(c->W_hq), epi, ks, splitk,
                        stat_part, nm);
     if (ks > 1)
       hipLaunchKernelGGL(hq_combine_kernel<T>, dim3((N + 127) / 128, (a.n + 15) / 16), dim3(256), 0, s,
@@ -618,7 +611,7 @@ fovea_status run_retrieve_fuse(fovea_ctx* c, const RFArgs& a, hipStream_t s) {
     epi.a_c = a_c;
     ProfScope ps(pc, kCorr1, s);
     hipLaunchKernelGGL(corr1_kernel<T>, dim3(tile_grid(tm), ksp.c1), dim3(C::NT), 0, s, tm, rT, D.d_m,
-                       static_cast<const T*>(c->W1r), epi, gate_part, ksp.c1, splitk);
+                       static_cast<const bf16_t*>(c->W1r), epi, gate_part, ksp.c1, splitk);
     if (ksp.c1 > 1)
       hipLaunchKernelGGL(corr1_combine_kernel<T>, dim3((epi.N + 127) / 128, (a.n + 15) / 16), dim3(256), 0,
                          s, epi, gate_part, ksp.c1, static_cast<const float*>(splitk));
@@ -649,7 +642,7 @@ fovea_status run_retrieve_fuse(fovea_ctx* c, const RFArgs& a, hipStream_t s) {
     {
       ProfScope ps(pc, kCorr2, s);
       hipLaunchKernelGGL((a.n <= 64 ? corr2_kernel<T, 64> : corr2_kernel<T>), dim3(tile_grid(tm), ksp.c2),
-                         dim3(C::NT), 0, s, tm, a_c, static_cast<const T*>(c->W_c2), epi, ca, ksp.c2,
+                         dim3(C::NT), 0, s, tm, a_c, static_cast<const bf16_t*>(c->W_c2), epi, ca, ksp.c2,
                          splitk);
       if (ksp.c2 > 1 && !fused_rms)
         hipLaunchKernelGGL(corr2_combine_kernel<T>, dim3((D.d + 127) / 128, (a.n + 15) / 16), dim3(256), 0, s,
@@ -1296,16 +1289,17 @@ fovea_status fovea_create(fovea_ctx** out, const fovea_dims* dims, const fovea_p
     return FOVEA_ERR_DEVICE;
   }
   const int64_t d = dims->d, d_v = dims->d_v, d_m = dims->d_m, d_c = dims->d_c, nd = dims->n_depth;
+  const size_t wb = c->bf16 ? 2 : 6;  // bytes per packed GEMM weight: bf16, or three bf16 planes of fp32
   size_t o = 0;
-  const size_t oWhq = o; o = align_up(o + (d_m + 2 * d_c) * d * c->es);
+  const size_t oWhq = o; o = align_up(o + (d_m + 2 * d_c) * d * wb);
   const size_t oQc1 = o; o = align_up(o + d_m * 4);
   const size_t oQc2 = o; o = align_up(o + nd * d_m * 4);
-  const size_t oWKU = o; o = align_up(o + 2 * d_m * d_v * c->es);
+  const size_t oWKU = o; o = align_up(o + 2 * d_m * d_v * wb);
   const size_t oMc1 = o; o = align_up(o + 2 * d_m * 4);
   const size_t oMc2 = o; o = align_up(o + 2 * d_m * 4);
-  const size_t oW1r = o; o = align_up(o + 2 * d_c * d_m * c->es);
+  const size_t oW1r = o; o = align_up(o + 2 * d_c * d_m * wb);
   const size_t oB1 = o; o = align_up(o + 2 * d_c * 4);
-  const size_t oWc2 = o; o = align_up(o + d * d_c * c->es);
+  const size_t oWc2 = o; o = align_up(o + d * d_c * wb);
   const size_t oBc2 = o; o = align_up(o + d * 4);
   const size_t oWg2 = o; o = align_up(o + d_c * 4);
   const size_t oRms = o; o = align_up(o + d * 4);

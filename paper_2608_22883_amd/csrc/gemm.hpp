@@ -28,6 +28,7 @@
 #pragma once
 
 #include <type_traits>
+#include <utility>
 
 #include "common.hpp"
 
@@ -653,23 +654,290 @@ inline int pp_rows(int64_t M, int64_t N) {
   return best;
 }
 
+// ---------------------------------------------------------------------------------
+// GEMM over fp32 operands on the bf16 matrix cores.
+//
+// x = x0 + x1 (+ x2) with x0 = bf16(x), x1 = bf16(x - x0), x2 = bf16(x - x0 - x1).  Two
+// planes leave 2^-16 |x| and take three products (00, 10, 01); three planes hold all 24
+// bits and take the six products of weight 2^-16 or more (00, 01, 10, 11, 02, 20): what is
+// left out is below fp32's own rounding, and the matrix cores round once per 32 products,
+// so the sum is closer to 64 bits than fp32 MFMA's (1920 x 2048 x 4096: 1.0e-6 against
+// 1.2e-6).
+//   B comes as planes, [row][K / 32][plane][32]: 64 P bytes hold 32 k of a row in every
+// plane, one LDS row of a k-tile, so that a loaded tile serves all products (three copies
+// of K in one ordinary GEMM load and read half as much again).  A comes as planes too, or
+// as fp32 rows whose fragments each wave splits in registers between the products, which
+// costs neither a pass over A nor room for its planes.
+//   128 (or 64) x 128 tiles, 2 x 2 waves.  Step kt multiplies the fragments of k-tile kt,
+// all in registers, and between the products reads those of kt + 1 and loads k-tile
+// kt + NST into the stage that kt left; one barrier per step.  Bound by the matrix cores:
+// three planes 1920 x 2048 x 4096 147 us (1314 TFLOP/s of bf16 products) against 292 us
+// on fp32 MFMA; two planes 87 us.
+// ---------------------------------------------------------------------------------
+template <int P_, int BM_, bool AF32_>
+struct SplitCfg {
+  static constexpr int P = P_, BM = BM_, BN = 128, WM = 2, WN = 2;
+  static constexpr bool AF32 = AF32_;
+  static constexpr int NT = WM * WN * kWave;
+  static constexpr int TM = BM / WM / 16, TN = BN / WN / 16;
+  static constexpr int CHA = AF32 ? 8 : 4 * P, CHB = 4 * P;  // 16-byte chunks of an LDS row (32 k)
+  static constexpr int NST = BM == 128 && P == 3 ? 3 : 4;
+  static constexpr int A_BYTES = BM * CHA * 16;
+  static constexpr int STAGE_BYTES = A_BYTES + BN * CHB * 16;
+  static constexpr int LA = BM * CHA / 64, LB = BN * CHB / 64;  // direct-to-LDS loads of a k-tile
+  static constexpr int NI = (LA + LB) / 4;                      // per wave
+  static constexpr int SROWS = TM * 16, SLD = BN + 4, OUT_BYTES = SROWS * SLD * 4;
+  static constexpr int PIPE_BYTES = NST * STAGE_BYTES;
+  static constexpr int SMEM_BYTES = PIPE_BYTES > OUT_BYTES ? PIPE_BYTES : OUT_BYTES;
+  static_assert((P == 2 || P == 3) && (BM == 64 || BM == 128), "planes, rows");
+  static_assert((LA + LB) % 4 == 0 && SMEM_BYTES <= 160 * 1024, "loads, LDS");
+  // slot of chunk c in row r of CH chunks: 16 rows' reads of one chunk fall on distinct banks
+  template <int CH>
+  __device__ static int slot(int c, int r) {
+    if constexpr (CH == 8) return c ^ ((r >> 1) & 7);
+    const int s = c + ((r >> 2) & 3);
+    return s >= CH ? s - CH : s;
+  }
+  template <int CH>
+  __device__ static int chunk(int s, int r) {  // the chunk held by slot s of row r
+    if constexpr (CH == 8) return s ^ ((r >> 1) & 7);
+    const int c = s - ((r >> 2) & 3);
+    return c < 0 ? c + CH : c;
+  }
+};
+
+// Element offset of column k in a row of planes (plane 0; plane p is 32 p further).
+template <int P>
+__host__ __device__ __forceinline__ int64_t plane_col(int64_t k) {
+  return (k >> 5) * (32 * P) + (k & 31);
+}
+
+// Two values into P packed planes.  The first plane saturates at the largest bf16, so that
+// a finite value never becomes infinite (an infinite one ends as NaN).
+template <int P>
+__device__ __forceinline__ void split_pair(float x, float y, uint32_t (&out)[P]) {
+  constexpr float kBig = 3.3895313892515355e38f;
+#pragma unroll
+  for (int p = 0; p < P; ++p) {
+    const uint32_t w = p == 0 ? pack_bf16x2(__builtin_amdgcn_fmed3f(x, -kBig, kBig),
+                                            __builtin_amdgcn_fmed3f(y, -kBig, kBig))
+                              : pack_bf16x2(x, y);
+    out[p] = w;
+    if (p + 1 < P) {
+      x -= __uint_as_float(w << 16);
+      y -= __uint_as_float(w & 0xffff0000u);
+    }
+  }
+}
+
+// Eight consecutive columns k .. k + 7 (k a multiple of 8) of a row of planes.
+template <int P>
+__device__ __forceinline__ void store_planes8(bf16_t* row, int64_t k, const float (&x)[8]) {
+  u32x4 w[P];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    uint32_t o[P];
+    split_pair<P>(x[2 * e], x[2 * e + 1], o);
+#pragma unroll
+    for (int p = 0; p < P; ++p) w[p][e] = o[p];
+  }
+#pragma unroll
+  for (int p = 0; p < P; ++p) *reinterpret_cast<u32x4*>(row + plane_col<P>(k) + 32 * p) = w[p];
+}
+
+// f(integral_constant 0), .., f(integral_constant N - 1)
+template <class F, int... I>
+__device__ __forceinline__ void static_for_seq(F&& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>()), ...);
+}
+
+template <int N, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  static_for_seq(f, std::make_integer_sequence<int, N>());
+}
+
+// acc = A B^T over the k-tiles [kt0, kt1) of 32 columns.  A: fp32 rows lda apart, or planes;
+// B: planes, rows ldb elements apart.
+template <class C, typename TA>
+__device__ __forceinline__ void split_mainloop(f32x4 (&acc)[C::TM][C::TN], const TA* __restrict__ A,
+                                               int64_t lda, int M, const bf16_t* __restrict__ Bw,
+                                               int64_t ldb, int N, int kt0, int kt1, int m0, int n0,
+                                               unsigned char* smem) {
+  static_assert(std::is_same<TA, float>::value == C::AF32, "operand A");
+  constexpr int P = C::P, TM = C::TM, TN = C::TN, NST = C::NST, NI = C::NI;
+  constexpr int RA = C::AF32 ? 2 * TM : P * TM;        // LDS reads of A per step
+  constexpr int NR = RA + P * TN;
+  constexpr int NP = P == 2 ? 3 : 6;                   // products
+  constexpr int PA[6] = {0, P == 2 ? 1 : 0, P == 2 ? 0 : 1, 1, 0, 2};
+  constexpr int PB[6] = {0, P == 2 ? 0 : 1, P == 2 ? 1 : 0, 1, 2, 0};
+  constexpr int NM = NP * TM * TN;                     // MFMAs per step
+  constexpr int NO = NR + NI, OP = NO / NI;            // reads and loads of a step, one load in OP
+  constexpr int SPREAD = NM - NM / 4;
+  constexpr int NC = C::AF32 ? 4 * TM : 0;             // pairs per lane to split
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+  const int wm = wave / C::WN, wn = wave % C::WN;
+  zero_acc<C>(acc);
+  const int nk = kt1 - kt0;
+  constexpr int SA = C::AF32 ? 128 : 64 * P, SB = 64 * P;  // bytes of a row per k-tile
+  const char* gp[NI];
+  int dp[NI];
+#pragma unroll
+  for (int u = 0; u < NI; ++u) {
+    const int j = wave * NI + u;  // uniform: the first LA loads are A's
+    if (j < C::LA) {
+      const int l = j * 64 + lane, row = l / C::CHA;
+      const int c = C::template chunk<C::CHA>(l % C::CHA, row);
+      gp[u] = reinterpret_cast<const char*>(A + static_cast<int64_t>(min(m0 + row, M - 1)) * lda) +
+              static_cast<int64_t>(kt0) * SA + c * 16;
+      dp[u] = j * 1024;
+    } else {
+      const int l = (j - C::LA) * 64 + lane, row = l / C::CHB;
+      const int c = C::template chunk<C::CHB>(l % C::CHB, row);
+      gp[u] = reinterpret_cast<const char*>(Bw + static_cast<int64_t>(min(n0 + row, N - 1)) * ldb) +
+              static_cast<int64_t>(kt0) * SB + c * 16;
+      dp[u] = j * 1024;
+    }
+  }
+  static_assert(C::LA * 1024 == C::A_BYTES, "B follows A");
+  int fa[C::AF32 ? 2 : P], fb[P];
+  const int r = lane & 15, kg = lane >> 4;
+#pragma unroll
+  for (int p = 0; p < (C::AF32 ? 2 : P); ++p) {
+    const int c = C::AF32 ? 2 * kg + p : 4 * p + kg;
+    fa[p] = ((wm * TM * 16 + r) * C::CHA + C::template slot<C::CHA>(c, r)) * 16;
+  }
+#pragma unroll
+  for (int p = 0; p < P; ++p)
+    fb[p] = C::A_BYTES + ((wn * TN * 16 + r) * C::CHB + C::template slot<C::CHB>(4 * p + kg, r)) * 16;
+  auto issue = [&](int kt, int st, int u) {
+    const int64_t step = (C::AF32 && wave * NI + u < C::LA) ? SA : SB;
+    load_lds16(reinterpret_cast<const bf16_t*>(gp[u] + min(kt, nk - 1) * step), smem + st * C::STAGE_BYTES + dp[u]);
+  };
+  bf16x8 af[2][P][TM], bf[2][P][TN];
+  f32x4 raw[C::AF32 ? TM : 1][2];
+  // read f of a step: A's first, then B's plane by plane
+  auto read_frag = [&](const unsigned char* sp, int f, bf16x8 (&a)[P][TM], bf16x8 (&b)[P][TN]) {
+    if (f < RA) {
+      if constexpr (C::AF32)
+        raw[f / 2][f % 2] = *reinterpret_cast<const f32x4*>(sp + fa[f % 2] + (f / 2) * 16 * C::CHA * 16);
+      else
+        a[f / TM][f % TM] = *reinterpret_cast<const bf16x8*>(sp + fa[f / TM] + (f % TM) * 16 * C::CHA * 16);
+    } else {
+      const int g = f - RA;
+      b[g / TN][g % TN] = *reinterpret_cast<const bf16x8*>(sp + fb[g / TN] + (g % TN) * 16 * C::CHB * 16);
+    }
+  };
+  // pair c of the next k-tile's A fragments into planes
+  auto split_frag = [&](int c, bf16x8 (&a)[P][TM]) {
+    if constexpr (C::AF32) {
+      const int i = c / 4, e = c % 4;
+      uint32_t o[P];
+      split_pair<P>(raw[i][e / 2][2 * (e % 2)], raw[i][e / 2][2 * (e % 2) + 1], o);
+#pragma unroll
+      for (int p = 0; p < P; ++p) {
+        u32x4 t = __builtin_bit_cast(u32x4, a[p][i]);
+        t[e] = o[p];
+        a[p][i] = __builtin_bit_cast(bf16x8, t);
+      }
+    }
+  };
+  // the splits run in the second half of a step, when the reads of A have returned
+  constexpr int C0 = NM / 2, CSTEP = NC > 0 ? (NM - C0) / NC : 1;
+  int st = 0;  // stage of the k-tile being multiplied
+  auto step = [&](int kt, auto S) {
+    constexpr int set = decltype(S)::value;
+    const int sn = st + 1 == NST ? 0 : st + 1;
+    const unsigned char* sp = smem + sn * C::STAGE_BYTES;
+    static_for<NM>([&](auto M_) {
+      constexpr int m = decltype(M_)::value;
+      constexpr int pr = m / (TM * TN), i = (m / TN) % TM, j = m % TN;
+      mfma_bf16_16x16x32_acc(acc[i][j], af[set][PA[pr]][i], bf[set][PB[pr]][j]);
+      // the reads and loads are spread evenly over the first SPREAD products (a read after
+      // every product would ask more than the LDS delivers)
+      constexpr int o0 = (m * NO + SPREAD - 1) / SPREAD, o1 = ((m + 1) * NO + SPREAD - 1) / SPREAD;
+      static_for<(o1 < NO ? o1 : NO) - (o0 < NO ? o0 : NO)>([&](auto O_) {
+        constexpr int o = o0 + decltype(O_)::value;
+        if constexpr (o % OP == OP - 1 && o / OP < NI)
+          issue(kt + NST, st, o / OP);
+        else
+          read_frag(sp, o - (o / OP < NI ? o / OP : NI), af[1 - set], bf[1 - set]);
+      });
+      if constexpr (m >= C0 && (m - C0) % CSTEP == 0 && (m - C0) / CSTEP < NC)
+        split_frag((m - C0) / CSTEP, af[1 - set]);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    // this wave has read k-tile kt + 1, and its loads of kt + 2 are done
+    __builtin_amdgcn_s_waitcnt(0xC07F);
+    wait_vmcnt<(NST - 2) * NI>();
+    lds_barrier();
+    st = sn;
+  };
+  // prologue: k-tiles 0 .. NST - 1; the fragments of k-tile 0
+#pragma unroll
+  for (int t = 0; t < NST; ++t)
+#pragma unroll
+    for (int u = 0; u < NI; ++u) issue(t, t, u);
+  wait_vmcnt<(NST - 1) * NI>();
+  lds_barrier();
+#pragma unroll
+  for (int f = 0; f < NR; ++f) read_frag(smem, f, af[0], bf[0]);
+#pragma unroll
+  for (int c = 0; c < NC; ++c) split_frag(c, af[0]);
+  __builtin_amdgcn_s_waitcnt(0xC07F);
+  wait_vmcnt<(NST - 2) * NI>();
+  lds_barrier();
+  int kt = 0;
+  for (; kt + 1 < nk; kt += 2) {
+    step(kt, std::integral_constant<int, 0>());
+    step(kt + 1, std::integral_constant<int, 1>());
+  }
+  if (kt < nk) step(kt, std::integral_constant<int, 0>());
+  wait_vmcnt<0>();  // the repeated loads land before the LDS is reused
+  mfma_results_ready();
+  lds_barrier();
+}
+
 struct NoRowSum {
   __device__ __forceinline__ void operator()(int, float) const {}
 };
+
+// The forward's GEMM core: bf16 storage on the bf16 core; fp32 storage with A as it is and
+// the packed weights B as three bf16 planes (rows 3 K apart).
+template <typename T, int BM, int NST>
+struct FwdCfg_ {
+  using type = SplitCfg<3, BM, true>;
+};
+template <int BM, int NST>
+struct FwdCfg_<bf16_t, BM, NST> {
+  using type = GemmCfg<bf16_t, BM, NST>;
+};
+template <typename T, int BM, int NST = 4>
+using FwdCfg = typename FwdCfg_<T, BM, NST>::type;
+
+// acc = A B^T over the columns [k0, k0 + Kc) of K (multiples of 64).
+template <class C, typename T>
+__device__ __forceinline__ void fwd_mainloop(f32x4 (&acc)[C::TM][C::TN], const T* A, int M,
+                                             const bf16_t* Bw, int N, int K, int k0, int Kc, int m0,
+                                             int n0, unsigned char* smem) {
+  if constexpr (std::is_same<T, bf16_t>::value)
+    gemm_mainloop<C>(acc, A + k0, K, M, Bw + k0, K, N, Kc, m0, n0, smem);
+  else
+    split_mainloop<C>(acc, A, K, M, Bw, 3 * static_cast<int64_t>(K), N, k0 / 32, (k0 + Kc) / 32, m0, n0, smem);
+}
 
 // Split-K for GEMMs with too few output tiles to fill the chip: block (tile, y) contracts
 // K slice y (Kc = K / ks columns, a multiple of BK) and stores its fp32 partial tile in
 // part[y][M][N]; a combine kernel then sums the slices in order and runs the fused
 // kernel's epilogue (splitk_combine), so the result does not depend on timing.
 template <class C, typename T>
-__device__ __forceinline__ void gemm_splitk_partial(const T* A, int64_t lda, int M, const T* Bw,
-                                                    int64_t ldb, int N, int K, int ks, int m0,
-                                                    int n0, float* __restrict__ part,
+__device__ __forceinline__ void gemm_splitk_partial(const T* A, int M, const bf16_t* Bw, int N, int K,
+                                                    int ks, int m0, int n0, float* __restrict__ part,
                                                     unsigned char* smem) {
   const int Kc = K / ks;
   const int k0 = static_cast<int>(blockIdx.y) * Kc;
   f32x4 acc[C::TM][C::TN];
-  gemm_mainloop<C>(acc, A + k0, lda, M, Bw + k0, ldb, N, Kc, m0, n0, smem);
+  fwd_mainloop<C>(acc, A, M, Bw, N, K, k0, Kc, m0, n0, smem);
   float* pp = part + static_cast<int64_t>(blockIdx.y) * M * N;
   gemm_epilogue<C>(
       acc, smem, m0, n0,

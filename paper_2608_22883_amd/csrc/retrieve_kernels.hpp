@@ -286,7 +286,7 @@ __device__ __forceinline__ void slice_row_stats(const T* __restrict__ h, int d, 
 // ---------------------------------------------------------------------------------
 
 template <typename T, int BM = 128>
-using HqCfg = GemmCfg<T, BM, 4>;
+using HqCfg = FwdCfg<T, BM>;
 
 // One GEMM over the hidden states for everything that depends on h alone:
 // columns [0, d_m) are the query projection (LayerNorm folded as described above),
@@ -344,7 +344,7 @@ struct HqEpi {
 // no separate statistics launch.
 template <typename T, int BM = 128>
 __global__ __launch_bounds__(256) void hq_kernel(TileMap tm, int n, const T* __restrict__ h, int d,
-                                                 const T* __restrict__ Whq, HqEpi<T> epi, int ks,
+                                                 const bf16_t* __restrict__ Whq, HqEpi<T> epi, int ks,
                                                  float* __restrict__ part,
                                                  float2* __restrict__ stat_part = nullptr,
                                                  NodeMapArgs nm = NodeMapArgs{}) {
@@ -354,7 +354,7 @@ __global__ __launch_bounds__(256) void hq_kernel(TileMap tm, int n, const T* __r
   if (!tm.map(tr, tc)) return;
   const int m0 = tr * C::BM, n0 = tc * C::BN;
   if (ks > 1) {
-    gemm_splitk_partial<C>(h, d, n, Whq, d, epi.N, d, ks, m0, n0, part, smem);
+    gemm_splitk_partial<C>(h, n, Whq, epi.N, d, ks, m0, n0, part, smem);
     if (stat_part != nullptr) {
       const int Kc = d / ks;
       slice_row_stats(h, d, n, m0, C::BM, tc, tm.cb, static_cast<int>(blockIdx.y) * Kc, Kc,
@@ -363,7 +363,7 @@ __global__ __launch_bounds__(256) void hq_kernel(TileMap tm, int n, const T* __r
     return;
   }
   f32x4 acc[C::TM][C::TN];
-  gemm_mainloop<C>(acc, h, d, n, Whq, d, epi.N, d, m0, n0, smem);
+  fwd_mainloop<C>(acc, h, n, Whq, epi.N, d, 0, d, m0, n0, smem);
   gemm_epilogue<C>(acc, smem, m0, n0, epi, NoRowSum{});
 }
 

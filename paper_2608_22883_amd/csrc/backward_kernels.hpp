@@ -696,44 +696,29 @@ __global__ __launch_bounds__(256) void colsum_multi_final_kernel(ColJobs jobs,
   out[j] = acc;
 }
 
-// fp32 operands as bf16 planes, for GEMMs on the bf16 matrix cores with close to fp32
-// accuracy: x = hi + lo + O(2^-16 |x|) with hi = bf16(x), lo = bf16(x - hi), and
-//   A B^T = A_hi B_hi^T + A_lo B_hi^T + A_hi B_lo^T + O(2^-16)
-// is one bf16 GEMM over a tripled K with A' = [A_hi | A_lo | A_hi] (pattern 0) and
-// B' = [B_hi | B_hi | B_lo] (pattern 1).  dst [R, 3 C] row-major.
-// Grid: (ceil(C / 1024), R); thread t of block (x, r) converts columns 4 (256 x + t) ..
-// + 3 of row r (C a multiple of 4, rows 16-byte aligned).
-__global__ __launch_bounds__(256) void split3_kernel(int R, int C, const float* __restrict__ src,
-                                                     int64_t lds, bf16_t* __restrict__ dst,
-                                                     int pattern) {
-  const int r = blockIdx.y;
-  const int c = 4 * (blockIdx.x * 256 + static_cast<int>(threadIdx.x));
-  if (r >= R || c >= C) return;
-  const f32x4 x = *reinterpret_cast<const f32x4*>(src + static_cast<int64_t>(r) * lds + c);
-  uint32_t hp[2], lp[2];
-#pragma unroll
-  for (int e = 0; e < 4; e += 2) {
-    const float h0 = bf16_round(x[e]), h1 = bf16_round(x[e + 1]);
-    hp[e / 2] = pack_bf16x2(h0, h1);
-    lp[e / 2] = pack_bf16x2(x[e] - h0, x[e + 1] - h1);
-  }
-  const uint2 hv = make_uint2(hp[0], hp[1]), lv = make_uint2(lp[0], lp[1]);
-  bf16_t* d = dst + static_cast<int64_t>(r) * 3 * C + c;
-  *reinterpret_cast<uint2*>(d) = hv;
-  *reinterpret_cast<uint2*>(d + C) = pattern == 0 ? lv : hv;
-  *reinterpret_cast<uint2*>(d + 2 * C) = pattern == 0 ? hv : lv;
+// fp32 rows as two bf16 planes (the split GEMM core's layout, dst rows 2 C apart): thread i
+// converts 8 consecutive columns (C a multiple of 32, rows 16-byte aligned).
+__global__ __launch_bounds__(256) void split_planes_kernel(int R, int C, const float* __restrict__ src,
+                                                           int64_t lds, bf16_t* __restrict__ dst) {
+  const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+  const int64_t r = i / (C / 8);
+  const int c = static_cast<int>(i % (C / 8)) * 8;
+  if (r >= R) return;
+  float x[8];
+  load8(src + r * lds + c, x);
+  store_planes8<2>(dst + r * 2 * C, c, x);
 }
 
-// The planes of src^T: row c of dst (3 W wide, planes W apart) holds column c of src
-// [R, C] (ld lds) at positions r_off .. r_off + R_pad - 1 of each plane (rows R .. R_pad - 1
-// zero), through 64 x 64 LDS tiles: the node-axis operands of the weight-gradient GEMMs
-// and the transposed weights.  Grid: (ceil(C / 64), ceil(R_pad / 64)).  Each thread
-// loads 16-byte row pieces and stores 8-byte plane pieces (four source rows): C, R_pad,
-// W, r_off and lds multiples of 4, src 16-byte and dst 8-byte aligned.
-__global__ __launch_bounds__(256) void transpose_split3_kernel(int R, int R_pad, int C,
+// The planes of src^T: row c of dst (2 W long) holds column c of src [R, C] (ld lds) at
+// columns r_off .. r_off + R_pad - 1 (rows R .. R_pad - 1 zero), through 64 x 64 LDS tiles:
+// the node-axis operands of the weight-gradient GEMMs and the transposed weights.  Grid:
+// (ceil(C / 64), ceil(R_pad / 64)).  Each thread loads 16-byte row pieces and stores 16-byte
+// plane pieces (eight source rows): C and lds multiples of 4, R_pad, W and r_off of 32, src
+// and dst 16-byte aligned.
+__global__ __launch_bounds__(256) void transpose_planes_kernel(int R, int R_pad, int C,
                                                                const float* __restrict__ src,
                                                                int64_t lds, bf16_t* __restrict__ dst,
-                                                               int W, int r_off, int pattern) {
+                                                               int W, int r_off) {
   __shared__ float t[64][65];
   const int c0 = blockIdx.x * 64, r0 = blockIdx.y * 64;
   const int tid = threadIdx.x;
@@ -751,34 +736,22 @@ __global__ __launch_bounds__(256) void transpose_split3_kernel(int R, int R_pad,
 #pragma unroll
     for (int e = 0; e < 4; ++e) t[(tid >> 4) + 16 * p][q + e] = v[p][e];
   __syncthreads();
-  // tile column (tid / 16) + 16 p (a row of dst), tile rows 4 (tid % 16) .. + 3
-  const int64_t ldd = 3 * static_cast<int64_t>(W);
+  // tile column (tid / 8) + 32 p (a row of dst), tile rows 8 (tid % 8) .. + 7
+  const int g = 8 * (tid & 7);
 #pragma unroll
-  for (int p = 0; p < 4; ++p) {
-    const int cl = (tid >> 4) + 16 * p, c = c0 + cl, r = r0 + q;
+  for (int p = 0; p < 2; ++p) {
+    const int cl = (tid >> 3) + 32 * p, c = c0 + cl, r = r0 + g;
     if (c < C && r < R_pad) {
-      float x[4];
+      float x[8];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) x[e] = t[q + e][cl];
-      uint32_t hp[2], lp[2];
-#pragma unroll
-      for (int e = 0; e < 4; e += 2) {
-        const float h0 = bf16_round(x[e]), h1 = bf16_round(x[e + 1]);
-        hp[e / 2] = pack_bf16x2(h0, h1);
-        lp[e / 2] = pack_bf16x2(x[e] - h0, x[e + 1] - h1);
-      }
-      const uint2 hv = make_uint2(hp[0], hp[1]), lv = make_uint2(lp[0], lp[1]);
-      bf16_t* d = dst + static_cast<int64_t>(c) * ldd + r_off + r;
-      *reinterpret_cast<uint2*>(d) = hv;
-      *reinterpret_cast<uint2*>(d + W) = pattern == 0 ? lv : hv;
-      *reinterpret_cast<uint2*>(d + 2 * W) = pattern == 0 ? hv : lv;
+      for (int e = 0; e < 8; ++e) x[e] = t[g + e][cl];
+      store_planes8<2>(dst + static_cast<int64_t>(c) * 2 * W, r_off + r, x);
     }
   }
 }
 
-// GEMM C = A B^T (A [M, K], B [N, K], K a multiple of the k-tile, N a multiple of 8) on
-// the gemm.hpp core, fp32 or bf16 operands (fp32 accumulation), with the epilogues the
-// backward needs.
+// GEMM C = A B^T over two-plane operands (A [M, K], B [N, K], K a multiple of 32, N of 8)
+// with the epilogues the backward needs.
 enum BwdEpi : int {
   kEpiStore = 0,  // out = v (+ bias[col])
   kEpiZ = 1,      // out = v + bias (pre-activation), out2 = SiLU(out)
@@ -789,11 +762,8 @@ enum BwdEpi : int {
 
 struct BwdGemm {
   int M, N, K;
-  const void* A;  // fp32, or bf16 planes when bf16
-  int64_t lda;
-  const void* B;
-  int64_t ldb;
-  bool bf16;
+  const bf16_t* A;  // planes
+  const bf16_t* B;
   float* out;
   int64_t ldo;
   const float* bias;   // nullable
@@ -805,19 +775,16 @@ struct BwdGemm {
   int split;
 };
 
-template <typename T, int BM>
-using BwdCfg = GemmCfg<T, BM, 4>;
-
-template <int EPI, typename T, int BM>
+template <int EPI, int BM>
 __global__ __launch_bounds__(256) void bwd_gemm_kernel(TileMap tm, BwdGemm g) {
-  using C = BwdCfg<T, BM>;
+  using C = SplitCfg<2, BM, false>;
   __shared__ __align__(16) unsigned char smem[C::SMEM_BYTES];
   int tr, tc;
   if (!tm.map(tr, tc)) return;
   const int m0 = tr * C::BM, n0 = tc * C::BN;
   f32x4 acc[C::TM][C::TN];
-  gemm_mainloop<C>(acc, static_cast<const T*>(g.A), g.lda, g.M, static_cast<const T*>(g.B), g.ldb,
-                   g.N, g.K, m0, n0, smem);
+  const int64_t ld = 2 * static_cast<int64_t>(g.K);
+  split_mainloop<C>(acc, g.A, ld, g.M, g.B, ld, g.N, 0, g.K / 32, m0, n0, smem);
   gemm_epilogue<C>(
       acc, smem, m0, n0,
       [&](int row, int col0, const float(&v)[8]) -> float {

@@ -763,15 +763,15 @@ BwdLayout bwd_layout(const fovea_dims& D, int B, int n, int k_max, int m_max) {
   // column-sum partials: b_c2, b_c1, b_g1, w_g2 and rms_w one slot each; dxe two plus
   // one per depth
   L.part = take(static_cast<size_t>(kColChunks) * (d * (D.n_depth + 4) + 3 * dc) * 4);
-  // bf16 planes of the largest A and B operand of the backward's GEMMs ([rows, 3 K])
+  // two bf16 planes of the largest A and B operand of the backward's GEMMs ([rows, 2 K])
   const size_t mk[] = {nn * d, nn * (d + dm), nn * dc, nn * 2 * dc, nn * dm, d * np, 2 * dc * np, dm * np};
   const size_t nk[] = {dm * d, 2 * dc * (d + dm), d * dc, dc * d, (d + dm) * 2 * dc, d * dm,
                        dc * np, (d + dm) * np, d * np};
   size_t ma = 0, mb = 0;
   for (size_t v : mk) ma = std::max(ma, v);
   for (size_t v : nk) mb = std::max(mb, v);
-  L.sa = take(ma * 3 * 2);
-  L.sb = take(mb * 3 * 2);
+  L.sa = take(ma * 2 * 2);
+  L.sb = take(mb * 2 * 2);
   L.total = o;
   return L;
 }
@@ -811,91 +811,69 @@ void launch_transpose(int R, int R_pad, int C, const float* src, int64_t lds, fl
                      R, R_pad, C, src, lds, dst, ldd);
 }
 
-template <int EPI, typename T, int BM>
+template <int EPI, int BM>
 void launch_bwd_gemm_bm(const BwdGemm& g, hipStream_t s) {
-  using C = BwdCfg<T, BM>;
-  const TileMap tm = make_tile_map((g.M + C::BM - 1) / C::BM, (g.N + C::BN - 1) / C::BN,
-                                   static_cast<double>(g.M) * g.K, static_cast<double>(g.N) * g.K);
-  hipLaunchKernelGGL((bwd_gemm_kernel<EPI, T, BM>), dim3(tile_grid(tm)), dim3(C::NT), 0, s, tm, g);
+  const TileMap tm = make_tile_map((g.M + BM - 1) / BM, (g.N + 127) / 128, static_cast<double>(g.M) * g.K,
+                                   static_cast<double>(g.N) * g.K);
+  hipLaunchKernelGGL((bwd_gemm_kernel<EPI, BM>), dim3(tile_grid(tm)), dim3(256), 0, s, tm, g);
 }
 
-// 64-row tiles, or 128-row ones where they take fewer rounds of the 256 compute units
-// at about 1.5 times the time of a 64-row tile per round (bf16 operands only)
+// 64- or 128-row tiles, whichever takes less time over its rounds of the 256 compute
+// units (a k-tile of 32: 0.58 us with 128 rows, 0.33 with 64)
 template <int EPI>
 void launch_bwd_gemm(const BwdGemm& g, hipStream_t s) {
   auto rounds = [&](int bm) {
     const int64_t tiles = static_cast<int64_t>((g.M + bm - 1) / bm) * ((g.N + 127) / 128);
     return (tiles + 255) / 256;
   };
-  if (!g.bf16)
-    launch_bwd_gemm_bm<EPI, float, 64>(g, s);
-  else if (3 * rounds(128) < 2 * rounds(64))
-    launch_bwd_gemm_bm<EPI, bf16_t, 128>(g, s);
+  if (58 * rounds(128) < 33 * rounds(64))
+    launch_bwd_gemm_bm<EPI, 128>(g, s);
   else
-    launch_bwd_gemm_bm<EPI, bf16_t, 64>(g, s);
+    launch_bwd_gemm_bm<EPI, 64>(g, s);
 }
 
-void launch_split3(int R, int C, const float* src, int64_t lds, bf16_t* dst, int pattern,
-                   hipStream_t s) {
-  hipLaunchKernelGGL(split3_kernel, dim3((C + 1023) / 1024, R), dim3(256), 0, s, R, C, src, lds, dst,
-                     pattern);
+void launch_split(int R, int C, const float* src, int64_t lds, bf16_t* dst, hipStream_t s) {
+  const int64_t items = static_cast<int64_t>(R) * (C / 8);
+  hipLaunchKernelGGL(split_planes_kernel, dim3(static_cast<unsigned>((items + 255) / 256)), dim3(256), 0, s, R, C,
+                     src, lds, dst);
 }
 
-BwdGemm bwd_gemm(int M, int N, int K, const float* A, int64_t lda, const float* B, int64_t ldb,
-                 float* out, int64_t ldo) {
+void launch_transpose_split(int R, int R_pad, int C, const float* src, int64_t lds, bf16_t* dst,
+                            int W, int r_off, hipStream_t s) {
+  hipLaunchKernelGGL(transpose_planes_kernel, dim3((C + 63) / 64, (R_pad + 63) / 64), dim3(256), 0, s,
+                     R, R_pad, C, src, lds, dst, W, r_off);
+}
+
+// A GEMM over planes already in sa (A, [M, 2 K]) and sb (B, [N, 2 K]).
+BwdGemm planes_gemm(int M, int N, int K, const bf16_t* sa, const bf16_t* sb, float* out, int64_t ldo) {
   BwdGemm g{};
   g.M = M;
   g.N = N;
   g.K = K;
-  g.A = A;
-  g.lda = lda;
-  g.B = B;
-  g.ldb = ldb;
+  g.A = sa;
+  g.B = sb;
   g.out = out;
   g.ldo = ldo;
   return g;
 }
 
-void launch_transpose_split3(int R, int R_pad, int C, const float* src, int64_t lds, bf16_t* dst,
-                             int W, int r_off, int pattern, hipStream_t s) {
-  hipLaunchKernelGGL(transpose_split3_kernel, dim3((C + 63) / 64, (R_pad + 63) / 64), dim3(256), 0, s,
-                     R, R_pad, C, src, lds, dst, W, r_off, pattern);
-}
-
-// A GEMM over bf16 planes already in sa (A', [M, 3 K]) and sb (B', [N, 3 K]).
-BwdGemm planes_gemm(int M, int N, int K, bf16_t* sa, bf16_t* sb, float* out, int64_t ldo) {
-  BwdGemm g = bwd_gemm(M, N, 3 * K, nullptr, 3 * K, nullptr, 3 * K, out, ldo);
-  g.A = sa;
-  g.B = sb;
-  g.bf16 = true;
-  return g;
-}
-
-// Splits A [M, K] and B [N, K] (fp32) into bf16 planes in sa / sb and returns the GEMM
-// over them (K' = 3 K); the caller launches it before the next split reuses sa / sb.
+// Splits A [M, K] and B [N, K] (fp32) into planes in sa / sb and returns the GEMM over
+// them; the caller launches it before the next split reuses sa / sb.
 BwdGemm split_gemm(int M, int N, int K, const float* A, int64_t lda, const float* B, int64_t ldb,
                    float* out, int64_t ldo, bf16_t* sa, bf16_t* sb, hipStream_t s) {
-  launch_split3(M, K, A, lda, sa, 0, s);
-  launch_split3(N, K, B, ldb, sb, 1, s);
-  BwdGemm g = bwd_gemm(M, N, 3 * K, nullptr, 3 * K, nullptr, 3 * K, out, ldo);
-  g.A = sa;
-  g.B = sb;
-  g.bf16 = true;
-  return g;
+  launch_split(M, K, A, lda, sa, s);
+  launch_split(N, K, B, ldb, sb, s);
+  return planes_gemm(M, N, K, sa, sb, out, ldo);
 }
 
 // The weight-gradient GEMM dW = X^T Y over the node axis: X [n, M] (ld ldx) and
-// Y [n, N] (ld ldy) are transposed into bf16 planes (K = n_pad) in sa / sb.
+// Y [n, N] (ld ldy) are transposed into planes (K = n_pad) in sa / sb.
 BwdGemm split_gemm_nodes(int n, int n_pad, int M, int N, const float* X, int64_t ldx,
                          const float* Y, int64_t ldy, float* out, int64_t ldo, bf16_t* sa,
                          bf16_t* sb, hipStream_t s) {
-  launch_transpose_split3(n, n_pad, M, X, ldx, sa, n_pad, 0, 0, s);
-  launch_transpose_split3(n, n_pad, N, Y, ldy, sb, n_pad, 0, 1, s);
-  BwdGemm g = bwd_gemm(M, N, 3 * n_pad, nullptr, 3 * n_pad, nullptr, 3 * n_pad, out, ldo);
-  g.A = sa;
-  g.B = sb;
-  g.bf16 = true;
-  return g;
+  launch_transpose_split(n, n_pad, M, X, ldx, sa, n_pad, 0, s);
+  launch_transpose_split(n, n_pad, N, Y, ldy, sb, n_pad, 0, s);
+  return planes_gemm(M, N, n_pad, sa, sb, out, ldo);
 }
 
 // Column-sum jobs launched together (up to kColJobs per launch pair); every job's
@@ -1022,9 +1000,9 @@ fovea_status run_backward(fovea_ctx* c, const BwdArgs& a, hipStream_t s) {
     ProfScope ps(c, kBwdGemm, s);
     // layer 1 of both nets in one GEMM (2 d_c columns); the bias is [b_c1; b_g1]
     // B = [W_c1; W_g1], split straight from the two weights
-    launch_split3(n, d + dm, F(L.y), d + dm, sa, 0, s);
-    launch_split3(dc, d + dm, W_c1, d + dm, sb, 1, s);
-    launch_split3(dc, d + dm, W_g1, d + dm, sb + static_cast<int64_t>(dc) * 3 * (d + dm), 1, s);
+    launch_split(n, d + dm, F(L.y), d + dm, sa, s);
+    launch_split(dc, d + dm, W_c1, d + dm, sb, s);
+    launch_split(dc, d + dm, W_g1, d + dm, sb + static_cast<int64_t>(dc) * 2 * (d + dm), s);
     BwdGemm g = planes_gemm(n, 2 * dc, d + dm, sa, sb, F(L.z), 2 * dc);
     g.bias = static_cast<const float*>(a.P->b_c1);
     g.bias2 = static_cast<const float*>(a.P->b_g1);
@@ -1045,16 +1023,16 @@ fovea_status run_backward(fovea_ctx* c, const BwdArgs& a, hipStream_t s) {
   {
     ProfScope ps(c, kBwdGemm, s);
     // B = W_c2^T, transposed straight into its planes
-    launch_split3(n, d, F(L.dc), d, sa, 0, s);
-    launch_transpose_split3(d, d, dc, W_c2, dc, sb, d, 0, 1, s);
+    launch_split(n, d, F(L.dc), d, sa, s);
+    launch_transpose_split(d, d, dc, W_c2, dc, sb, d, 0, s);
     BwdGemm g = planes_gemm(n, dc, d, sa, sb, F(L.dz), 2 * dc);
     g.aux = F(L.z);
     g.ldaux = 2 * dc;
     launch_bwd_gemm<kEpiDsilu>(g, s);
     // B = [W_c1; W_g1]^T: the two weights transposed side by side along K
-    launch_split3(n, 2 * dc, F(L.dz), 2 * dc, sa, 0, s);
-    launch_transpose_split3(dc, dc, d + dm, W_c1, d + dm, sb, 2 * dc, 0, 1, s);
-    launch_transpose_split3(dc, dc, d + dm, W_g1, d + dm, sb, 2 * dc, dc, 1, s);
+    launch_split(n, 2 * dc, F(L.dz), 2 * dc, sa, s);
+    launch_transpose_split(dc, dc, d + dm, W_c1, d + dm, sb, 2 * dc, 0, s);
+    launch_transpose_split(dc, dc, d + dm, W_g1, d + dm, sb, 2 * dc, dc, s);
     BwdGemm g2 = planes_gemm(n, d + dm, 2 * dc, sa, sb, a.dh, d);
     g2.split = d;
     g2.out2 = F(L.dr);
@@ -1073,8 +1051,8 @@ fovea_status run_backward(fovea_ctx* c, const BwdArgs& a, hipStream_t s) {
   }
   {
     ProfScope ps(c, kBwdGemm, s);
-    launch_split3(n, dm, F(L.dq), dm, sa, 0, s);
-    launch_transpose_split3(dm, dm, d, W_Q, d, sb, dm, 0, 1, s);
+    launch_split(n, dm, F(L.dq), dm, sa, s);
+    launch_transpose_split(dm, dm, d, W_Q, d, sb, dm, 0, s);
     launch_bwd_gemm<kEpiStore>(planes_gemm(n, d, dm, sa, sb, F(L.dxe), d), s);
   }
   {
@@ -1154,8 +1132,8 @@ MemBwdLayout mem_bwd_layout(const fovea_dims& D, int64_t n) {
   L.WKT = take(dv * dm * 4);
   L.WUT = take(dv * dm * 4);
   L.part = take(static_cast<size_t>(kColChunks) * 2 * dv * 4);
-  L.sa = take(std::max(dm * np, nn * dm) * 3 * 2);
-  L.sb = take(std::max(dv * np, dv * dm) * 3 * 2);
+  L.sa = take(std::max(dm * np, nn * dm) * 2 * 2);
+  L.sb = take(std::max(dv * np, dv * dm) * 2 * 2);
   L.total = o;
   return L;
 }

@@ -112,58 +112,76 @@ __global__ __launch_bounds__(256) void fill_f32_kernel(int64_t count, float* __r
     p[i] = v;
 }
 
-// dst[c * ldd + r] = src[r * lds + c] for r < R, and 0 for R <= r < R_pad (c < C);
-// 64 x 64 tiles through LDS.  Grid: (ceil(C / 64), ceil(R_pad / 64)).
-__global__ __launch_bounds__(256) void transpose_f32_kernel(int R, int R_pad, int C,
-                                                            const float* __restrict__ src,
-                                                            int64_t lds, float* __restrict__ dst,
-                                                            int64_t ldd) {
-  __shared__ float t[64][65];
-  const int c0 = blockIdx.x * 64, r0 = blockIdx.y * 64;
-  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-  for (int i = ty; i < 64; i += 4) {
-    const int r = r0 + i, c = c0 + tx;
-    t[i][tx] = (r < R && c < C) ? src[static_cast<int64_t>(r) * lds + c] : 0.f;
-  }
-  __syncthreads();
-  for (int i = ty; i < 64; i += 4) {
-    const int c = c0 + i, r = r0 + tx;
-    if (c < C && r < R_pad) dst[static_cast<int64_t>(c) * ldd + r] = t[tx][i];
-  }
+// Four consecutive floats, 16-byte aligned only if vec.
+__device__ __forceinline__ f32x4 load4(const float* p, bool vec) {
+  if (vec) return *reinterpret_cast<const f32x4*>(p);
+  return f32x4{p[0], p[1], p[2], p[3]};
 }
 
-// Per node: xhat and xe = xhat g_q + b_q + E_dep[l], and h into y[:, :d] (ld d + d_m).
-// Rows of nodes that failed validation are written as zeros.
-__global__ __launch_bounds__(256) void bwd_prep_kernel(int n, int d, int d_m,
-                                                       const float* __restrict__ h,
-                                                       const float2* __restrict__ stats,
-                                                       const int32_t* __restrict__ node_req,
-                                                       const int32_t* __restrict__ depth, int n_depth,
-                                                       const float* __restrict__ g_q,
-                                                       const float* __restrict__ b_q,
-                                                       const float* __restrict__ E_dep,
-                                                       float* __restrict__ xhat,
-                                                       float* __restrict__ xe,
-                                                       float* __restrict__ y) {
+// Planes of the recomputed forward's two net layers (z and c): three, as exact as fp32, since
+// dL/db_g2 is one sum of both signs over every node of what c's error leaves; every other
+// product takes two.
+constexpr int kFwdPlanes = 3;
+
+// Four consecutive columns k .. k + 3 (k a multiple of 4) of a row of P planes.
+template <int P>
+__device__ __forceinline__ void store_planes4(bf16_t* row, int64_t k, const f32x4& x) {
+  uint32_t a[P], b[P];
+  split_pair<P>(x[0], x[1], a);
+  split_pair<P>(x[2], x[3], b);
+#pragma unroll
+  for (int p = 0; p < P; ++p)
+    *reinterpret_cast<uint2*>(row + plane_col<P>(k) + 32 * p) = make_uint2(a[p], b[p]);
+}
+
+// Rows of an fp32 matrix as a GEMM operand sees them: as they are, or with a LayerNorm
+// applied on the way ((x - mu) rstd g + b, plus the depth's row of E if given), so that the
+// normalised rows need not be stored.  Rows with ok < 0 (if given) are zero.
+struct RowSrc {
+  const float* x;
+  int64_t ld;
+  const float2* stats;    // nullable
+  const float* g;         // with stats
+  const float* b;
+  const float* E;         // nullable
+  const int32_t* depth;   // with E
+  int n_depth;
+  const int32_t* ok;      // nullable
+  bool vec;               // x, g, b and E 16-byte aligned, ld a multiple of 4
+  __device__ __forceinline__ f32x4 load(int r, int c, int cols) const {
+    if (ok != nullptr && ok[r] < 0) return f32x4{0.f, 0.f, 0.f, 0.f};
+    f32x4 v = load4(x + static_cast<int64_t>(r) * ld + c, vec);
+    if (stats != nullptr) {
+      const float2 st = stats[r];
+      const f32x4 gv = load4(g + c, vec);
+      f32x4 bv = load4(b + c, vec);
+      if (E != nullptr)
+        bv += load4(E + static_cast<int64_t>(min(max(depth[r], 0), n_depth - 1)) * cols + c, vec);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = fmaf((v[e] - st.x) * st.y, gv[e], bv[e]);
+    }
+    return v;
+  }
+};
+
+// Per node: the planes of xe = LN(h) + E_dep[l] and of h as the left part of y = [h; r]
+// (rows of kFwdPlanes (d + d_m)), four columns per thread and step.  Nodes that failed validation
+// are zeros.
+__global__ __launch_bounds__(256) void bwd_prep_kernel(int n, int d, int d_m, RowSrc xe, RowSrc h,
+                                                       bf16_t* __restrict__ xe_p,
+                                                       bf16_t* __restrict__ y_p) {
   const int row = blockIdx.x;
   if (row >= n) return;
-  const bool ok = node_req[row] >= 0;
-  const float2 st = stats[row];
-  const int l = min(max(depth[row], 0), n_depth - 1);
-  const float* hr = h + static_cast<int64_t>(row) * d;
-  const float* er = E_dep + static_cast<int64_t>(l) * d;
-  #pragma unroll 8
-  for (int j = threadIdx.x; j < d; j += 256) {
-    const float x = ok ? (hr[j] - st.x) * st.y : 0.f;
-    xhat[static_cast<int64_t>(row) * d + j] = x;
-    xe[static_cast<int64_t>(row) * d + j] = ok ? fmaf(x, g_q[j], b_q[j] + er[j]) : 0.f;
-    y[static_cast<int64_t>(row) * (d + d_m) + j] = ok ? hr[j] : 0.f;
+#pragma unroll 4
+  for (int j = 4 * threadIdx.x; j < d; j += 1024) {
+    store_planes4<2>(xe_p + static_cast<int64_t>(row) * 2 * d, j, xe.load(row, j, d));
+    store_planes4<kFwdPlanes>(y_p + static_cast<int64_t>(row) * kFwdPlanes * (d + d_m), j, h.load(row, j, d));
   }
 }
 
 // Per node (one block): validates its K and indices, then recomputes the renormalised
-// softmax over the selected entries (alpha [n, k_max]) and the readout r into
-// y[:, d:].  ok[n] = 0 marks a node that failed validation (here or in the statistics
+// softmax over the selected entries (alpha [n, k_max]) and the readout r [n, d_m], also as
+// the right part of y's planes.  ok[n] = 0 marks a node that failed validation (here or in the statistics
 // kernel); it contributes nothing to any gradient and its dh row becomes NaN.
 __global__ __launch_bounds__(256) void bwd_sel_fwd_kernel(int n, int d, int d_m, int k_max,
                                                           const NodeInfo* __restrict__ info,
@@ -173,7 +191,8 @@ __global__ __launch_bounds__(256) void bwd_sel_fwd_kernel(int n, int d, int d_m,
                                                           const float* __restrict__ keys,
                                                           const float* __restrict__ values,
                                                           float scale, float* __restrict__ alpha,
-                                                          float* __restrict__ y,
+                                                          float* __restrict__ r_out,
+                                                          bf16_t* __restrict__ y_p,
                                                           int32_t* __restrict__ ok_out,
                                                           uint32_t* err) {
   extern __shared__ float smem_f[];
@@ -229,14 +248,19 @@ __global__ __launch_bounds__(256) void bwd_sel_fwd_kernel(int n, int d, int d_m,
   __syncthreads();
   // r = sum alpha_i u_i, columns over the threads
   const int32_t* ixr = idx + static_cast<int64_t>(row) * k_max;
-  for (int j = 4 * tid; j < d_m; j += 1024)
-    *reinterpret_cast<f32x4*>(y + static_cast<int64_t>(row) * (d + d_m) + d + j) =
-        weighted_rows4(sa, ixr, K, values, ni.m0, d_m, j);
+  for (int j = 4 * tid; j < d_m; j += 1024) {
+    const f32x4 v = weighted_rows4(sa, ixr, K, values, ni.m0, d_m, j);
+    *reinterpret_cast<f32x4*>(r_out + static_cast<int64_t>(row) * d_m + j) = v;
+    store_planes4<kFwdPlanes>(y_p + static_cast<int64_t>(row) * kFwdPlanes * (d + d_m), d + j, v);
+  }
 }
 
 // Per node: gate, h' = h + g c, RMSNorm backward, the residual split and the gate's
-// backward.  Writes dh (= dh'), dc = g dh', hn = h' rho (for dL/drms_w), dlogit[row] and
-// dz[:, d_c:] = dlogit w_g2 SiLU'(z_g).  Nodes with ok = 0 get zero gradients.
+// backward.  Writes dh (= dh'), dc = g dh' (also as planes), hn = h' rho (for dL/drms_w),
+// dlogit[row] and dz[:, d_c:] = dlogit w_g2 SiLU'(z_g) (also as planes).  Nodes with ok = 0
+// get zero gradients.  A row of up to 1024 R columns stays in registers between the sums and
+// the outputs (1920 rows of 4096: 51.7 us reading it twice, 8 bytes a load).
+template <int R>
 __global__ __launch_bounds__(256) void bwd_rms_gate_kernel(int n, int d, int d_c,
                                                            const float* __restrict__ h,
                                                            const float* __restrict__ c,
@@ -248,27 +272,56 @@ __global__ __launch_bounds__(256) void bwd_rms_gate_kernel(int n, int d, int d_c
                                                            const int32_t* __restrict__ ok_in,
                                                            float* __restrict__ dh,
                                                            float* __restrict__ dc,
+                                                           bf16_t* __restrict__ dc_p,
                                                            float* __restrict__ hn,
                                                            float* __restrict__ dlogit,
-                                                           float* __restrict__ dz) {
+                                                           float* __restrict__ dz,
+                                                           bf16_t* __restrict__ dz_p) {
   __shared__ float red[4];
   const int row = blockIdx.x, tid = threadIdx.x;
   if (row >= n) return;
   const bool ok = ok_in[row] != 0;
   const int64_t ro = static_cast<int64_t>(row) * d;
   const int64_t zo = static_cast<int64_t>(row) * 2 * d_c;
+  constexpr f32x4 zero = f32x4{0.f, 0.f, 0.f, 0.f};
+  f32x4 hv[R], cv[R], gv[R];  // h then h', c, dh_hat
+  auto load = [&](int u, int j) {
+    hv[u] = *reinterpret_cast<const f32x4*>(h + ro + j);
+    cv[u] = *reinterpret_cast<const f32x4*>(c + ro + j);
+    gv[u] = *reinterpret_cast<const f32x4*>(dh_hat + ro + j);
+  };
+  const bool held = d <= 1024 * R;
+  if (held)
+#pragma unroll
+    for (int u = 0; u < R; ++u) {
+      hv[u] = cv[u] = gv[u] = zero;
+      if (4 * tid + 1024 * u < d) load(u, 4 * tid + 1024 * u);
+    }
   float t = 0.f;
-  #pragma unroll 8
+#pragma unroll 8
   for (int j = tid; j < d_c; j += 256) t = fmaf(a[zo + d_c + j], w_g2[j], t);
   const float g = sigmoid_f(block_sum256(t, red) + b_g2);
   float rho = 1.f, tw = 0.f;
   if (rms_w != nullptr) {
     float ss = 0.f, sw = 0.f;
-    #pragma unroll 8
-    for (int j = tid; j < d; j += 256) {
-      const float hp = fmaf(g, c[ro + j], h[ro + j]);
-      ss = fmaf(hp, hp, ss);
-      sw = fmaf(rms_w[j] * dh_hat[ro + j], hp, sw);
+    auto sums = [&](int u, int j) {
+      const f32x4 w = *reinterpret_cast<const f32x4*>(rms_w + j);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float hp = fmaf(g, cv[u][e], hv[u][e]);
+        ss = fmaf(hp, hp, ss);
+        sw = fmaf(w[e] * gv[u][e], hp, sw);
+      }
+    };
+    if (held) {
+#pragma unroll
+      for (int u = 0; u < R; ++u)
+        if (4 * tid + 1024 * u < d) sums(u, 4 * tid + 1024 * u);
+    } else {
+      for (int j = 4 * tid; j < d; j += 1024) {
+        load(0, j);
+        sums(0, j);
+      }
     }
     ss = block_sum256(ss, red);
     tw = block_sum256(sw, red);
@@ -276,28 +329,47 @@ __global__ __launch_bounds__(256) void bwd_rms_gate_kernel(int n, int d, int d_c
   }
   const float k3 = rho * rho * rho * tw / static_cast<float>(d);
   float sdg = 0.f;
-  #pragma unroll 8
-  for (int j = tid; j < d; j += 256) {
-    const float hp = fmaf(g, c[ro + j], h[ro + j]);
-    float dhp;
-    if (rms_w != nullptr) {
-      dhp = rho * rms_w[j] * dh_hat[ro + j] - k3 * hp;
-      hn[ro + j] = ok ? hp * rho : 0.f;
-    } else {
-      dhp = dh_hat[ro + j];
+  auto finish = [&](int u, int j) {
+    const f32x4 w = rms_w != nullptr ? *reinterpret_cast<const f32x4*>(rms_w + j) : zero;
+    f32x4 dhv, dcv, hnv;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float hp = fmaf(g, cv[u][e], hv[u][e]);
+      float dhp = rms_w != nullptr ? rho * w[e] * gv[u][e] - k3 * hp : gv[u][e];
+      dhp = ok ? dhp : 0.f;
+      hnv[e] = ok ? hp * rho : 0.f;
+      dhv[e] = dhp;
+      dcv[e] = g * dhp;
+      sdg = fmaf(dhp, cv[u][e], sdg);
     }
-    dhp = ok ? dhp : 0.f;
-    dh[ro + j] = dhp;
-    dc[ro + j] = g * dhp;
-    sdg = fmaf(dhp, c[ro + j], sdg);
+    if (rms_w != nullptr) *reinterpret_cast<f32x4*>(hn + ro + j) = hnv;
+    *reinterpret_cast<f32x4*>(dh + ro + j) = dhv;
+    *reinterpret_cast<f32x4*>(dc + ro + j) = dcv;
+    store_planes4<2>(dc_p + 2 * ro, j, dcv);
+  };
+  if (held) {
+#pragma unroll
+    for (int u = 0; u < R; ++u)
+      if (4 * tid + 1024 * u < d) finish(u, 4 * tid + 1024 * u);
+  } else {
+    for (int j = 4 * tid; j < d; j += 1024) {
+      load(0, j);
+      finish(0, j);
+    }
   }
   const float dl = block_sum256(sdg, red) * g * (1.0f - g);
   if (tid == 0) dlogit[row] = dl;
-  #pragma unroll 8
-  for (int j = tid; j < d_c; j += 256) dz[zo + d_c + j] = dl * w_g2[j] * dsilu_f(z[zo + d_c + j]);
+  for (int j = 4 * tid; j < d_c; j += 1024) {
+    const f32x4 zv = *reinterpret_cast<const f32x4*>(z + zo + d_c + j);
+    f32x4 v;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = dl * w_g2[j + e] * dsilu_f(zv[e]);
+    *reinterpret_cast<f32x4*>(dz + zo + d_c + j) = v;
+    store_planes4<2>(dz_p + 2 * zo, d_c + j, v);
+  }
 }
 
-// Per node: the readout and score backward.  dr [n, d_m]; writes dq [n, d_m] and the
+// Per node: the readout and score backward.  dr [n, d_m]; writes dq [n, d_m] (also as planes) and the
 // node's dense rows over its request's memory (m_max wide): wa = alpha_i and
 // ws = ds_i / sqrt(d_m) at the selected entries, 0 elsewhere (the selected indices are
 // distinct, as the forward produces them).
@@ -311,6 +383,7 @@ __global__ __launch_bounds__(256) void bwd_sel_kernel(int n, int d_m, int k_max,
                                                       const float* __restrict__ keys,
                                                       const float* __restrict__ values,
                                                       float scale, float* __restrict__ dq,
+                                                      bf16_t* __restrict__ dq_p,
                                                       float* __restrict__ wa,
                                                       float* __restrict__ ws) {
   extern __shared__ float smem_f[];
@@ -346,8 +419,9 @@ __global__ __launch_bounds__(256) void bwd_sel_kernel(int n, int d_m, int k_max,
   __syncthreads();
   for (int j = 4 * tid; j < d_m; j += 1024) {
     const f32x4 v = weighted_rows4(sds, ix, K, keys, m0, d_m, j);
-    *reinterpret_cast<f32x4*>(dq + static_cast<int64_t>(row) * d_m + j) =
-        f32x4{v[0] * scale, v[1] * scale, v[2] * scale, v[3] * scale};
+    const f32x4 o = f32x4{v[0] * scale, v[1] * scale, v[2] * scale, v[3] * scale};
+    *reinterpret_cast<f32x4*>(dq + static_cast<int64_t>(row) * d_m + j) = o;
+    store_planes4<2>(dq_p + static_cast<int64_t>(row) * 2 * d_m, j, o);
   }
 }
 
@@ -406,9 +480,11 @@ __global__ __launch_bounds__(256) void bwd_mem_grad_kernel(int d_m, int m_max, i
                                                            const float* __restrict__ q,
                                                            float* __restrict__ dkeys,
                                                            float* __restrict__ dvalues) {
-  extern __shared__ float smem_f[];  // [t_max][kMemRows] of wa, then of ws
+  // [t_max][kMemRows] of wa, then of ws, then each wave's list of nodes
+  extern __shared__ float smem_f[];
   float* swa = smem_f;
   float* sws = smem_f + t_max * kMemRows;
+  uint16_t* slist = reinterpret_cast<uint16_t*>(smem_f + 2 * t_max * kMemRows);
   const int b = blockIdx.z, r0 = blockIdx.y * kMemRows;
   const int64_t m0 = mem_off[b], m1 = mem_off[b + 1];
   const int t0 = node_off[b], t1 = node_off[b + 1];
@@ -438,9 +514,24 @@ __global__ __launch_bounds__(256) void bwd_mem_grad_kernel(int d_m, int m_max, i
     }
   }
   __syncthreads();
-  // wave w owns memory rows r0 + 8 w .. + 7; lane l owns columns j0 .. j0 + 3
-  const int wv = threadIdx.x >> 6;
-  const int j0 = blockIdx.x * 256 + 4 * (threadIdx.x & 63);
+  // wave w owns memory rows r0 + 8 w .. + 7; lane l owns columns j0 .. j0 + 3.  A node selects
+  // few entries (16 of 576, say), so most have none of the wave's rows: the wave lists those
+  // that have, in node order (their weights may still be 0 or NaN), and walks the list.
+  const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  uint16_t* list = slist + wv * t_max;
+  int nl = 0;
+  for (int tb = 0; tb < T; tb += 64) {
+    const int t = min(tb + lane, T - 1);
+    bool any = false;
+#pragma unroll
+    for (int r = 0; r < 8; ++r)
+      any |= !(swa[t * kMemRows + 8 * wv + r] == 0.f) || !(sws[t * kMemRows + 8 * wv + r] == 0.f);
+    const unsigned long long m = __ballot(any && tb + lane < T);
+    if (any && tb + lane < T) list[nl + __popcll(m & ((1ull << lane) - 1ull))] = static_cast<uint16_t>(t);
+    nl += __popcll(m);
+  }
+  wave_lds_sync();
+  const int j0 = blockIdx.x * 256 + 4 * lane;
   if (j0 >= d_m) return;
   float au[8][4], ak[8][4];
 #pragma unroll
@@ -450,28 +541,24 @@ __global__ __launch_bounds__(256) void bwd_mem_grad_kernel(int d_m, int m_max, i
       au[r][c] = 0.f;
       ak[r][c] = 0.f;
     }
-  // the node rows of dr and q come through a 4-deep register prefetch (a request
-  // without nodes skips the loop and writes zeros)
+  // the listed nodes' rows of dr and q come through a 4-deep register prefetch
   constexpr int PF = 4;
   f32x4 drb[PF], qb[PF];
-  if (T > 0) {
+  auto fetch = [&](int u, int i) {
+    const int64_t tt = t0 + list[min(i, nl - 1)];
+    drb[u] = *reinterpret_cast<const f32x4*>(dr + tt * d_m + j0);
+    qb[u] = *reinterpret_cast<const f32x4*>(q + tt * d_m + j0);
+  };
+  if (nl > 0) {
+#pragma unroll
+  for (int u = 0; u < PF; ++u) fetch(u, u);
+  for (int ib = 0; ib < nl; ib += PF) {
 #pragma unroll
   for (int u = 0; u < PF; ++u) {
-    const int tt = t0 + min(u, T - 1);
-    drb[u] = *reinterpret_cast<const f32x4*>(dr + static_cast<int64_t>(tt) * d_m + j0);
-    qb[u] = *reinterpret_cast<const f32x4*>(q + static_cast<int64_t>(tt) * d_m + j0);
-  }
-  for (int tb = 0; tb < T; tb += PF) {
-#pragma unroll
-  for (int u = 0; u < PF; ++u) {
-    const int t = tb + u;
-    if (t >= T) break;
+    if (ib + u >= nl) break;
+    const int t = list[ib + u];
     const f32x4 drv = drb[u], qv = qb[u];
-    {
-      const int tt = t0 + min(t + PF, T - 1);
-      drb[u] = *reinterpret_cast<const f32x4*>(dr + static_cast<int64_t>(tt) * d_m + j0);
-      qb[u] = *reinterpret_cast<const f32x4*>(q + static_cast<int64_t>(tt) * d_m + j0);
-    }
+    fetch(u, ib + u + PF);
     const f32x4 wa0 = *reinterpret_cast<const f32x4*>(swa + t * kMemRows + 8 * wv);
     const f32x4 wa1 = *reinterpret_cast<const f32x4*>(swa + t * kMemRows + 8 * wv + 4);
     const f32x4 ws0 = *reinterpret_cast<const f32x4*>(sws + t * kMemRows + 8 * wv);
@@ -498,52 +585,73 @@ __global__ __launch_bounds__(256) void bwd_mem_grad_kernel(int d_m, int m_max, i
   }
 }
 
-// Per node: dh += LayerNorm backward of dxe g_q (xhat, rstd); rows of nodes with
-// ok = 0 become NaN (ok_in null: every row is valid).
-__global__ __launch_bounds__(256) void bwd_ln_kernel(int n, int d, const float* __restrict__ dxe,
-                                                     const float* __restrict__ xhat,
-                                                     const float* __restrict__ g_q,
+// Per row: out (+)= LayerNorm backward of dx g, with xhat = (x - mu) rstd from the input
+// and its statistics; rows with ok = 0 become NaN (ok_in null: every row is valid).  Rows of
+// up to 1024 R columns are read once into registers.
+template <int R, bool ADD>
+__global__ __launch_bounds__(256) void bwd_ln_kernel(int n, int d, const float* __restrict__ dx,
+                                                     const float* __restrict__ x,
+                                                     const float* __restrict__ g, bool g_vec,
                                                      const float2* __restrict__ stats,
                                                      const int32_t* __restrict__ ok_in,
-                                                     float* __restrict__ dh) {
+                                                     float* __restrict__ out) {
   __shared__ float red[4];
   const int row = blockIdx.x, tid = threadIdx.x;
   if (row >= n) return;
   const int64_t ro = static_cast<int64_t>(row) * d;
+  const float2 st = stats[row];
+  f32x4 tv[R], xv[R], ov[R];
   float s1 = 0.f, s2 = 0.f;
-  #pragma unroll 8
-  for (int j = tid; j < d; j += 256) {
-    const float t = dxe[ro + j] * g_q[j];
-    s1 += t;
-    s2 = fmaf(t, xhat[ro + j], s2);
+  auto load = [&](int u, int j) {
+    tv[u] = *reinterpret_cast<const f32x4*>(dx + ro + j) * load4(g + j, g_vec);
+    xv[u] = *reinterpret_cast<const f32x4*>(x + ro + j);
+    if (ADD) ov[u] = *reinterpret_cast<const f32x4*>(out + ro + j);
+  };
+  auto sums = [&](int u) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      xv[u][e] = (xv[u][e] - st.x) * st.y;
+      s1 += tv[u][e];
+      s2 = fmaf(tv[u][e], xv[u][e], s2);
+    }
+  };
+  const bool held = d <= 1024 * R;
+  if (held) {
+#pragma unroll
+    for (int u = 0; u < R; ++u)
+      if (4 * tid + 1024 * u < d) load(u, 4 * tid + 1024 * u);
+#pragma unroll
+    for (int u = 0; u < R; ++u)
+      if (4 * tid + 1024 * u < d) sums(u);
+  } else {
+    for (int j = 4 * tid; j < d; j += 1024) {
+      load(0, j);
+      sums(0);
+    }
   }
   const float m1 = block_sum256(s1, red) / static_cast<float>(d);
   const float m2 = block_sum256(s2, red) / static_cast<float>(d);
-  const float rstd = stats[row].y;
   const bool ok = ok_in == nullptr || ok_in[row] != 0;
-  #pragma unroll 8
-  for (int j = tid; j < d; j += 256) {
-    const float t = dxe[ro + j] * g_q[j];
-    dh[ro + j] = ok ? dh[ro + j] + rstd * (t - m1 - xhat[ro + j] * m2) : __builtin_nanf("");
-  }
-}
-
-// Per row of the memory build's input: xhat = (v - mu) rstd and xn = xhat g + b.
-__global__ __launch_bounds__(256) void ln_apply_kernel(int n, int d, const float* __restrict__ x,
-                                                       const float2* __restrict__ stats,
-                                                       const float* __restrict__ g,
-                                                       const float* __restrict__ b,
-                                                       float* __restrict__ xhat,
-                                                       float* __restrict__ xn) {
-  const int row = blockIdx.x;
-  if (row >= n) return;
-  const float2 st = stats[row];
-  const int64_t ro = static_cast<int64_t>(row) * d;
-#pragma unroll 8
-  for (int j = threadIdx.x; j < d; j += 256) {
-    const float v = (x[ro + j] - st.x) * st.y;
-    xhat[ro + j] = v;
-    xn[ro + j] = fmaf(v, g[j], b[j]);
+  auto finish = [&](int u, int j) {
+    f32x4 o;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float v = st.y * (tv[u][e] - m1 - xv[u][e] * m2);
+      o[e] = ok ? (ADD ? ov[u][e] + v : v) : __builtin_nanf("");
+    }
+    *reinterpret_cast<f32x4*>(out + ro + j) = o;
+  };
+  if (held) {
+#pragma unroll
+    for (int u = 0; u < R; ++u)
+      if (4 * tid + 1024 * u < d) finish(u, 4 * tid + 1024 * u);
+  } else {
+    for (int j = 4 * tid; j < d; j += 1024) {
+      load(0, j);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) xv[0][e] = (xv[0][e] - st.x) * st.y;
+      finish(0, j);
+    }
   }
 }
 
@@ -588,6 +696,8 @@ struct ColJob {
   int64_t ldx;
   const float* Y;  // nullable (needed for out_xy)
   int64_t ldy;
+  const float2* ys;      // nullable: Y[i][j] stands for (Y[i][j] - ys[i].x) ys[i].y, 0 where yok[i] < 0
+  const int32_t* yok;    // nullable
   const float* rs;       // nullable
   const int32_t* grp;    // nullable (needed for out_grp)
   float* out_x;          // nullable
@@ -607,63 +717,71 @@ __device__ __forceinline__ int col_job_slots(const ColJob& jb) {
   return (jb.out_x != nullptr) + (jb.out_xy != nullptr) + (jb.out_grp != nullptr ? jb.ng : 0);
 }
 
-// Stage 1: grid (ceil(max cols / 1024), kColChunks, n_jobs); thread t of block x sums the
-// columns 4 (256 x + t) .. + 3 over the block's chunk of rows, eight rows in flight.
+// Stage 1: grid (ceil(max cols / 256), kColChunks, n_jobs); the block's 256 columns are four
+// per lane, its chunk of rows is split over the four waves (consecutive quarters, eight rows
+// in flight each), whose sums are added in wave order through LDS.  Bound by HBM; with a
+// block of 1024 columns per chunk one array of 4096 columns held one block per compute unit
+// (two arrays of 4608 x 4096: 58 us).
 __global__ __launch_bounds__(256) void colsum_multi_kernel(int n, ColJobs jobs,
                                                            float* __restrict__ part) {
+  __shared__ f32x4 red[3][64];
   const ColJob& jb = jobs.job[blockIdx.z];
-  const int j = 4 * (blockIdx.x * 256 + threadIdx.x);
-  if (j >= jb.cols) return;
-  const int per = (n + kColChunks - 1) / kColChunks;
-  const int i0 = blockIdx.y * per, i1 = min(n, i0 + per);
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+  if (static_cast<int>(blockIdx.x) * 256 >= jb.cols) return;  // uniform
+  const int j = 4 * (blockIdx.x * 64 + lane);
+  const int jc = min(j, jb.cols - 4);
+  const int per = (n + kColChunks - 1) / kColChunks, sub = (per + 3) / 4;
+  const int c0 = blockIdx.y * per, c1 = min(n, c0 + per);
+  const int i0 = c0 + wave * sub, i1 = min(c1, i0 + sub);
   const bool want_x = jb.out_x != nullptr, want_xy = jb.out_xy != nullptr,
              want_g = jb.out_grp != nullptr;
-  f32x4 ax = f32x4{0.f, 0.f, 0.f, 0.f}, axy = ax, ag[kColGroups];
+  constexpr f32x4 zero = f32x4{0.f, 0.f, 0.f, 0.f};
+  f32x4 acc[kColSlots];  // x, x y, then the groups
 #pragma unroll
-  for (int g = 0; g < kColGroups; ++g) ag[g] = ax;
+  for (int t = 0; t < kColSlots; ++t) acc[t] = zero;
   for (int ib = i0; ib < i1; ib += 8) {
     f32x4 x[8], y[8];
+    float sc[8], mu[8], rs[8];
+    int grp[8];
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      x[u] = f32x4{0.f, 0.f, 0.f, 0.f};
-      y[u] = x[u];
-      if (ib + u < i1) {
-        x[u] = *reinterpret_cast<const f32x4*>(jb.X + static_cast<int64_t>(ib + u) * jb.ldx + j);
-        if (want_xy) y[u] = *reinterpret_cast<const f32x4*>(jb.Y + static_cast<int64_t>(ib + u) * jb.ldy + j);
-      }
+      const int i = min(ib + u, i1 - 1);  // repeated rows are dropped below
+      x[u] = *reinterpret_cast<const f32x4*>(jb.X + static_cast<int64_t>(i) * jb.ldx + jc);
+      y[u] = want_xy ? *reinterpret_cast<const f32x4*>(jb.Y + static_cast<int64_t>(i) * jb.ldy + jc) : zero;
+      sc[u] = jb.rs != nullptr ? jb.rs[i] : 1.f;
+      mu[u] = jb.ys != nullptr ? jb.ys[i].x : 0.f;
+      rs[u] = jb.ys != nullptr ? jb.ys[i].y : 1.f;
+      if (jb.yok != nullptr && jb.yok[i] < 0) rs[u] = -1.f;  // (an rstd is positive or NaN)
+      grp[u] = want_g ? min(max(jb.grp[i], 0), jb.n_grp_total - 1) - jb.g0 : 0;
     }
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      if (ib + u < i1) {
-        const float sc = jb.rs != nullptr ? jb.rs[ib + u] : 1.f;
-        f32x4 v;
+      if (ib + u >= i1) break;  // uniform
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          v[c] = x[u][c] * sc;
-          ax[c] += v[c];
-          axy[c] = fmaf(v[c], y[u][c], axy[c]);
-        }
-        if (want_g) {
-          const int g = min(max(jb.grp[ib + u], 0), jb.n_grp_total - 1) - jb.g0;
+      for (int c = 0; c < 4; ++c) {
+        const float v = x[u][c] * sc[u];
+        const float yv = rs[u] < 0.f ? 0.f : (y[u][c] - mu[u]) * rs[u];
+        acc[0][c] += v;
+        acc[1][c] = fmaf(v, yv, acc[1][c]);
+        if (want_g)
 #pragma unroll
-          for (int gg = 0; gg < kColGroups; ++gg) {
-            const bool hit = gg == g;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) ag[gg][c] += hit ? v[c] : 0.f;
-          }
-        }
+          for (int g = 0; g < kColGroups; ++g) acc[2 + g][c] += g == grp[u] ? v : 0.f;
       }
     }
   }
   const int slots = col_job_slots(jb);
   float* pp = part + jb.part_off + static_cast<int64_t>(blockIdx.y) * slots * jb.cols + j;
   int sl = 0;
-  if (want_x) *reinterpret_cast<f32x4*>(pp + static_cast<int64_t>(sl++) * jb.cols) = ax;
-  if (want_xy) *reinterpret_cast<f32x4*>(pp + static_cast<int64_t>(sl++) * jb.cols) = axy;
-  if (want_g) {
 #pragma unroll
-    for (int g = 0; g < kColGroups; ++g)
-      if (g < jb.ng) *reinterpret_cast<f32x4*>(pp + static_cast<int64_t>(sl + g) * jb.cols) = ag[g];
+  for (int t = 0; t < kColSlots; ++t) {
+    if (t == 0 ? !want_x : t == 1 ? !want_xy : !(want_g && t - 2 < jb.ng)) continue;  // uniform
+    __syncthreads();
+    if (wave > 0) red[wave - 1][lane] = acc[t];
+    __syncthreads();
+    if (wave == 0 && j < jb.cols)
+      *reinterpret_cast<f32x4*>(pp + static_cast<int64_t>(sl) * jb.cols) =
+          ((acc[t] + red[0][lane]) + red[1][lane]) + red[2][lane];
+    ++sl;
   }
 }
 
@@ -696,29 +814,29 @@ __global__ __launch_bounds__(256) void colsum_multi_final_kernel(ColJobs jobs,
   out[j] = acc;
 }
 
-// fp32 rows as two bf16 planes (the split GEMM core's layout, dst rows 2 C apart): thread i
-// converts 8 consecutive columns (C a multiple of 32, rows 16-byte aligned).
+// fp32 rows as P bf16 planes (the split GEMM core's layout), at columns c_off .. of rows
+// of W columns: thread i converts 8 consecutive columns (C, W and c_off multiples of 32).
+template <int P>
 __global__ __launch_bounds__(256) void split_planes_kernel(int R, int C, const float* __restrict__ src,
-                                                           int64_t lds, bf16_t* __restrict__ dst) {
+                                                           int64_t lds, bf16_t* __restrict__ dst, int W,
+                                                           int c_off, bool vec) {
   const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
   const int64_t r = i / (C / 8);
   const int c = static_cast<int>(i % (C / 8)) * 8;
   if (r >= R) return;
-  float x[8];
-  load8(src + r * lds + c, x);
-  store_planes8<2>(dst + r * 2 * C, c, x);
+  const f32x4 a = load4(src + r * lds + c, vec), b = load4(src + r * lds + c + 4, vec);
+  const float x[8] = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+  store_planes8<P>(dst + r * P * W, c_off + c, x);
 }
 
-// The planes of src^T: row c of dst (2 W long) holds column c of src [R, C] (ld lds) at
-// columns r_off .. r_off + R_pad - 1 (rows R .. R_pad - 1 zero), through 64 x 64 LDS tiles:
-// the node-axis operands of the weight-gradient GEMMs and the transposed weights.  Grid:
-// (ceil(C / 64), ceil(R_pad / 64)).  Each thread loads 16-byte row pieces and stores 16-byte
-// plane pieces (eight source rows): C and lds multiples of 4, R_pad, W and r_off of 32, src
-// and dst 16-byte aligned.
-__global__ __launch_bounds__(256) void transpose_planes_kernel(int R, int R_pad, int C,
-                                                               const float* __restrict__ src,
-                                                               int64_t lds, bf16_t* __restrict__ dst,
-                                                               int W, int r_off) {
+// The planes of src^T: row c of dst (2 W long) holds column c of src [R, C] at columns
+// r_off .. r_off + R_pad - 1 (rows R .. R_pad - 1 zero), through 64 x 64 LDS tiles: the
+// node-axis operands of the weight-gradient GEMMs and the transposed weights.  Grid:
+// (ceil(C / 64), ceil(R_pad / 64)).  Each thread loads four columns of a row and stores
+// 16-byte plane pieces (eight source rows): C a multiple of 4, R_pad, W and r_off of 32.
+__global__ __launch_bounds__(256) void transpose_planes_kernel(int R, int R_pad, int C, RowSrc src,
+                                                               bf16_t* __restrict__ dst, int W,
+                                                               int r_off) {
   __shared__ float t[64][65];
   const int c0 = blockIdx.x * 64, r0 = blockIdx.y * 64;
   const int tid = threadIdx.x;
@@ -728,8 +846,7 @@ __global__ __launch_bounds__(256) void transpose_planes_kernel(int R, int R_pad,
 #pragma unroll
   for (int p = 0; p < 4; ++p) {
     const int r = r0 + (tid >> 4) + 16 * p, c = c0 + q;
-    v[p] = (r < R && c < C) ? *reinterpret_cast<const f32x4*>(src + static_cast<int64_t>(r) * lds + c)
-                            : f32x4{0.f, 0.f, 0.f, 0.f};
+    v[p] = (r < R && c < C) ? src.load(r, c, C) : f32x4{0.f, 0.f, 0.f, 0.f};
   }
 #pragma unroll
   for (int p = 0; p < 4; ++p)
@@ -750,12 +867,12 @@ __global__ __launch_bounds__(256) void transpose_planes_kernel(int R, int R_pad,
   }
 }
 
-// GEMM C = A B^T over two-plane operands (A [M, K], B [N, K], K a multiple of 32, N of 8)
+// GEMM C = A B^T over P-plane operands (A [M, K], B [N, K], K a multiple of 32, N of 8)
 // with the epilogues the backward needs.
 enum BwdEpi : int {
   kEpiStore = 0,  // out = v (+ bias[col])
-  kEpiZ = 1,      // out = v + bias (pre-activation), out2 = SiLU(out)
-  kEpiDsilu = 2,  // out = v * SiLU'(aux)
+  kEpiZ = 1,      // out = v + bias (pre-activation), out2 = SiLU(out), planes of out2[:, :split]
+  kEpiDsilu = 2,  // out = v * SiLU'(aux), also as planes
   kEpiSplit = 3,  // col < split: out[col] += v; else out2[col - split] = v
   kEpiRows = 4,   // row < split: out[row] = v; else out2[row - split] = v
 };
@@ -773,17 +890,19 @@ struct BwdGemm {
   const float* aux;
   int64_t ldaux;
   int split;
+  bf16_t* planes;  // Z, Dsilu: rows ldp elements apart
+  int64_t ldp;
 };
 
-template <int EPI, int BM>
+template <int EPI, int BM, int P>
 __global__ __launch_bounds__(256) void bwd_gemm_kernel(TileMap tm, BwdGemm g) {
-  using C = SplitCfg<2, BM, false>;
+  using C = SplitCfg<P, BM, false>;
   __shared__ __align__(16) unsigned char smem[C::SMEM_BYTES];
   int tr, tc;
   if (!tm.map(tr, tc)) return;
   const int m0 = tr * C::BM, n0 = tc * C::BN;
   f32x4 acc[C::TM][C::TN];
-  const int64_t ld = 2 * static_cast<int64_t>(g.K);
+  const int64_t ld = P * static_cast<int64_t>(g.K);
   split_mainloop<C>(acc, g.A, ld, g.M, g.B, ld, g.N, 0, g.K / 32, m0, n0, smem);
   gemm_epilogue<C>(
       acc, smem, m0, n0,
@@ -803,6 +922,7 @@ __global__ __launch_bounds__(256) void bwd_gemm_kernel(TileMap tm, BwdGemm g) {
 #pragma unroll
             for (int e = 0; e < 8; ++e) o[e] = silu_f(o[e]);
             store8(g.out2 + static_cast<int64_t>(row) * g.ldo2 + col0, o);
+            if (col0 < g.split) store_planes8<kFwdPlanes>(g.planes + static_cast<int64_t>(row) * g.ldp, col0, o);
           }
         } else if (EPI == kEpiDsilu) {
           float zz[8];
@@ -810,6 +930,7 @@ __global__ __launch_bounds__(256) void bwd_gemm_kernel(TileMap tm, BwdGemm g) {
 #pragma unroll
           for (int e = 0; e < 8; ++e) o[e] = v[e] * dsilu_f(zz[e]);
           store8(g.out + static_cast<int64_t>(row) * g.ldo + col0, o);
+          store_planes8<2>(g.planes + static_cast<int64_t>(row) * g.ldp, col0, o);
         } else if (EPI == kEpiRows) {
 #pragma unroll
           for (int e = 0; e < 8; ++e) o[e] = v[e];

@@ -722,7 +722,7 @@ fovea_status run_lm_topk(fovea_ctx* c, int n, const void* h, const void* W, int 
 struct BwdLayout {
   int npad;
   size_t node_req, info, stats, tau0, ok, dlogit;
-  size_t xhat, xe, y, q, alpha, z, a, c, hn, dc, dz, dr, dq, dxe, wa, wsel;
+  size_t xe_p, y_p, r, q, alpha, z, a, a_p, c, hn, dc, dc_p, dz, dz_p, dr, dq, dq_p, dxe, wa, wsel;  // _p: planes
   size_t part, sa, sb;
   size_t total;
 };
@@ -744,34 +744,37 @@ BwdLayout bwd_layout(const fovea_dims& D, int B, int n, int k_max, int m_max) {
   L.tau0 = take(static_cast<size_t>(B) * 4);
   L.ok = take(nn * 4);
   L.dlogit = take(np * 4);
-  L.xhat = take(nn * d * 4);
-  L.xe = take(nn * d * 4);
-  L.y = take(nn * (d + dm) * 4);
+  L.xe_p = take(nn * d * 4);
+  L.y_p = take(nn * (d + dm) * kFwdPlanes * 2);
+  L.r = take(nn * dm * 4);
   L.q = take(nn * dm * 4);
   L.alpha = take(nn * static_cast<size_t>(k_max) * 4);
   L.z = take(nn * 2 * dc * 4);
   L.a = take(nn * 2 * dc * 4);
+  L.a_p = take(nn * dc * kFwdPlanes * 2);
   L.c = take(nn * d * 4);
   L.hn = take(nn * d * 4);
   L.dc = take(nn * d * 4);
+  L.dc_p = take(nn * d * 4);
   L.dz = take(nn * 2 * dc * 4);
+  L.dz_p = take(nn * 2 * dc * 4);
   L.dr = take(nn * dm * 4);
   L.dq = take(nn * dm * 4);
+  L.dq_p = take(nn * dm * 4);
   L.dxe = take(nn * d * 4);
   L.wa = take(nn * static_cast<size_t>(m_max) * 4);
   L.wsel = take(nn * static_cast<size_t>(m_max) * 4);
   // column-sum partials: b_c2, b_c1, b_g1, w_g2 and rms_w one slot each; dxe two plus
   // one per depth
   L.part = take(static_cast<size_t>(kColChunks) * (d * (D.n_depth + 4) + 3 * dc) * 4);
-  // two bf16 planes of the largest A and B operand of the backward's GEMMs ([rows, 2 K])
-  const size_t mk[] = {nn * d, nn * (d + dm), nn * dc, nn * 2 * dc, nn * dm, d * np, 2 * dc * np, dm * np};
-  const size_t nk[] = {dm * d, 2 * dc * (d + dm), d * dc, dc * d, (d + dm) * 2 * dc, d * dm,
-                       dc * np, (d + dm) * np, d * np};
+  // two bf16 planes of the largest weight and node-axis operands ([rows, 2 K])
+  const size_t mk[] = {d * np, 2 * dc * np, dm * np};
+  const size_t nk[] = {dm * d, 2 * dc * (d + dm), d * dc, dc * np, (d + dm) * np, d * np};
   size_t ma = 0, mb = 0;
   for (size_t v : mk) ma = std::max(ma, v);
   for (size_t v : nk) mb = std::max(mb, v);
   L.sa = take(ma * 2 * 2);
-  L.sb = take(mb * 2 * 2);
+  L.sb = take(std::max(mb * 2, std::max(2 * dc * (d + dm), d * dc) * kFwdPlanes) * 2);
   L.total = o;
   return L;
 }
@@ -805,46 +808,71 @@ void launch_fill(float* p, int64_t count, hipStream_t s) {
   hipLaunchKernelGGL(fill_f32_kernel, dim3(static_cast<unsigned>(blocks)), dim3(256), 0, s, count, p, 0.f);
 }
 
-void launch_transpose(int R, int R_pad, int C, const float* src, int64_t lds, float* dst,
-                      int64_t ldd, hipStream_t s) {
-  hipLaunchKernelGGL(transpose_f32_kernel, dim3((C + 63) / 64, (R_pad + 63) / 64), dim3(256), 0, s,
-                     R, R_pad, C, src, lds, dst, ldd);
-}
-
-template <int EPI, int BM>
+template <int EPI, int BM, int P>
 void launch_bwd_gemm_bm(const BwdGemm& g, hipStream_t s) {
   const TileMap tm = make_tile_map((g.M + BM - 1) / BM, (g.N + 127) / 128, static_cast<double>(g.M) * g.K,
                                    static_cast<double>(g.N) * g.K);
-  hipLaunchKernelGGL((bwd_gemm_kernel<EPI, BM>), dim3(tile_grid(tm)), dim3(256), 0, s, tm, g);
+  hipLaunchKernelGGL((bwd_gemm_kernel<EPI, BM, P>), dim3(tile_grid(tm)), dim3(256), 0, s, tm, g);
 }
 
 // 64- or 128-row tiles, whichever takes less time over its rounds of the 256 compute
-// units (a k-tile of 32: 0.58 us with 128 rows, 0.33 with 64)
-template <int EPI>
+// units (a k-tile of 32 in two planes: 0.58 us with 128 rows, 0.33 with 64; in three: 1.08
+// and 0.60)
+template <int EPI, int P = 2>
 void launch_bwd_gemm(const BwdGemm& g, hipStream_t s) {
   auto rounds = [&](int bm) {
     const int64_t tiles = static_cast<int64_t>((g.M + bm - 1) / bm) * ((g.N + 127) / 128);
     return (tiles + 255) / 256;
   };
   if (58 * rounds(128) < 33 * rounds(64))
-    launch_bwd_gemm_bm<EPI, 128>(g, s);
+    launch_bwd_gemm_bm<EPI, 128, P>(g, s);
   else
-    launch_bwd_gemm_bm<EPI, 64>(g, s);
+    launch_bwd_gemm_bm<EPI, 64, P>(g, s);
 }
 
-void launch_split(int R, int C, const float* src, int64_t lds, bf16_t* dst, hipStream_t s) {
+// planes of src at columns c_off .. of rows of W (default: C) columns
+template <int P = 2>
+void launch_split(int R, int C, const float* src, int64_t lds, bf16_t* dst, hipStream_t s, int W = 0,
+                  int c_off = 0) {
   const int64_t items = static_cast<int64_t>(R) * (C / 8);
-  hipLaunchKernelGGL(split_planes_kernel, dim3(static_cast<unsigned>((items + 255) / 256)), dim3(256), 0, s, R, C,
-                     src, lds, dst);
+  hipLaunchKernelGGL(split_planes_kernel<P>, dim3(static_cast<unsigned>((items + 255) / 256)), dim3(256), 0, s, R, C,
+                     src, lds, dst, W > 0 ? W : C, c_off, aligned16(src) && lds % 4 == 0);
 }
 
-void launch_transpose_split(int R, int R_pad, int C, const float* src, int64_t lds, bf16_t* dst,
-                            int W, int r_off, hipStream_t s) {
+RowSrc plain_rows(const float* x, int64_t ld, const int32_t* ok = nullptr) {
+  RowSrc r{};
+  r.x = x;
+  r.ld = ld;
+  r.ok = ok;
+  r.vec = aligned16(x) && ld % 4 == 0;
+  return r;
+}
+
+// LN(x) of rows d apart (and wide)
+RowSrc norm_rows(const float* x, int d, const float2* stats, const float* g, const float* b,
+                 const int32_t* ok = nullptr) {
+  RowSrc r = plain_rows(x, d, ok);
+  r.stats = stats;
+  r.g = g;
+  r.b = b;
+  r.vec = r.vec && aligned16(g) && aligned16(b);
+  return r;
+}
+
+void launch_transpose_split(int R, int R_pad, int C, const RowSrc& src, bf16_t* dst, int W, int r_off,
+                            hipStream_t s) {
   hipLaunchKernelGGL(transpose_planes_kernel, dim3((C + 63) / 64, (R_pad + 63) / 64), dim3(256), 0, s,
-                     R, R_pad, C, src, lds, dst, W, r_off);
+                     R, R_pad, C, src, dst, W, r_off);
 }
 
-// A GEMM over planes already in sa (A, [M, 2 K]) and sb (B, [N, 2 K]).
+template <bool ADD>
+void launch_bwd_ln(int n, int d, const float* dx, const float* x, const float* g, const float2* stats,
+                   const int32_t* ok, float* out, hipStream_t s) {
+  hipLaunchKernelGGL((d <= 4096 ? bwd_ln_kernel<4, ADD> : bwd_ln_kernel<8, ADD>), dim3(n), dim3(256), 0, s, n, d,
+                     dx, x, g, aligned16(g), stats, ok, out);
+}
+
+// A GEMM over planes already in sa (A, rows of P K) and sb (B).
 BwdGemm planes_gemm(int M, int N, int K, const bf16_t* sa, const bf16_t* sb, float* out, int64_t ldo) {
   BwdGemm g{};
   g.M = M;
@@ -855,25 +883,6 @@ BwdGemm planes_gemm(int M, int N, int K, const bf16_t* sa, const bf16_t* sb, flo
   g.out = out;
   g.ldo = ldo;
   return g;
-}
-
-// Splits A [M, K] and B [N, K] (fp32) into planes in sa / sb and returns the GEMM over
-// them; the caller launches it before the next split reuses sa / sb.
-BwdGemm split_gemm(int M, int N, int K, const float* A, int64_t lda, const float* B, int64_t ldb,
-                   float* out, int64_t ldo, bf16_t* sa, bf16_t* sb, hipStream_t s) {
-  launch_split(M, K, A, lda, sa, s);
-  launch_split(N, K, B, ldb, sb, s);
-  return planes_gemm(M, N, K, sa, sb, out, ldo);
-}
-
-// The weight-gradient GEMM dW = X^T Y over the node axis: X [n, M] (ld ldx) and
-// Y [n, N] (ld ldy) are transposed into planes (K = n_pad) in sa / sb.
-BwdGemm split_gemm_nodes(int n, int n_pad, int M, int N, const float* X, int64_t ldx,
-                         const float* Y, int64_t ldy, float* out, int64_t ldo, bf16_t* sa,
-                         bf16_t* sb, hipStream_t s) {
-  launch_transpose_split(n, n_pad, M, X, ldx, sa, n_pad, 0, s);
-  launch_transpose_split(n, n_pad, N, Y, ldy, sb, n_pad, 0, s);
-  return planes_gemm(M, N, n_pad, sa, sb, out, ldo);
 }
 
 // Column-sum jobs launched together (up to kColJobs per launch pair); every job's
@@ -918,7 +927,7 @@ struct ColSums {
   }
   void flush() {
     if (js.n_jobs == 0) return;
-    hipLaunchKernelGGL(colsum_multi_kernel, dim3((max_cols + 1023) / 1024, kColChunks, js.n_jobs),
+    hipLaunchKernelGGL(colsum_multi_kernel, dim3((max_cols + 255) / 256, kColChunks, js.n_jobs),
                        dim3(256), 0, s, n, js, part);
     hipLaunchKernelGGL(colsum_multi_final_kernel, dim3((max_cols + 255) / 256, kColSlots, js.n_jobs),
                        dim3(256), 0, s, js, part);
@@ -940,11 +949,7 @@ fovea_status run_backward(fovea_ctx* c, const BwdArgs& a, hipStream_t s) {
   char* w = a.ws;
   auto F = [&](size_t off) { return reinterpret_cast<float*>(w + off); };
   // every GEMM of the backward runs on the bf16 matrix cores over its operands' planes
-  auto bwd_gemm = [&](int M, int N, int K, const float* A, int64_t lda, const float* B,
-                      int64_t ldb, float* out, int64_t ldo) {
-    return split_gemm(M, N, K, A, lda, B, ldb, out, ldo, reinterpret_cast<bf16_t*>(w + L.sa),
-                      reinterpret_cast<bf16_t*>(w + L.sb), s);
-  };
+  auto PL = [&](size_t off) { return reinterpret_cast<bf16_t*>(w + off); };
   int32_t* node_req = reinterpret_cast<int32_t*>(w + L.node_req);
   NodeInfo* info = reinterpret_cast<NodeInfo*>(w + L.info);
   float2* stats = reinterpret_cast<float2*>(w + L.stats);
@@ -959,7 +964,7 @@ fovea_status run_backward(fovea_ctx* c, const BwdArgs& a, hipStream_t s) {
   // per-node kernels keep q, dr and the selection's scores in LDS
   const size_t sm_fwd = static_cast<size_t>(dm + a.k_max) * 4;
   const size_t sm_bwd = static_cast<size_t>(dm + a.k_max) * 4;
-  const size_t sm_mem = static_cast<size_t>(a.t_max) * kMemRows * 2 * 4;
+  const size_t sm_mem = static_cast<size_t>(a.t_max) * (kMemRows * 2 * 4 + 4 * 2);
   if (sm_mem > c->lds_limit[kLdsBwdMem] || sm_fwd > c->lds_limit[kLdsBwdSelFwd] ||
       sm_bwd > c->lds_limit[kLdsBwdSel])
     return FOVEA_ERR_UNSUPPORTED;
@@ -980,60 +985,67 @@ fovea_status run_backward(fovea_ctx* c, const BwdArgs& a, hipStream_t s) {
   }
   bf16_t* sa = reinterpret_cast<bf16_t*>(w + L.sa);
   bf16_t* sb = reinterpret_cast<bf16_t*>(w + L.sb);
+  RowSrc xe = norm_rows(a.h, d, stats, static_cast<const float*>(a.P->q_ln_g),
+                        static_cast<const float*>(a.P->q_ln_b), node_req);
+  xe.E = static_cast<const float*>(a.P->E_dep);
+  xe.depth = a.depth;
+  xe.n_depth = nd;
+  const RowSrc hr = plain_rows(a.h, d, node_req);
   {
     ProfScope ps(c, kBwdPrep, s);
-    hipLaunchKernelGGL(bwd_prep_kernel, dim3(n), dim3(256), 0, s, n, d, dm, a.h, stats, node_req,
-                       a.depth, nd, static_cast<const float*>(a.P->q_ln_g),
-                       static_cast<const float*>(a.P->q_ln_b), static_cast<const float*>(a.P->E_dep),
-                       F(L.xhat), F(L.xe), F(L.y));
+    hipLaunchKernelGGL(bwd_prep_kernel, dim3(n), dim3(256), 0, s, n, d, dm, xe, hr, PL(L.xe_p), PL(L.y_p));
   }
   {
     ProfScope ps(c, kBwdGemm, s);
-    launch_bwd_gemm<kEpiStore>(bwd_gemm(n, dm, d, F(L.xe), d, W_Q, d, F(L.q), dm), s);
+    launch_split(dm, d, W_Q, d, sb, s);
+    launch_bwd_gemm<kEpiStore>(planes_gemm(n, dm, d, PL(L.xe_p), sb, F(L.q), dm), s);
   }
   {
     ProfScope ps(c, kBwdSelFwd, s);
     hipLaunchKernelGGL(bwd_sel_fwd_kernel, dim3(n), dim3(256), sm_fwd, s, n, d, dm, a.k_max, info, a.K,
-                       a.idx, F(L.q), a.keys, a.values, scale, F(L.alpha), F(L.y), ok, c->err);
+                       a.idx, F(L.q), a.keys, a.values, scale, F(L.alpha), F(L.r), PL(L.y_p), ok, c->err);
   }
   {
     ProfScope ps(c, kBwdGemm, s);
     // layer 1 of both nets in one GEMM (2 d_c columns); the bias is [b_c1; b_g1]
     // B = [W_c1; W_g1], split straight from the two weights
-    launch_split(n, d + dm, F(L.y), d + dm, sa, s);
-    launch_split(dc, d + dm, W_c1, d + dm, sb, s);
-    launch_split(dc, d + dm, W_g1, d + dm, sb + static_cast<int64_t>(dc) * 2 * (d + dm), s);
-    BwdGemm g = planes_gemm(n, 2 * dc, d + dm, sa, sb, F(L.z), 2 * dc);
+    launch_split<kFwdPlanes>(dc, d + dm, W_c1, d + dm, sb, s);
+    launch_split<kFwdPlanes>(dc, d + dm, W_g1, d + dm, sb + static_cast<int64_t>(dc) * kFwdPlanes * (d + dm), s);
+    BwdGemm g = planes_gemm(n, 2 * dc, d + dm, PL(L.y_p), sb, F(L.z), 2 * dc);
     g.bias = static_cast<const float*>(a.P->b_c1);
     g.bias2 = static_cast<const float*>(a.P->b_g1);
     g.split = dc;
     g.out2 = F(L.a);
     g.ldo2 = 2 * dc;
-    launch_bwd_gemm<kEpiZ>(g, s);
-    BwdGemm g2 = bwd_gemm(n, d, dc, F(L.a), 2 * dc, W_c2, dc, F(L.c), d);
+    g.planes = PL(L.a_p);
+    g.ldp = kFwdPlanes * dc;
+    launch_bwd_gemm<kEpiZ, kFwdPlanes>(g, s);
+    launch_split<kFwdPlanes>(d, dc, W_c2, dc, sb, s);
+    BwdGemm g2 = planes_gemm(n, d, dc, PL(L.a_p), sb, F(L.c), d);
     g2.bias = static_cast<const float*>(a.P->b_c2);
-    launch_bwd_gemm<kEpiStore>(g2, s);
+    launch_bwd_gemm<kEpiStore, kFwdPlanes>(g2, s);
   }
   {
     ProfScope ps(c, kBwdRmsGate, s);
-    hipLaunchKernelGGL(bwd_rms_gate_kernel, dim3(n), dim3(256), 0, s, n, d, dc, a.h, F(L.c), F(L.z),
+    hipLaunchKernelGGL((d <= 4096 ? bwd_rms_gate_kernel<4> : bwd_rms_gate_kernel<8>), dim3(n), dim3(256), 0, s, n,
+                       d, dc, a.h, F(L.c), F(L.z),
                        F(L.a), static_cast<const float*>(a.P->w_g2), a.P->b_g2, rms_w, D.rms_eps,
-                       a.dh_hat, ok, a.dh, F(L.dc), F(L.hn), F(L.dlogit), F(L.dz));
+                       a.dh_hat, ok, a.dh, F(L.dc), PL(L.dc_p), F(L.hn), F(L.dlogit), F(L.dz), PL(L.dz_p));
   }
   {
     ProfScope ps(c, kBwdGemm, s);
     // B = W_c2^T, transposed straight into its planes
-    launch_split(n, d, F(L.dc), d, sa, s);
-    launch_transpose_split(d, d, dc, W_c2, dc, sb, d, 0, s);
-    BwdGemm g = planes_gemm(n, dc, d, sa, sb, F(L.dz), 2 * dc);
+    launch_transpose_split(d, d, dc, plain_rows(W_c2, dc), sb, d, 0, s);
+    BwdGemm g = planes_gemm(n, dc, d, PL(L.dc_p), sb, F(L.dz), 2 * dc);
     g.aux = F(L.z);
     g.ldaux = 2 * dc;
+    g.planes = PL(L.dz_p);
+    g.ldp = 4 * dc;
     launch_bwd_gemm<kEpiDsilu>(g, s);
     // B = [W_c1; W_g1]^T: the two weights transposed side by side along K
-    launch_split(n, 2 * dc, F(L.dz), 2 * dc, sa, s);
-    launch_transpose_split(dc, dc, d + dm, W_c1, d + dm, sb, 2 * dc, 0, s);
-    launch_transpose_split(dc, dc, d + dm, W_g1, d + dm, sb, 2 * dc, dc, s);
-    BwdGemm g2 = planes_gemm(n, d + dm, 2 * dc, sa, sb, a.dh, d);
+    launch_transpose_split(dc, dc, d + dm, plain_rows(W_c1, d + dm), sb, 2 * dc, 0, s);
+    launch_transpose_split(dc, dc, d + dm, plain_rows(W_g1, d + dm), sb, 2 * dc, dc, s);
+    BwdGemm g2 = planes_gemm(n, d + dm, 2 * dc, PL(L.dz_p), sb, a.dh, d);
     g2.split = d;
     g2.out2 = F(L.dr);
     g2.ldo2 = dm;
@@ -1042,7 +1054,7 @@ fovea_status run_backward(fovea_ctx* c, const BwdArgs& a, hipStream_t s) {
   {
     ProfScope ps(c, kBwdSel, s);
     hipLaunchKernelGGL(bwd_sel_kernel, dim3(n), dim3(256), sm_bwd, s, n, dm, a.k_max, a.m_max, info,
-                       a.K, a.idx, ok, F(L.alpha), F(L.dr), a.keys, a.values, scale, F(L.dq),
+                       a.K, a.idx, ok, F(L.alpha), F(L.dr), a.keys, a.values, scale, F(L.dq), PL(L.dq_p),
                        F(L.wa), F(L.wsel));
     if (a.m_max > 0)
       hipLaunchKernelGGL(bwd_mem_grad_kernel, dim3((dm + 255) / 256, (a.m_max + kMemRows - 1) / kMemRows, a.B),
@@ -1051,25 +1063,34 @@ fovea_status run_backward(fovea_ctx* c, const BwdArgs& a, hipStream_t s) {
   }
   {
     ProfScope ps(c, kBwdGemm, s);
-    launch_split(n, dm, F(L.dq), dm, sa, s);
-    launch_transpose_split(dm, dm, d, W_Q, d, sb, dm, 0, s);
-    launch_bwd_gemm<kEpiStore>(planes_gemm(n, d, dm, sa, sb, F(L.dxe), d), s);
+    launch_transpose_split(dm, dm, d, plain_rows(W_Q, d), sb, dm, 0, s);
+    launch_bwd_gemm<kEpiStore>(planes_gemm(n, d, dm, PL(L.dq_p), sb, F(L.dxe), d), s);
   }
   {
     ProfScope ps(c, kBwdLn, s);
-    hipLaunchKernelGGL(bwd_ln_kernel, dim3(n), dim3(256), 0, s, n, d, F(L.dxe), F(L.xhat),
-                       static_cast<const float*>(a.P->q_ln_g), stats, ok, a.dh);
+    launch_bwd_ln<true>(n, d, F(L.dxe), a.h, static_cast<const float*>(a.P->q_ln_g), stats, ok, a.dh, s);
   }
   {
-    // weight gradients: GEMMs over the node axis, operands transposed into bf16 planes
+    // weight gradients dW = X^T Y: GEMMs over the node axis, operands transposed into planes
+    // (K = np)
     ProfScope ps(c, kBwdGemm, s);
-    launch_bwd_gemm<kEpiStore>(split_gemm_nodes(n, np, d, dc, F(L.dc), d, F(L.a), 2 * dc, G.W_c2, dc, sa, sb, s), s);
-    BwdGemm g1 = split_gemm_nodes(n, np, 2 * dc, d + dm, F(L.dz), 2 * dc, F(L.y), d + dm, G.W_c1, d + dm, sa, sb, s);
+    auto nodes = [&](int C, const RowSrc& src, bf16_t* dst) {
+      launch_transpose_split(n, np, C, src, dst, np, 0, s);
+    };
+    nodes(d, plain_rows(F(L.dc), d), sa);
+    nodes(dc, plain_rows(F(L.a), 2 * dc), sb);
+    launch_bwd_gemm<kEpiStore>(planes_gemm(d, dc, np, sa, sb, G.W_c2, dc), s);
+    nodes(2 * dc, plain_rows(F(L.dz), 2 * dc), sa);
+    nodes(d, hr, sb);
+    nodes(dm, plain_rows(F(L.r), dm), sb + static_cast<int64_t>(d) * 2 * np);
+    BwdGemm g1 = planes_gemm(2 * dc, d + dm, np, sa, sb, G.W_c1, d + dm);
     g1.split = dc;
     g1.out2 = G.W_g1;
     g1.ldo2 = d + dm;
     launch_bwd_gemm<kEpiRows>(g1, s);
-    launch_bwd_gemm<kEpiStore>(split_gemm_nodes(n, np, dm, d, F(L.dq), dm, F(L.xe), d, G.W_Q, d, sa, sb, s), s);
+    nodes(dm, plain_rows(F(L.dq), dm), sa);
+    nodes(d, xe, sb);
+    launch_bwd_gemm<kEpiStore>(planes_gemm(dm, d, np, sa, sb, G.W_Q, d), s);
   }
   {
     ProfScope ps(c, kBwdReduce, s);
@@ -1096,8 +1117,10 @@ fovea_status run_backward(fovea_ctx* c, const BwdArgs& a, hipStream_t s) {
     }
     // dxe read once for the LayerNorm bias and gain and the depth embeddings
     jb = ColSums::job(d, F(L.dxe), d);
-    jb.Y = F(L.xhat);
+    jb.Y = a.h;  // xhat, from h and its statistics
     jb.ldy = d;
+    jb.ys = stats;
+    jb.yok = node_req;
     jb.out_x = G.q_ln_b;
     jb.out_xy = G.q_ln_g;
     cs.add_grouped(jb, a.depth, nd, G.E_dep);
@@ -1111,7 +1134,7 @@ fovea_status run_backward(fovea_ctx* c, const BwdArgs& a, hipStream_t s) {
 // memory-build backward: workspace layout and launches
 struct MemBwdLayout {
   int npad;
-  size_t stats, xhat, xn, dxn, WKT, WUT, part, sa, sb, total;
+  size_t stats, dxn, part, sa, sb, total;
 };
 
 MemBwdLayout mem_bwd_layout(const fovea_dims& D, int64_t n) {
@@ -1126,14 +1149,11 @@ MemBwdLayout mem_bwd_layout(const fovea_dims& D, int64_t n) {
     return at;
   };
   L.stats = take(nn * 8);
-  L.xhat = take(nn * dv * 4);
-  L.xn = take(nn * dv * 4);
   L.dxn = take(nn * dv * 4);
-  L.WKT = take(dv * dm * 4);
-  L.WUT = take(dv * dm * 4);
   L.part = take(static_cast<size_t>(kColChunks) * 2 * dv * 4);
-  L.sa = take(std::max(dm * np, nn * dm) * 2 * 2);
-  L.sb = take(std::max(dv * np, dv * dm) * 2 * 2);
+  // planes: [dk | du] and its transpose; LN(V)^T and [W_K; W_U]^T
+  L.sa = take(2 * dm * np * 2 * 2);
+  L.sb = take(std::max(dv * np, dv * 2 * dm) * 2 * 2);
   L.total = o;
   return L;
 }
@@ -1146,48 +1166,43 @@ fovea_status run_mem_backward(fovea_ctx* c, const fovea_params* P, int n, const 
   const MemBwdLayout L = mem_bwd_layout(D, n);
   const int np = L.npad;
   auto F = [&](size_t off) { return reinterpret_cast<float*>(w + off); };
-  auto bwd_gemm = [&](int M, int N, int K, const float* A, int64_t lda, const float* B,
-                      int64_t ldb, float* out, int64_t ldo) {
-    return split_gemm(M, N, K, A, lda, B, ldb, out, ldo, reinterpret_cast<bf16_t*>(w + L.sa),
-                      reinterpret_cast<bf16_t*>(w + L.sb), s);
-  };
   float2* stats = reinterpret_cast<float2*>(w + L.stats);
   const float* W_K = static_cast<const float*>(P->W_K);
   const float* W_U = static_cast<const float*>(P->W_U);
+  const float* g = static_cast<const float*>(P->mem_ln_g);
+  bf16_t* sa = reinterpret_cast<bf16_t*>(w + L.sa);
+  bf16_t* sb = reinterpret_cast<bf16_t*>(w + L.sb);
   ProfScope ps(c, kBwdMem, s);
   hipLaunchKernelGGL(row_stats_kernel<float>, dim3((n + 3) / 4), dim3(256), 0, s, n, V, dv, D.ln_eps,
                      stats, static_cast<const int32_t*>(nullptr), 0, static_cast<const int32_t*>(nullptr),
                      0, 0, static_cast<const float*>(nullptr), static_cast<const int64_t*>(nullptr),
                      int64_t{0}, 0, static_cast<int32_t*>(nullptr), static_cast<NodeInfo*>(nullptr), c->err);
-  hipLaunchKernelGGL(ln_apply_kernel, dim3(n), dim3(256), 0, s, n, dv, V, stats,
-                     static_cast<const float*>(P->mem_ln_g), static_cast<const float*>(P->mem_ln_b),
-                     F(L.xhat), F(L.xn));
-  launch_transpose(dm, dm, dv, W_K, dv, F(L.WKT), dm, s);
-  launch_transpose(dm, dm, dv, W_U, dv, F(L.WUT), dm, s);
-  // weight gradients over the row axis
-  bf16_t* sa = reinterpret_cast<bf16_t*>(w + L.sa);
-  bf16_t* sb = reinterpret_cast<bf16_t*>(w + L.sb);
-  launch_bwd_gemm<kEpiStore>(split_gemm_nodes(n, np, dm, dv, dk, dm, F(L.xn), dv, dW_K, dv, sa, sb, s), s);
-  launch_bwd_gemm<kEpiStore>(split_gemm_nodes(n, np, dm, dv, du, dm, F(L.xn), dv, dW_U, dv, sa, sb, s), s);
-  // dL/dLN(v) = dk W_K + du W_U
-  launch_bwd_gemm<kEpiStore>(bwd_gemm(n, dv, dm, dk, dm, F(L.WKT), dm, F(L.dxn), dv), s);
-  BwdGemm g2 = bwd_gemm(n, dv, dm, du, dm, F(L.WUT), dm, F(L.dxn), dv);
-  g2.split = dv;  // every column accumulates into dxn
-  launch_bwd_gemm<kEpiSplit>(g2, s);
+  // weight gradients [dW_K; dW_U] = [dk | du]^T LN(V) over the row axis, the LayerNorm
+  // applied on the way into the planes
+  launch_transpose_split(n, np, dm, plain_rows(dk, dm), sa, np, 0, s);
+  launch_transpose_split(n, np, dm, plain_rows(du, dm), sa + static_cast<int64_t>(dm) * 2 * np, np, 0, s);
+  launch_transpose_split(n, np, dv, norm_rows(V, dv, stats, g, static_cast<const float*>(P->mem_ln_b)), sb, np, 0, s);
+  BwdGemm g1 = planes_gemm(2 * dm, dv, np, sa, sb, dW_K, dv);
+  g1.split = dm;
+  g1.out2 = dW_U;
+  g1.ldo2 = dv;
+  launch_bwd_gemm<kEpiRows>(g1, s);
+  // dL/dLN(v) = [dk | du] [W_K; W_U]
+  launch_split(n, dm, dk, dm, sa, s, 2 * dm, 0);
+  launch_split(n, dm, du, dm, sa, s, 2 * dm, dm);
+  launch_transpose_split(dm, dm, dv, plain_rows(W_K, dv), sb, 2 * dm, 0, s);
+  launch_transpose_split(dm, dm, dv, plain_rows(W_U, dv), sb, 2 * dm, dm, s);
+  launch_bwd_gemm<kEpiStore>(planes_gemm(n, dv, 2 * dm, sa, sb, F(L.dxn), dv), s);
   ColSums cs(n, F(L.part), s);
   ColJob jb = ColSums::job(dv, F(L.dxn), dv);
-  jb.Y = F(L.xhat);
+  jb.Y = V;  // xhat, from V and its statistics
   jb.ldy = dv;
+  jb.ys = stats;
   jb.out_x = db;
   jb.out_xy = dg;
   cs.add(jb);
   cs.flush();
-  if (dV != nullptr) {
-    launch_fill(dV, static_cast<int64_t>(n) * dv, s);
-    hipLaunchKernelGGL(bwd_ln_kernel, dim3(n), dim3(256), 0, s, n, dv, F(L.dxn), F(L.xhat),
-                       static_cast<const float*>(P->mem_ln_g), stats, static_cast<const int32_t*>(nullptr),
-                       dV);
-  }
+  if (dV != nullptr) launch_bwd_ln<false>(n, dv, F(L.dxn), V, g, stats, nullptr, dV, s);
   FOVEA_HIP(hipGetLastError());
   return FOVEA_OK;
 }

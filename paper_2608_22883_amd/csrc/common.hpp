@@ -82,13 +82,16 @@ __device__ __forceinline__ void load8(const float* p, float (&x)[8]) {
   x[4] = b[0]; x[5] = b[1]; x[6] = b[2]; x[7] = b[3];
 }
 
-__device__ __forceinline__ void load8(const bf16_t* p, float (&x)[8]) {
-  const u32x4 a = *reinterpret_cast<const u32x4*>(p);
+__device__ __forceinline__ void unpack8(u32x4 a, float (&x)[8]) {
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     x[2 * e] = __uint_as_float(a[e] << 16);
     x[2 * e + 1] = __uint_as_float(a[e] & 0xffff0000u);
   }
+}
+
+__device__ __forceinline__ void load8(const bf16_t* p, float (&x)[8]) {
+  unpack8(*reinterpret_cast<const u32x4*>(p), x);
 }
 
 __device__ __forceinline__ void store8(float* p, const float (&x)[8]) {

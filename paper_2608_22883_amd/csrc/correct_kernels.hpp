@@ -132,10 +132,15 @@ struct Corr2Epi {
   int m0;
   __device__ __forceinline__ float operator()(int row, int col0, const float (&v)[8]) const {
     if (row >= n || col0 >= d) return 0.f;
-    const float g = sg[row - m0];
+    float hv[8];
+    load8(h + static_cast<int64_t>(row) * d + col0, hv);
+    return finish(row, col0, v, hv, sg[row - m0]);
+  }
+  // the epilogue for 8 columns whose h and gate are given
+  __device__ __forceinline__ float finish(int row, int col0, const float (&v)[8], const float (&hv)[8],
+                                          float g) const {
     const int64_t o = static_cast<int64_t>(row) * d + col0;
-    float hv[8], b[8], hp[8];
-    load8(h + o, hv);
+    float b[8], hp[8];
     load8(b_c2 + col0, b);
     float ss = 0.f;
 #pragma unroll
@@ -150,7 +155,10 @@ struct Corr2Epi {
 
 struct Corr2Args {
   int d_c;
+  // gate logit partials of row i: n_gate values, gate_step apart, from gate_part + i gate_ld
   const float* gate_part;
+  int n_gate, gate_step;
+  int64_t gate_ld;
   float b_g2;
   float* gate_out;
   float* rms_part;  // or null without RMSNorm
@@ -160,12 +168,11 @@ struct Corr2Args {
 __device__ __forceinline__ void stage_gates(const Corr2Args& ca, int n, int m0, int rows, bool first,
                                             float* sg) {
   if (threadIdx.x < static_cast<unsigned>(rows)) {
-    const int n_gp = n_parts(2 * ca.d_c);
     const int row = m0 + threadIdx.x;
     float g = 0.f;
     if (row < n) {
       float sum = 0.f;
-      for (int p2 = 0; p2 < n_gp; ++p2) sum += ca.gate_part[static_cast<int64_t>(row) * n_gp + p2];
+      for (int p2 = 0; p2 < ca.n_gate; ++p2) sum += ca.gate_part[row * ca.gate_ld + p2 * ca.gate_step];
       g = sigmoid_f(sum + ca.b_g2);
       if (ca.gate_out != nullptr && first) ca.gate_out[row] = g;
     }
@@ -202,13 +209,101 @@ template <typename T>
 __global__ __launch_bounds__(256) void corr2_combine_kernel(Corr2Epi<T> epi, Corr2Args ca, int ks,
                                                             const float* __restrict__ part) {
   __shared__ float sg[16];
-  const int m0 = static_cast<int>(blockIdx.y) * 16;
-  stage_gates(ca, epi.n, m0, 16, blockIdx.x == 0, sg);
+  const int rows = static_cast<int>(blockDim.x >> 4), m0 = static_cast<int>(blockIdx.y) * rows;
+  stage_gates(ca, epi.n, m0, rows, blockIdx.x == 0, sg);
   __syncthreads();
   epi.sg = sg;
   epi.m0 = m0;
   splitk_combine(epi.n, epi.d, ks, part, epi,
                  RowPart{epi.n, n_parts(epi.d), static_cast<int>(blockIdx.x), ca.rms_part});
+}
+
+// Few rows (bf16): the two layers in skinny tiles (gemm.hpp), each in one launch.  Their row
+// partials stay in P, whose columns a block has read itself (layer 1: the gate logit of its 16
+// columns, at their first) or that layer 1 has consumed (layer 2: the squares of tile t, at
+// column t < d / 16 <= d_c).  One request: layer 1 4.9 + 4.4 us (split-K and combine) before.
+__global__ __launch_bounds__(512, 2) void corr1_skinny_kernel(const bf16_t* __restrict__ rT, int d_m,
+                                                              const bf16_t* __restrict__ W1r,
+                                                              Corr1Epi<bf16_t> epi, float* __restrict__ P) {
+  const int m0 = blockIdx.y * 32, n0 = blockIdx.x * 16;
+  skinny_tile<2, 8, 4>(rT, epi.n, W1r, d_m, m0, n0, epi, [&](int row, float sum) {
+    if (row < epi.n && n0 >= epi.d_c) P[static_cast<int64_t>(row) * epi.N + n0] = sum;
+  });
+}
+
+__global__ __launch_bounds__(256) void corr2_skinny_kernel(const bf16_t* __restrict__ a_c,
+                                                           const bf16_t* __restrict__ Wc2,
+                                                           Corr2Epi<bf16_t> epi, Corr2Args ca,
+                                                           int64_t rms_ld) {
+  __shared__ float sg[64];
+  const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 16;
+  // the operands of the epilogue are loaded before the product: the gate partials (four
+  // threads per row, kGateU each at a time) and each epilogue thread's 8 columns of h
+  constexpr int kGateU = 16;
+  const int grow = m0 + (threadIdx.x >> 2), q = threadIdx.x & 3;
+  float gp[kGateU];
+#pragma unroll
+  for (int u = 0; u < kGateU; ++u) {
+    const int p = q + 4 * u;
+    gp[u] = grow < epi.n && p < ca.n_gate ? ca.gate_part[grow * ca.gate_ld + p * ca.gate_step] : 0.f;
+  }
+  const int hrow = min(m0 + static_cast<int>(threadIdx.x >> 1), epi.n - 1), hcol = n0 + (threadIdx.x & 1) * 8;
+  const u32x4 hraw = *reinterpret_cast<const u32x4*>(epi.h + static_cast<int64_t>(hrow) * epi.d + hcol);
+  {
+    float s = 0.f;
+#pragma unroll
+    for (int u = 0; u < kGateU; ++u) s += gp[u];
+    for (int p = q + 4 * kGateU; p < ca.n_gate; p += 4)
+      if (grow < epi.n) s += ca.gate_part[grow * ca.gate_ld + p * ca.gate_step];
+    s += __shfl_xor(s, 1, kWave);
+    s += __shfl_xor(s, 2, kWave);
+    if (q == 0) {
+      const float g = sigmoid_f(s + ca.b_g2);
+      sg[threadIdx.x >> 2] = g;
+      if (grow < epi.n && ca.gate_out != nullptr && blockIdx.x == 0) ca.gate_out[grow] = g;
+    }
+  }
+  skinny_tile<4, 4, 2>(
+      a_c, epi.n, Wc2, ca.d_c, m0, n0,
+      [&](int row, int col0, const float(&v)[8]) -> float {
+        if (row >= epi.n) return 0.f;
+        float hv[8];
+        unpack8(hraw, hv);
+        return epi.finish(row, col0, v, hv, sg[row - m0]);
+      },
+      [&](int row, float sum) {
+        if (row < epi.n && ca.rms_part != nullptr) ca.rms_part[row * rms_ld + blockIdx.x] = sum;
+      });
+}
+
+// RMSNorm of h' in place, one block per row (d / 16 partials per row, rms_ld apart).
+__global__ __launch_bounds__(256) void rms_row_kernel(int d, const float* __restrict__ rms_part, int64_t rms_ld,
+                                                      const float* __restrict__ w, float eps,
+                                                      bf16_t* __restrict__ h_out) {
+  __shared__ float red[4];
+  const int row = blockIdx.x;
+  bf16_t* hr = h_out + static_cast<int64_t>(row) * d;
+  const int c0 = 8 * threadIdx.x;
+  float v[8], wv[8];
+  if (c0 < d) {
+    load8(hr + c0, v);
+    load8(w + c0, wv);
+  }
+  float s2 = 0.f;
+  for (int p = threadIdx.x; p < d / 16; p += 256) s2 += rms_part[row * rms_ld + p];
+  s2 = wave_sum_f32(s2);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s2;
+  __syncthreads();
+  const float rstd = 1.0f / sqrtf(((red[0] + red[1]) + (red[2] + red[3])) / static_cast<float>(d) + eps);
+  for (int c = c0; c < d; c += 2048) {
+    if (c > c0) {
+      load8(hr + c, v);
+      load8(w + c, wv);
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = v[e] * rstd * wv[e];
+    store8(hr + c, v);
+  }
 }
 
 // Split-K layer 2 and the RMSNorm in one pass, one 256-thread block per row (d at most

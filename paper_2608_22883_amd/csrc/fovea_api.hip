@@ -430,6 +430,18 @@ int score_parts(const fovea_dims& D, int B, int n, int m_max, int t_max) {
   return best;
 }
 
+// Few nodes: the two correction layers run in skinny tiles, which need no combine launches
+// (measured at 60 nodes: layer 1 over d_m = 1024 5.7 us against 9.3, over 4096 13.8 against
+// 13.5, so up to 2048); the row partials of layer 2 must fit the consumed half of P.
+constexpr int kSkinnyNodes = 64, kSkinnyK = 2048;
+
+bool use_skinny(const fovea_dims& D, int n) {
+  return D.dtype == FOVEA_BF16 && n <= kSkinnyNodes && D.d_c <= kSkinnyK && D.d / 16 <= D.d_c;
+}
+
+// Threads of a combine block: 4 rows of 128 columns while 16 would leave compute units idle.
+int combine_threads(int n, int N) { return (n + 15) / 16 * ((N + 127) / 128) < 256 ? 64 : 256; }
+
 template <typename T>
 fovea_status run_retrieve_fuse(fovea_ctx* c, const RFArgs& a, hipStream_t s) {
   const fovea_dims& D = c->dims;
@@ -453,6 +465,7 @@ fovea_status run_retrieve_fuse(fovea_ctx* c, const RFArgs& a, hipStream_t s) {
   // 1. LayerNorm statistics of h, node -> request map, depth / tau / offset checks (with
   // a split-K query GEMM its slices and its combine do this, without a launch of its own)
   const bool split_stats = ksp.hq > 1;
+  const bool skinny2 = use_skinny(D, a.n), skinny1 = skinny2 && D.d_m <= kSkinnyK;
   if (!split_stats) {
     ProfScope ps(pc, kRowStats, s);
     hipLaunchKernelGGL(row_stats_kernel<T>, dim3((a.n + 3) / 4), dim3(256), 0, s, a.n, h, D.d,
@@ -498,13 +511,20 @@ fovea_status run_retrieve_fuse(fovea_ctx* c, const RFArgs& a, hipStream_t s) {
       nm.info = info;
       nm.err = c->err;
     }
-    hipLaunchKernelGGL((a.n <= 64 ? hq_kernel<T, 64> : hq_kernel<T>), dim3(tile_grid(tm), ks),
-                       dim3(C::NT), 0, s, tm, a.n, h, D.d, static_cast<const bf16_t*>(c->W_hq), epi, ks, splitk,
-                       stat_part, nm);
-    if (ks > 1)
-      hipLaunchKernelGGL(hq_combine_kernel<T>, dim3((N + 127) / 128, (a.n + 15) / 16), dim3(256), 0, s,
+    // the statistics beside the tiles if every block is resident at once (one per compute unit)
+    const int stat_blocks = (a.n + 3) / 4;
+    const bool beside = split_stats && tile_grid(tm) * ks + stat_blocks * ks <= 256;
+    if (beside) stat_part = nullptr;
+    hipLaunchKernelGGL((a.n <= 64 ? hq_kernel<T, 64> : hq_kernel<T>),
+                       dim3(tile_grid(tm) + (beside ? stat_blocks : 0), ks), dim3(C::NT), 0, s, tm, a.n, h, D.d,
+                       static_cast<const bf16_t*>(c->W_hq), epi, ks, splitk, stat_part,
+                       beside ? stats : static_cast<float2*>(nullptr), D.ln_eps, nm);
+    if (ks > 1) {
+      const int ct = combine_threads(a.n, N), cr = ct / 16;
+      hipLaunchKernelGGL(hq_combine_kernel<T>, dim3((N + 127) / 128, (a.n + cr - 1) / cr), dim3(ct), 0, s,
                          epi, ks, static_cast<const float*>(splitk),
                          static_cast<const float2*>(stat_part), D.d, D.ln_eps);
+    }
   }
   // 3. scores for every (node, key) of each request
   if (a.m_max > 0) {
@@ -610,11 +630,19 @@ fovea_status run_retrieve_fuse(fovea_ctx* c, const RFArgs& a, hipStream_t s) {
     epi.w_g2 = c->w_g2;
     epi.a_c = a_c;
     ProfScope ps(pc, kCorr1, s);
-    hipLaunchKernelGGL(corr1_kernel<T>, dim3(tile_grid(tm), ksp.c1), dim3(C::NT), 0, s, tm, rT, D.d_m,
-                       static_cast<const bf16_t*>(c->W1r), epi, gate_part, ksp.c1, splitk);
-    if (ksp.c1 > 1)
-      hipLaunchKernelGGL(corr1_combine_kernel<T>, dim3((epi.N + 127) / 128, (a.n + 15) / 16), dim3(256), 0,
+    if (skinny1) {
+      if constexpr (std::is_same<T, bf16_t>::value)
+        hipLaunchKernelGGL(corr1_skinny_kernel, dim3(epi.N / 16, (a.n + 31) / 32), dim3(512), 0, s, rT, D.d_m,
+                           static_cast<const bf16_t*>(c->W1r), epi, P);
+    } else {
+      hipLaunchKernelGGL(corr1_kernel<T>, dim3(tile_grid(tm), ksp.c1), dim3(C::NT), 0, s, tm, rT, D.d_m,
+                         static_cast<const bf16_t*>(c->W1r), epi, gate_part, ksp.c1, splitk);
+    }
+    if (ksp.c1 > 1 && !skinny1) {
+      const int ct = combine_threads(a.n, epi.N), cr = ct / 16;
+      hipLaunchKernelGGL(corr1_combine_kernel<T>, dim3((epi.N + 127) / 128, (a.n + cr - 1) / cr), dim3(ct), 0,
                          s, epi, gate_part, ksp.c1, static_cast<const float*>(splitk));
+    }
   }
   // 6. correction layer 2, gate, residual (+ RMS partials)
   T* h_out = static_cast<T*>(a.h_out);
@@ -633,20 +661,38 @@ fovea_status run_retrieve_fuse(fovea_ctx* c, const RFArgs& a, hipStream_t s) {
     epi.m0 = 0;
     Corr2Args ca;
     ca.d_c = D.d_c;
-    ca.gate_part = gate_part;
+    ca.gate_part = skinny1 ? P + D.d_c : gate_part;
+    ca.n_gate = skinny1 ? D.d_c / 16 : n_parts(2 * D.d_c);
+    ca.gate_step = skinny1 ? 16 : 1;
+    ca.gate_ld = skinny1 ? 2 * D.d_c : n_parts(2 * D.d_c);
     ca.b_g2 = c->b_g2;
     ca.gate_out = a.gate_out;
-    ca.rms_part = c->rms_w ? rms_part : nullptr;
+    ca.rms_part = c->rms_w ? (skinny2 ? P : rms_part) : nullptr;
     // split-K with the RMSNorm: the slices' sum, the residual and the norm in one pass
-    fused_rms = ksp.c2 > 1 && c->rms_w != nullptr && D.d <= kCorr2RmsMaxD;
-    {
+    fused_rms = ksp.c2 > 1 && c->rms_w != nullptr && D.d <= kCorr2RmsMaxD && !skinny2;
+    if (skinny2) {
+      if constexpr (std::is_same<T, bf16_t>::value) {
+        {
+          ProfScope ps(pc, kCorr2, s);
+          hipLaunchKernelGGL(corr2_skinny_kernel, dim3(D.d / 16, (a.n + 63) / 64), dim3(256), 0, s, a_c,
+                             static_cast<const bf16_t*>(c->W_c2), epi, ca, static_cast<int64_t>(2 * D.d_c));
+        }
+        if (c->rms_w) {
+          ProfScope ps(pc, kRms, s);
+          hipLaunchKernelGGL(rms_row_kernel, dim3(a.n), dim3(256), 0, s, D.d, ca.rms_part,
+                             static_cast<int64_t>(2 * D.d_c), c->rms_w, D.rms_eps, h_out);
+        }
+      }
+    } else {
       ProfScope ps(pc, kCorr2, s);
       hipLaunchKernelGGL((a.n <= 64 ? corr2_kernel<T, 64> : corr2_kernel<T>), dim3(tile_grid(tm), ksp.c2),
                          dim3(C::NT), 0, s, tm, a_c, static_cast<const bf16_t*>(c->W_c2), epi, ca, ksp.c2,
                          splitk);
-      if (ksp.c2 > 1 && !fused_rms)
-        hipLaunchKernelGGL(corr2_combine_kernel<T>, dim3((D.d + 127) / 128, (a.n + 15) / 16), dim3(256), 0, s,
+      if (ksp.c2 > 1 && !fused_rms) {
+        const int ct = combine_threads(a.n, D.d), cr = ct / 16;
+        hipLaunchKernelGGL(corr2_combine_kernel<T>, dim3((D.d + 127) / 128, (a.n + cr - 1) / cr), dim3(ct), 0, s,
                            epi, ca, ksp.c2, static_cast<const float*>(splitk));
+      }
     }
     if (fused_rms) {
       ProfScope ps(pc, kRms, s);
@@ -655,7 +701,7 @@ fovea_status run_retrieve_fuse(fovea_ctx* c, const RFArgs& a, hipStream_t s) {
     }
   }
   // 7. RMSNorm
-  if (c->rms_w && !fused_rms) {
+  if (c->rms_w && !fused_rms && !skinny2) {
     ProfScope ps(pc, kRms, s);
     hipLaunchKernelGGL(rms_kernel<T>, dim3((a.n + 3) / 4), dim3(256), 0, s, a.n, D.d, rms_part, c->rms_w,
                        D.rms_eps, h_out);

@@ -948,14 +948,14 @@ __device__ __forceinline__ void gemm_splitk_partial(const T* A, int M, const bf1
       NoRowSum{});
 }
 
-// One block of 256 threads per (16 rows, 128-column tile blockIdx.x): thread t owns
-// columns 8 (t % 16) .. + 7 of row 16 blockIdx.y + t / 16, sums the ks partials in slice
+// One block per (blockDim / 16 rows, 128-column tile blockIdx.x): thread t owns columns
+// 8 (t % 16) .. + 7 of row (blockDim / 16) blockIdx.y + t / 16, sums the ks partials in slice
 // order and calls f(row, col0, v) and fr(row, sum over the tile's 128 columns) exactly
 // as gemm_epilogue does (rows and columns past the matrix included: f drops them).
 template <class F, class FR>
 __device__ __forceinline__ void splitk_combine(int M, int N, int ks, const float* __restrict__ part,
                                                F&& f, FR&& fr) {
-  const int row = static_cast<int>(blockIdx.y) * 16 + static_cast<int>(threadIdx.x >> 4);
+  const int row = static_cast<int>(blockIdx.y * (blockDim.x >> 4) + (threadIdx.x >> 4));
   const int col0 = static_cast<int>(blockIdx.x) * 128 + static_cast<int>(threadIdx.x & 15) * 8;
   float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   if (row < M && col0 < N) {
@@ -975,6 +975,77 @@ __device__ __forceinline__ void splitk_combine(int M, int N, int ks, const float
   float s = f(row, col0, v);
   s = sum16(s);
   if ((threadIdx.x & 15) == 0) fr(row, s);
+}
+
+// ---------------------------------------------------------------------------------
+// Skinny GEMM for a few rows (bf16, one request's draft tree): a block of NW waves computes a
+// (16 RM) x 16 tile over the whole of K, wave w the w-th part of it, fragments straight from
+// global memory (no staging, up to U steps of 64 k in flight); the waves' sums are added in
+// wave order through LDS.  Bound by latency for short K, which is what it is for; over
+// K = 4096 the fragment loads (16 rows a load) run at a quarter of the staged core's rate.
+// Inside a step the k are permuted alike in A and B: lane group g takes 16 g .. + 7, then
+// 16 g + 8 .. + 15, so that every load touches both halves of its 128-byte lines.
+//   f(row, col0, v): 8 consecutive columns of a row as in gemm_epilogue (rows past M
+// included); the sum of its results over the tile's 16 columns goes to fr(row, sum).
+// Reached by every thread of the block.  K a multiple of 64.
+// ---------------------------------------------------------------------------------
+template <int RM, int NW, int U, class F, class FR>
+__device__ __forceinline__ void skinny_tile(const bf16_t* __restrict__ A, int M, const bf16_t* __restrict__ B,
+                                            int K, int m0, int n0, F&& f, FR&& fr) {
+  __shared__ __align__(16) float red[NW * RM * 4 * 64];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+  const int nk = K / 64, per = (nk + NW - 1) / NW;
+  const int s0 = wave * per, cnt = max(0, min(per, nk - s0));
+  const int r = lane & 15, kofs = s0 * 64 + 16 * (lane >> 4);
+  const bf16_t* pa[RM];
+#pragma unroll
+  for (int i = 0; i < RM; ++i) pa[i] = A + static_cast<int64_t>(min(m0 + 16 * i + r, M - 1)) * K + kofs;
+  const bf16_t* pb = B + static_cast<int64_t>(n0 + r) * K + kofs;
+  f32x4 acc[RM];
+#pragma unroll
+  for (int i = 0; i < RM; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int b0 = 0; b0 < cnt; b0 += U) {
+    bf16x8 a[U][RM][2], b[U][2];
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (b0 + u < cnt)  // uniform
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          b[u][q] = *reinterpret_cast<const bf16x8*>(pb + (b0 + u) * 64 + 8 * q);
+#pragma unroll
+          for (int i = 0; i < RM; ++i)
+            a[u][i][q] = *reinterpret_cast<const bf16x8*>(pa[i] + (b0 + u) * 64 + 8 * q);
+        }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (b0 + u < cnt)
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+          for (int i = 0; i < RM; ++i) acc[i] = mfma_bf16_16x16x32(a[u][i][q], b[u][q], acc[i]);
+  }
+#pragma unroll
+  for (int i = 0; i < RM; ++i)
+#pragma unroll
+    for (int v = 0; v < 4; ++v) red[((wave * RM + i) * 4 + v) * 64 + lane] = acc[i][v];
+  __syncthreads();
+  const int t = threadIdx.x;
+  if (t < 32 * RM) {  // whole waves (RM even)
+    const int row = t >> 1, c8 = (t & 1) * 8;
+    const int e = ((row >> 4) * 4 + (row & 3)) * 64 + 16 * ((row & 15) >> 2) + c8;
+    float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      float x[8];
+      load8(red + w * RM * 256 + e, x);
+#pragma unroll
+      for (int q = 0; q < 8; ++q) v[q] += x[q];
+    }
+    float sum = f(m0 + row, n0 + c8, v);
+    sum += __shfl_xor(sum, 1, kWave);
+    if ((t & 1) == 0) fr(m0 + row, sum);
+  }
 }
 
 // Number of K slices for a GEMM of `tiles` output tiles: powers of two while the grid

@@ -455,12 +455,9 @@ __global__ __launch_bounds__(512, 2) void mem_proj_pp_kernel(TileMap tm, const b
 template <typename T>
 __global__ void pack_rows_kernel(const T* __restrict__ W, int64_t ldw, const T* __restrict__ g, int64_t rows,
                                  int cols, bf16_t* __restrict__ out) {
-  const int64_t total = rows * (cols / 8);
   const bool aligned = ((reinterpret_cast<uintptr_t>(W) | static_cast<uintptr_t>(ldw * sizeof(T))) & 15u) == 0;
-  for (int64_t i = blockIdx.x * static_cast<int64_t>(blockDim.x) + threadIdx.x; i < total;
-       i += static_cast<int64_t>(gridDim.x) * blockDim.x) {
-    const int64_t r = i / (cols / 8);
-    const int j = static_cast<int>(i % (cols / 8)) * 8;
+  for (int64_t r = blockIdx.x; r < rows; r += gridDim.x)
+  for (int j = 8 * threadIdx.x; j < cols; j += 8 * blockDim.x) {
     float x[8];
     if (aligned)
       load8(W + r * ldw + j, x);
@@ -489,16 +486,34 @@ __global__ void row_dot_kernel(const T* __restrict__ W, int rows, int cols, cons
   if (item >= rows * n_l) return;
   const int l = item / rows, i = item % rows;
   const T* wr = W + static_cast<int64_t>(i) * cols;
+  const T* er = E != nullptr ? E + static_cast<int64_t>(l) * cols : nullptr;
+  const bool aligned = ((reinterpret_cast<uintptr_t>(W) | reinterpret_cast<uintptr_t>(b) |
+                         reinterpret_cast<uintptr_t>(E) | reinterpret_cast<uintptr_t>(g)) & 15u) == 0;
+  auto get = [&](const T* p, int j, float (&x)[8]) {  // 8 columns from j
+    if (aligned)
+      load8(p + j, x);
+    else
+#pragma unroll
+      for (int e = 0; e < 8; ++e) x[e] = Elem<T>::to_f32(p[j + e]);
+  };
   double s = 0.0;
-  for (int j = lane; j < cols; j += 64) {
+#pragma unroll 2
+  for (int j = 8 * lane; j < cols; j += 512) {
+    float w[8], y[8], z[8];
+    get(wr, j, w);
+    get(b == nullptr ? g : b, j, y);
     if (b == nullptr) {
-      const T w = Elem<T>::from_f32(Elem<T>::to_f32(wr[j]) * Elem<T>::to_f32(g[j]));
-      s += static_cast<double>(Elem<T>::to_f32(w));
+#pragma unroll
+      for (int e = 0; e < 8; ++e) s += static_cast<double>(Elem<T>::to_f32(Elem<T>::from_f32(w[e] * y[e])));
       continue;
     }
-    double x = static_cast<double>(Elem<T>::to_f32(b[j]));
-    if (E != nullptr) x += static_cast<double>(Elem<T>::to_f32(E[static_cast<int64_t>(l) * cols + j]));
-    s += static_cast<double>(Elem<T>::to_f32(wr[j])) * x;
+    if (er != nullptr) get(er, j, z);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      double x = static_cast<double>(y[e]);
+      if (er != nullptr) x += static_cast<double>(z[e]);
+      s += static_cast<double>(w[e]) * x;
+    }
   }
   s = wave_sum(s);
   if (lane == 0) out[item] = static_cast<float>(s);

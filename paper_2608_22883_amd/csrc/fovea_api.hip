@@ -111,6 +111,30 @@ SplitK forward_splitk(const fovea_dims& D, int64_t n) {
   return k;
 }
 
+// The slices a call runs with: forward_splitk's, or for the hidden-state GEMM of a few hundred
+// bf16 nodes 64-row tiles over all of K instead of 128-row slices and a combine, while they
+// fill most of the compute units in one round (768 x 1920 x 3584, 180 tiles: 30 + 7 us in 2
+// slices against 27.6 and the statistics' 5; 512 x 2304 x 5120, 144 tiles: 45 us either way).
+SplitK run_splitk(const fovea_dims& D, int64_t n) {
+  SplitK k = forward_splitk(D, n);
+  const int64_t hq = (n + 63) / 64 * ((D.d_m + 2 * D.d_c + 127) / 128);
+  if (D.dtype == FOVEA_BF16 && n > 64 && hq >= 160 && hq <= 256) k.hq = 1;
+  return k;
+}
+
+// 64-row tiles of the hidden-state GEMM and of layer 2: one tile row of a small batch, or bf16
+// batches whose 128-row tiles would leave compute units idle (layer 2, 512 x 5120 x 512: 20
+// -> 16 us)
+bool hq_rows64(const fovea_dims& D, int64_t n) {
+  if (n <= 64) return true;
+  return D.dtype == FOVEA_BF16 && run_splitk(D, n).hq == 1 &&
+         (n + 63) / 64 * ((D.d_m + 2 * D.d_c + 127) / 128) <= 256;
+}
+
+bool c2_rows64(const fovea_dims& D, int64_t n) {
+  return n <= 64 || (D.dtype == FOVEA_BF16 && (n + 127) / 128 * ((D.d + 127) / 128) < 256);
+}
+
 WsLayout ws_layout(const fovea_dims& dm, int64_t n, int64_t m_max) {
   const size_t es = dm.dtype == FOVEA_BF16 ? 2 : 4;
   WsLayout L;
@@ -447,7 +471,7 @@ fovea_status run_retrieve_fuse(fovea_ctx* c, const RFArgs& a, hipStream_t s) {
   const fovea_dims& D = c->dims;
   fovea_ctx* const pc = a.track ? c : nullptr;  // profiling context, if any
   const WsLayout L = ws_layout(D, a.n, a.m_max);
-  const SplitK ksp = forward_splitk(D, a.n);
+  const SplitK ksp = run_splitk(D, a.n);
   float* splitk = reinterpret_cast<float*>(a.ws + L.splitk);
   int32_t* node_req = reinterpret_cast<int32_t*>(a.ws + L.node_req);
   NodeInfo* info = reinterpret_cast<NodeInfo*>(a.ws + L.info);
@@ -476,7 +500,9 @@ fovea_status run_retrieve_fuse(fovea_ctx* c, const RFArgs& a, hipStream_t s) {
   {
     using C = HqCfg<T>;
     const int N = D.d_m + 2 * D.d_c;
-    const TileMap tm = make_tile_map((a.n + C::BM - 1) / C::BM, (N + C::BN - 1) / C::BN,
+    const bool rows64 = hq_rows64(D, a.n);
+    const int bm = rows64 ? 64 : C::BM;
+    const TileMap tm = make_tile_map((a.n + bm - 1) / bm, (N + C::BN - 1) / C::BN,
                                      static_cast<double>(a.n) * D.d, static_cast<double>(N) * D.d);
     HqEpi<T> epi;
     epi.n = a.n;
@@ -493,7 +519,6 @@ fovea_status run_retrieve_fuse(fovea_ctx* c, const RFArgs& a, hipStream_t s) {
     epi.P = P;
     const int ks = ksp.hq;
     ProfScope ps(pc, kHq, s);
-    // at most 64 rows: the same single row of tiles in 64-row tiles (no clamped rows)
     float2* stat_part = split_stats ? stats : nullptr;
     NodeMapArgs nm;
     {
@@ -515,7 +540,7 @@ fovea_status run_retrieve_fuse(fovea_ctx* c, const RFArgs& a, hipStream_t s) {
     const int stat_blocks = (a.n + 3) / 4;
     const bool beside = split_stats && tile_grid(tm) * ks + stat_blocks * ks <= 256;
     if (beside) stat_part = nullptr;
-    hipLaunchKernelGGL((a.n <= 64 ? hq_kernel<T, 64> : hq_kernel<T>),
+    hipLaunchKernelGGL((rows64 ? hq_kernel<T, 64> : hq_kernel<T>),
                        dim3(tile_grid(tm) + (beside ? stat_blocks : 0), ks), dim3(C::NT), 0, s, tm, a.n, h, D.d,
                        static_cast<const bf16_t*>(c->W_hq), epi, ks, splitk, stat_part,
                        beside ? stats : static_cast<float2*>(nullptr), D.ln_eps, nm);
@@ -649,7 +674,9 @@ fovea_status run_retrieve_fuse(fovea_ctx* c, const RFArgs& a, hipStream_t s) {
   bool fused_rms = false;
   {
     using C = Corr2Cfg<T>;
-    const TileMap tm = make_tile_map((a.n + C::BM - 1) / C::BM, (D.d + C::BN - 1) / C::BN,
+    const bool rows64 = c2_rows64(D, a.n);
+    const int bm = rows64 ? 64 : C::BM;
+    const TileMap tm = make_tile_map((a.n + bm - 1) / bm, (D.d + C::BN - 1) / C::BN,
                                      static_cast<double>(a.n) * D.d_c, static_cast<double>(D.d) * D.d_c);
     Corr2Epi<T> epi;
     epi.n = a.n;
@@ -685,7 +712,7 @@ fovea_status run_retrieve_fuse(fovea_ctx* c, const RFArgs& a, hipStream_t s) {
       }
     } else {
       ProfScope ps(pc, kCorr2, s);
-      hipLaunchKernelGGL((a.n <= 64 ? corr2_kernel<T, 64> : corr2_kernel<T>), dim3(tile_grid(tm), ksp.c2),
+      hipLaunchKernelGGL((rows64 ? corr2_kernel<T, 64> : corr2_kernel<T>), dim3(tile_grid(tm), ksp.c2),
                          dim3(C::NT), 0, s, tm, a_c, static_cast<const bf16_t*>(c->W_c2), epi, ca, ksp.c2,
                          splitk);
       if (ksp.c2 > 1 && !fused_rms) {

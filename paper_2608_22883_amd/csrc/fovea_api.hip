@@ -48,7 +48,7 @@ struct fovea_ctx {
   float* rms_w;  // [d] or null
   uint32_t* err;  // sticky device-data error bits
   void* scratch;  // device address of this device's no-allocation workspace
-  size_t lds_limit[5];  // dynamic LDS limit of each LdsKernel
+  size_t lds_limit[3];  // dynamic LDS limit of each LdsKernel
   // one completion event per stream that calls have enqueued work on: fovea_destroy
   // waits for these (not for the whole device) before it frees the packed weights
   struct StreamUse {
@@ -67,7 +67,7 @@ struct fovea_ctx {
 };
 
 // kernels whose dynamic LDS limit the context sets (raise_lds_limits)
-enum LdsKernel { kLdsSelBf16, kLdsSelF32, kLdsBwdMem, kLdsBwdSelFwd, kLdsBwdSel, kNumLdsKernels };
+enum LdsKernel { kLdsBwdMem, kLdsBwdSelFwd, kLdsBwdSel, kNumLdsKernels };
 
 namespace {
 
@@ -247,8 +247,6 @@ constexpr int kLdsBytes = 160 * 1024;
 
 fovea_status raise_lds_limits(fovea_ctx* c) {
   const void* kernels[kNumLdsKernels] = {
-      reinterpret_cast<const void*>(select_gather_kernel<bf16_t>),
-      reinterpret_cast<const void*>(select_gather_kernel<float>),
       reinterpret_cast<const void*>(bwd_mem_grad_kernel),
       reinterpret_cast<const void*>(bwd_sel_fwd_kernel),
       reinterpret_cast<const void*>(bwd_sel_kernel)};
@@ -601,9 +599,8 @@ fovea_status run_retrieve_fuse(fovea_ctx* c, const RFArgs& a, hipStream_t s) {
     ProfScope ps(pc, kSelect, s);
     const int VEC = D.dtype == FOVEA_BF16 ? 8 : 4;
     const int nch = (D.d_m / VEC + 63) / 64;  // 16-byte chunks per lane per value row
-    // one wave selects a node of at most 1024 entries (16 keys per lane); larger memories
-    // go to the block-wide kernel, whose radix threshold and counting rank use all four
-    // waves (ragged Qwen workload, memories of up to 4096: 98.6 -> 41.4 us)
+    // one wave selects a node of at most 1024 entries (16 keys per lane); larger memories,
+    // wider value rows and larger k_max go to the block-wide kernel
     const bool wave_path = a.k_max <= kWaveSelKmax && a.m_max <= 1024 && nch <= 4;
     if (wave_path) {
       // one node per block when the pairs would leave compute units idle: the gather of a
@@ -630,15 +627,18 @@ fovea_status run_retrieve_fuse(fovea_ctx* c, const RFArgs& a, hipStream_t s) {
 #undef FOVEA_SEL
 #undef FOVEA_SEL_C
     } else {
-      // the order keys (later the gather's partial sums) and the candidate arrays
-      const size_t sel_smem = static_cast<size_t>(select_gather_smem(a.m_max, a.k_max, VEC));
-      if (sel_smem > c->lds_limit[std::is_same<T, bf16_t>::value ? kLdsSelBf16 : kLdsSelF32])
-        return FOVEA_ERR_UNSUPPORTED;
       // few nodes: each node's row is also split into column slices over several blocks
       // (each repeats the selection) so that the gathers run on more compute units
       const int cpr64 = (D.d_m / VEC + 63) / 64;
       const int slices = std::max(1, std::min(cpr64, 512 / std::max(a.n, 1)));
-      hipLaunchKernelGGL(select_gather_kernel<T>, dim3(a.n, slices), dim3(256), sel_smem, s, sa);
+      const int nk = (a.m_max + kSelNT - 1) / kSelNT;  // keys per thread
+      auto kern = nk <= 2    ? select_gather_kernel<T, 2>
+                  : nk <= 4  ? select_gather_kernel<T, 4>
+                  : nk <= 8  ? select_gather_kernel<T, 8>
+                  : nk <= 16 ? select_gather_kernel<T, 16>
+                             : select_gather_kernel<T, 32>;
+      static_assert(kMaxM <= 32 * kSelNT, "keys per thread");
+      hipLaunchKernelGGL(kern, dim3(a.n, slices), dim3(kSelNT), 0, s, sa);
     }
   }
   // 5. correction layer 1: the r half, plus P, bias and SiLU (+ gate logit partials)

@@ -805,11 +805,11 @@ __global__ __launch_bounds__(256) void score_f32_kernel(int B, const int64_t* __
 }
 
 // ---------------------------------------------------------------------------------
-// Per-node selection and gather, one 256-thread block per node:
-//   max and Z over the valid scores; exact top-k_max by (score desc, index asc) with an
-//   MSB-first radix select on the order-preserving score key (plus, for ties, on the
-//   inverted index); candidates ranked by counting; prefix masses in fp64; K from the
-//   cumulative-mass rule; renormalised weights; weighted gather of value rows.
+// Per-node selection and gather: max and Z over the valid scores; exact top-k_max by (score
+// desc, index asc); candidates ranked by counting; prefix masses in fp64; K from the
+// cumulative-mass rule; renormalised weights; weighted gather of value rows.  One wave selects
+// a node of at most 1024 entries (select_node_kernel), a block a larger one
+// (select_gather_kernel).
 // ---------------------------------------------------------------------------------
 
 constexpr int kScoreMaxParts = 4;  // k slices of the score GEMM (partial score arrays)
@@ -837,12 +837,13 @@ struct SelectArgs {
   uint32_t* err;
 };
 
+// Sums and maxima over a block of NT threads, in every thread (red: NT / 64 values of LDS;
+// wave results added in wave order).
 template <int NT>
 __device__ __forceinline__ int block_sum_int(int v, int* red) {
-  v = wave_sum(v);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  v = wave_sum_i32(v);
   __syncthreads();
-  if (lane == 0) red[wave] = v;
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
   __syncthreads();
   int s = 0;
 #pragma unroll
@@ -852,10 +853,9 @@ __device__ __forceinline__ int block_sum_int(int v, int* red) {
 
 template <int NT>
 __device__ __forceinline__ double block_sum_f64(double v, double* red) {
-  v = wave_sum(v);
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  v = wave_sum_f64(v);
   __syncthreads();
-  if (lane == 0) red[wave] = v;
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
   __syncthreads();
   double s = 0.0;
 #pragma unroll
@@ -865,67 +865,14 @@ __device__ __forceinline__ double block_sum_f64(double v, double* red) {
 
 template <int NT>
 __device__ __forceinline__ uint32_t block_max_u32(uint32_t v, uint32_t* red) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) v = max(v, static_cast<uint32_t>(__shfl_xor(static_cast<int>(v), o, kWave)));
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  v = wave_max_u32(v);
   __syncthreads();
-  if (lane == 0) red[wave] = v;
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
   __syncthreads();
   uint32_t m = 0;
 #pragma unroll
   for (int w = 0; w < NT / 64; ++w) m = max(m, red[w]);
   return m;
-}
-
-// Radix step: among elements whose key matches `prefix` on `pmask`, histogram the
-// 8-bit digit at `shift` and find the digit holding the krem-th largest element.
-// Returns the digit; *above = elements in higher digits, *in_bin = elements in it.
-struct RadixPick {
-  int digit, above, in_bin;
-};
-
-__device__ __forceinline__ RadixPick radix_pick(int* hist, int krem, RadixPick* out) {
-  // called by wave 0 after the histogram is complete; lane l owns bins 255-4l .. 252-4l
-  const int lane = threadIdx.x & 63;
-  int cnt[4], tot = 0;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    cnt[j] = hist[255 - 4 * lane - j];
-    tot += cnt[j];
-  }
-  int incl = tot;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int y = __shfl_up(incl, o, kWave);
-    if (lane >= o) incl += y;
-  }
-  int run = incl - tot;  // elements in bins above this lane's bins
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    if (run < krem && run + cnt[j] >= krem) {
-      out->digit = 255 - 4 * lane - j;
-      out->above = run;
-      out->in_bin = cnt[j];
-    }
-    run += cnt[j];
-  }
-  return *out;
-}
-
-// keys read per load round in the block-wide selection's scans over its LDS keys, for
-// memories of more than kSelScanB * 256 entries (shorter ones scan one key at a time)
-constexpr int kSelScanB = 8;
-
-// Dynamic LDS of select_gather_kernel: the order keys (or the gather's partial sums,
-// 3 x 64 lanes x VEC floats, whichever is larger; 8-byte aligned end), then the candidate
-// keys (8 B), prefix masses (8 B), weights (4 B) and indices (4 B) of kcap slots.
-__host__ __device__ inline int select_kcap(int k_max) { return (k_max + 3) & ~3; }
-__host__ __device__ inline int select_key_bytes(int m_max, int vec) {
-  const int b = m_max * 4 > 3 * 64 * vec * 4 ? m_max * 4 : 3 * 64 * vec * 4;
-  return (b + 7) & ~7;
-}
-__host__ __device__ inline int select_gather_smem(int m_max, int k_max, int vec) {
-  return select_key_bytes(m_max, vec) + select_kcap(k_max) * 24;
 }
 
 // exp(s - smax) of an order key as 2^((s - smax) log2 e) on the hardware exp2 (relative
@@ -960,382 +907,6 @@ __device__ __forceinline__ void rank_sort_desc(unsigned long long* list, int C, 
     if (tid + NT * q < C) list[rk[q]] = mine[q];
   __syncthreads();
 }
-
-template <typename T>
-__global__ __launch_bounds__(256) void select_gather_kernel(SelectArgs<T> a) {
-  constexpr int NT = 256;
-  // dynamic LDS (select_gather_smem): the order keys [m_max] (0 marks a masked entry;
-  // later the gather's partial sums), then the candidate arrays sized for k_max, so that
-  // two blocks share a compute unit even at 16384 keys
-  extern __shared__ __align__(16) unsigned char sel_smem[];
-  uint32_t* skey = reinterpret_cast<uint32_t*>(sel_smem);
-  const int kcap = select_kcap(a.k_max);
-  unsigned long long* cand =
-      reinterpret_cast<unsigned long long*>(sel_smem + select_key_bytes(a.m_max, Elem<T>::kPer16B));
-  double* pre = reinterpret_cast<double*>(cand + kcap);
-  float* alpha = reinterpret_cast<float*>(pre + kcap);
-  int* sidx = reinterpret_cast<int*>(alpha + kcap);
-  __shared__ int hist[256];
-  __shared__ int ired[NT / 64];
-  __shared__ double dred[NT / 64];
-  __shared__ uint32_t ured[NT / 64];
-  __shared__ RadixPick pick;
-  __shared__ int s_count, s_first;
-
-  const int n = blockIdx.x;
-  const int tid = threadIdx.x;
-  const int b = a.node_req[n];
-  int64_t m0 = 0, m1 = 0;
-  bool ok = b >= 0;
-  if (ok) {
-    m0 = a.mem_off[b];
-    m1 = a.mem_off[b + 1];
-    if (!(0 <= m0 && m0 <= m1 && m1 <= a.n_mem && m1 - m0 <= a.m_max)) {
-      ok = false;
-      if (tid == 0) atomicOr(a.err, kErrMemOff);
-    }
-  }
-  const int64_t rbase = static_cast<int64_t>(n) * a.d_m;
-  if (!ok) {
-    const float qnan = __builtin_nanf("");
-    for (int c = tid; c < a.d_m; c += NT) {
-      st_f32(a.rT, rbase + c, qnan);
-      if (a.r_out) a.r_out[rbase + c] = qnan;
-    }
-    if (a.idx_out)
-      for (int t = tid; t < a.k_max; t += NT) a.idx_out[static_cast<int64_t>(n) * a.k_max + t] = -1;
-    if (tid == 0) {
-      if (a.k_out) a.k_out[n] = 0;
-      if (a.mass_out) a.mass_out[n] = qnan;
-    }
-    return;
-  }
-  const int M = static_cast<int>(m1 - m0);
-  const float* srow = a.S + static_cast<int64_t>(n) * a.m_max;
-
-  // keys, valid count, max
-  int cnt = 0;
-  uint32_t kmax = 0;
-  // U entries per thread and step, every load issued before the first use (16 for long
-  // memories, whose rows take many steps; 4 otherwise)
-  auto load_keys = [&](auto U_) {
-    constexpr int U = decltype(U_)::value;
-    for (int i0 = tid; i0 < M; i0 += U * NT) {
-      float sc[U], ps[U][kScoreMaxParts - 1];
-      bool v[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int i = i0 + u * NT;
-        const bool in = i < M;
-        sc[u] = in ? srow[i] : 0.f;
-#pragma unroll
-        for (int p = 1; p < kScoreMaxParts; ++p)
-          ps[u][p - 1] = in && p < a.s_parts ? srow[p * a.s_stride + i] : 0.f;
-        v[u] = in && (a.valid == nullptr || a.valid[m0 + i] != 0);
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int i = i0 + u * NT;
-        if (i < M) {
-#pragma unroll
-          for (int p = 1; p < kScoreMaxParts; ++p)
-            if (p < a.s_parts) sc[u] += ps[u][p - 1];
-          const uint32_t k = v[u] ? order_key(sc[u]) : 0u;
-          skey[i] = k;
-          cnt += v[u] ? 1 : 0;
-          kmax = max(kmax, k);
-        }
-      }
-    }
-  };
-  if (M > 16 * NT)
-    load_keys(std::integral_constant<int, 16>());
-  else
-    load_keys(std::integral_constant<int, 4>());
-  const int nV = block_sum_int<NT>(cnt, ired);
-  kmax = block_max_u32<NT>(kmax, ured);
-
-  int K = 0;
-  double mass = 0.0;
-  if (nV > 0) {
-    const float smax = key_to_float(kmax);
-    double z = 0.0;
-    for (int i = tid; i < M; i += NT) {
-      const uint32_t k = skey[i];
-      if (k != 0u) z += static_cast<double>(key_mass(k, smax));
-    }
-    const double Z = block_sum_f64<NT>(z, dred);
-
-    // ---- candidates: the top min(nV, k_max) entries ----
-    const int C = min(nV, a.k_max);
-    uint32_t thr = 0u, thr_inv = 0u;
-    bool all_eq = true;
-    if (nV > a.k_max) {
-      uint32_t prefix = 0u, pmask = 0u;
-      int krem = a.k_max;
-      int in_bin = 0;
-      for (int shift = 24; shift >= 0; shift -= 8) {
-        hist[tid] = 0;
-        __syncthreads();
-        // a thread's keys mostly share a digit: one atomic per run of equal digits; the
-        // keys are read SB at a time (all reads issued before the first use)
-        int cur = -1, run = 0;
-        auto hist_scan = [&](auto SB_) {
-          constexpr int SB = decltype(SB_)::value;
-          for (int i0 = tid; i0 < M; i0 += SB * NT) {
-            uint32_t kk[SB];
-#pragma unroll
-            for (int u = 0; u < SB; ++u) kk[u] = i0 + u * NT < M ? skey[i0 + u * NT] : 0u;
-#pragma unroll
-            for (int u = 0; u < SB; ++u) {
-              const uint32_t k = kk[u];
-              if (k != 0u && (k & pmask) == prefix) {
-                const int dg = static_cast<int>((k >> shift) & 255u);
-                if (dg != cur) {
-                  if (run > 0) atomicAdd(&hist[cur], run);
-                  cur = dg;
-                  run = 0;
-                }
-                ++run;
-              }
-            }
-          }
-        };
-        if (M > kSelScanB * NT)
-          hist_scan(std::integral_constant<int, kSelScanB>());
-        else
-          hist_scan(std::integral_constant<int, 1>());
-        if (run > 0) atomicAdd(&hist[cur], run);
-        __syncthreads();
-        if (tid < 64) radix_pick(hist, krem, &pick);
-        __syncthreads();
-        prefix |= static_cast<uint32_t>(pick.digit) << shift;
-        pmask |= 255u << shift;
-        krem -= pick.above;
-        in_bin = pick.in_bin;
-        __syncthreads();
-      }
-      thr = prefix;
-      if (in_bin > krem) {
-        // ties at the threshold score: keep the krem lowest indices (largest 0xFFFF - i)
-        all_eq = false;
-        uint32_t iprefix = 0u, imask = 0u;
-        for (int shift = 8; shift >= 0; shift -= 8) {
-          hist[tid] = 0;
-          __syncthreads();
-          for (int i = tid; i < M; i += NT) {
-            const uint32_t inv = 0xFFFFu - static_cast<uint32_t>(i);
-            if (skey[i] == thr && (inv & imask) == iprefix) atomicAdd(&hist[(inv >> shift) & 255u], 1);
-          }
-          __syncthreads();
-          if (tid < 64) radix_pick(hist, krem, &pick);
-          __syncthreads();
-          iprefix |= static_cast<uint32_t>(pick.digit) << shift;
-          imask |= 255u << shift;
-          krem -= pick.above;
-          __syncthreads();
-        }
-        thr_inv = iprefix;
-      }
-    }
-    if (tid == 0) s_count = 0;
-    __syncthreads();
-    // the candidates appended in any order (the ranking below orders them); long memories:
-    // per wave one atomic per step for all its lanes' picks, keys read SB at a time
-    auto compact = [&](auto SB_) {
-      constexpr int SB = decltype(SB_)::value;
-      for (int i0 = tid - (tid & 63); i0 < M; i0 += SB * NT) {
-        uint32_t kk[SB];
-#pragma unroll
-        for (int u = 0; u < SB; ++u) {
-          const int i = i0 + (tid & 63) + u * NT;
-          kk[u] = i < M ? skey[i] : 0u;
-        }
-#pragma unroll
-        for (int u = 0; u < SB; ++u) {
-          const int i = i0 + (tid & 63) + u * NT;
-          const uint32_t k = kk[u];
-          const bool take = k != 0u && (nV <= a.k_max || k > thr ||
-                                        (k == thr && (all_eq || 0xFFFFu - static_cast<uint32_t>(i) >= thr_inv)));
-          const unsigned long long bal = __ballot(take);
-          if (bal == 0ull) continue;  // wave-uniform
-          int base = 0;
-          if ((tid & 63) == __ffsll(static_cast<long long>(bal)) - 1) base = atomicAdd(&s_count, __popcll(bal));
-          base = __shfl(base, __ffsll(static_cast<long long>(bal)) - 1, kWave);
-          if (take) {
-            const int pos = base + __popcll(bal & ((1ull << (tid & 63)) - 1ull));
-            if (pos < kcap)
-              cand[pos] = (static_cast<unsigned long long>(k) << 32) |
-                          static_cast<unsigned long long>(0xFFFFFFFFu - static_cast<uint32_t>(i));
-          }
-        }
-      }
-    };
-    if (M > kSelScanB * NT) {
-      compact(std::integral_constant<int, kSelScanB>());
-    } else {
-      for (int i = tid; i < M; i += NT) {
-        const uint32_t k = skey[i];
-        if (k == 0u) continue;
-        const bool take = nV <= a.k_max || k > thr ||
-                          (k == thr && (all_eq || 0xFFFFu - static_cast<uint32_t>(i) >= thr_inv));
-        if (take) {
-          const int pos = atomicAdd(&s_count, 1);
-          if (pos < kcap)
-            cand[pos] = (static_cast<unsigned long long>(k) << 32) |
-                        static_cast<unsigned long long>(0xFFFFFFFFu - static_cast<uint32_t>(i));
-        }
-      }
-    }
-    __syncthreads();
-    // s_count equals C by construction; never let a short count expose stale slots
-    const int C_ok = min(C, s_count);
-    // (distinct values below every real key, which has a nonzero high word)
-    for (int i = C_ok + tid; i < C; i += NT) cand[i] = static_cast<unsigned long long>(C - i);
-    __syncthreads();
-    // descending order by counting (the keys are distinct: each holds its entry index)
-    if (C <= NT)
-      rank_sort_desc<1, NT>(cand, C, tid);
-    else
-      rank_sort_desc<kMaxKmax / NT, NT>(cand, C, tid);
-    // prefix sums of exp(s - max) in rank order, four consecutive ranks per thread
-    double e4[4];
-    double loc = 0.0;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int t = 4 * tid + j;
-      e4[j] = t < C ? static_cast<double>(key_mass(static_cast<uint32_t>(cand[t] >> 32), smax))
-                    : 0.0;
-      loc += e4[j];
-      e4[j] = loc;
-    }
-    // exclusive scan of the thread totals
-    {
-      const int lane = tid & 63, wave = tid >> 6;
-      double incl = loc;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const double y = __shfl_up(incl, o, kWave);
-        if (lane >= o) incl += y;
-      }
-      __syncthreads();
-      if (lane == 63) dred[wave] = incl;
-      __syncthreads();
-      double off = incl - loc;
-      for (int w = 0; w < wave; ++w) off += dred[w];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int t = 4 * tid + j;
-        if (t < kcap) pre[t] = off + e4[j];
-      }
-    }
-    if (tid == 0) s_first = INT_MAX;
-    __syncthreads();
-    // the first rank whose prefix reaches tau Z: the prefixes only grow with the rank, so
-    // a wave's first qualifying rank sits in its lowest qualifying lane (one atomic per wave)
-    const double tau = static_cast<double>(a.tau[b]);
-    {
-      int first = INT_MAX;
-#pragma unroll
-      for (int j = 3; j >= 0; --j) {
-        const int t = 4 * tid + j;
-        if (t < C && pre[t] / Z >= tau) first = t;
-      }
-      const unsigned long long hit = __ballot(first != INT_MAX);
-      if (hit != 0ull && (tid & 63) == __ffsll(static_cast<long long>(hit)) - 1) atomicMin(&s_first, first);
-    }
-    __syncthreads();
-    const int K_raw = s_first != INT_MAX ? s_first + 1 : (C == nV ? nV : a.k_max + 1);
-    K = min(nV, min(a.k_max, max(a.k_min, K_raw)));
-    mass = pre[K - 1] / Z;
-    const double sumI = pre[K - 1];
-    for (int t = tid; t < K; t += NT) {
-      const float et = key_mass(static_cast<uint32_t>(cand[t] >> 32), smax);
-      alpha[t] = static_cast<float>(static_cast<double>(et) / sumI);
-      const uint32_t ix = 0xFFFFFFFFu - static_cast<uint32_t>(cand[t]);
-      sidx[t] = static_cast<int>(min(ix, static_cast<uint32_t>(M - 1)));
-    }
-    __syncthreads();
-  }
-
-  // ---- renormalised gather r = sum_t alpha_t u_{idx_t} ----
-  // This block covers the 16-byte chunks [c_lo, c_hi) of the row (its column slice);
-  // lane l takes chunk c_lo + l + 64 j in pass j, wave w the ranks w, w + 4, .. in
-  // batches of GR rows whose loads all issue before the first multiply-add; the four
-  // partial sums are added by wave 0 in a fixed order through LDS.
-  {
-    constexpr int VEC = Elem<T>::kPer16B;
-    constexpr int GR = 8;
-    const int cpr = a.d_m / VEC;
-    const int ns = gridDim.y;
-    const int c_lo = static_cast<int>(static_cast<int64_t>(cpr) * blockIdx.y / ns);
-    const int c_hi = static_cast<int>(static_cast<int64_t>(cpr) * (blockIdx.y + 1) / ns);
-    const int lane = tid & 63, w = tid >> 6;
-    const int mine = K > w ? (K - w + 3) / 4 : 0;
-    float* red = reinterpret_cast<float*>(skey);  // the keys are no longer needed
-    for (int cb = c_lo; cb < c_hi; cb += 64) {
-      const int c = min(cb + lane, c_hi - 1);
-      float acc[VEC];
-#pragma unroll
-      for (int x = 0; x < VEC; ++x) acc[x] = 0.f;
-      // batches of 2 GR rows while that many remain, then of up to GR
-      auto batch = [&](auto G_, int q0, int nr) {
-        constexpr int G = decltype(G_)::value;
-        u32x4 raw[G];
-#pragma unroll
-        for (int r = 0; r < G; ++r) {
-          const int t = w + 4 * (q0 + min(r, nr - 1));
-          raw[r] = *reinterpret_cast<const u32x4*>(a.values + (m0 + sidx[t]) * a.d_m + c * VEC);
-        }
-#pragma unroll
-        for (int r = 0; r < G; ++r) {
-          if (r < nr) {
-            const float wt = alpha[w + 4 * (q0 + r)];
-            const T* v = reinterpret_cast<const T*>(&raw[r]);
-#pragma unroll
-            for (int x = 0; x < VEC; ++x) acc[x] = fmaf(wt, Elem<T>::to_f32(v[x]), acc[x]);
-          }
-        }
-      };
-      for (int q0 = 0; q0 < mine;) {
-        if (mine - q0 >= 2 * GR) {
-          batch(std::integral_constant<int, 2 * GR>(), q0, 2 * GR);
-          q0 += 2 * GR;
-        } else {
-          const int nr = min(GR, mine - q0);
-          batch(std::integral_constant<int, GR>(), q0, nr);
-          q0 += nr;
-        }
-      }
-      if (w > 0)
-#pragma unroll
-        for (int x = 0; x < VEC; ++x) red[((w - 1) * 64 + lane) * VEC + x] = acc[x];
-      __syncthreads();
-      if (w == 0 && cb + lane < c_hi) {
-#pragma unroll
-        for (int q = 0; q < 3; ++q)
-#pragma unroll
-          for (int x = 0; x < VEC; ++x) acc[x] += red[(q * 64 + lane) * VEC + x];
-        const int64_t o = rbase + static_cast<int64_t>(c) * VEC;
-#pragma unroll
-        for (int x = 0; x < VEC; ++x) {
-          st_f32(a.rT, o + x, acc[x]);
-          if (a.r_out) a.r_out[o + x] = acc[x];
-        }
-      }
-      __syncthreads();
-    }
-  }
-  if (blockIdx.y != 0) return;  // one block of the node writes the selection outputs
-  if (a.idx_out)
-    for (int t = tid; t < a.k_max; t += NT)
-      a.idx_out[static_cast<int64_t>(n) * a.k_max + t] = t < K ? sidx[t] : -1;
-  if (tid == 0) {
-    if (a.k_out) a.k_out[n] = K;
-    if (a.mass_out) a.mass_out[n] = static_cast<float>(mass);
-  }
-}
-
 
 // ---------------------------------------------------------------------------------
 // Per-node selection by one wave, for memories of at most 64 * NPL entries and
@@ -1815,6 +1386,328 @@ __global__ __launch_bounds__(256) void select_node_kernel(SelectArgs<T> a, int n
         }
       }
     }
+  }
+}
+
+// One block of 512 threads per node, NK order keys per thread in registers (memories of at
+// most 512 NK entries; 0 marks a masked or missing entry).  The top C = min(nV, k_max) entries:
+//  * the block's 1024 chunks (two per thread, NK / 2 keys each; single keys at NK = 2) have
+//    1024 maxima, whose C-th largest bounds the C-th largest key from below (wave 0 searches
+//    it bit by bit on ballots and stops within C / 16 of the count);
+//  * the few keys that reach the bound (about 290 of 16384 for C = 256) go to a list, which is
+//    ranked by counting; its first C entries are the candidates in order;
+//  * where the list would overflow (ties, or scores that crowd few chunks) the C-th largest
+//    key is searched over every register, ties cut by index.
+// Then the prefix masses, K, the weights, and the gather by eight waves.
+//   Bound by the latency of its phases and, for large K, of the value rows.  With the keys in
+// LDS, a histogram of every key per radix digit and four waves a node (512 nodes of 16384
+// entries): score row 13 us, normaliser 7, threshold 23, compaction 12, ranking 4, gather 18.
+constexpr int kSelNT = 512;
+constexpr int kSelList = 2048;  // candidate list entries (at least kMaxKmax)
+
+template <typename T, int NK>
+__global__ __launch_bounds__(kSelNT, 4) void select_gather_kernel(SelectArgs<T> a) {
+  constexpr int NT = kSelNT, NW = NT / 64, VEC = Elem<T>::kPer16B;
+  static_assert(kSelList >= kMaxKmax && kSelList % NT == 0, "list");
+  __shared__ unsigned long long cand[kSelList];  // later the gather's partial sums
+  __shared__ double pre[kMaxKmax];
+  __shared__ float alpha[kMaxKmax];
+  __shared__ int sidx[kMaxKmax];
+  __shared__ uint32_t cmax[2 * NT];
+  __shared__ int ired[NW];
+  __shared__ double dred[NW];
+  __shared__ uint32_t ured[NW];
+  __shared__ int s_first;
+  __shared__ uint32_t s_thr;
+  static_assert(sizeof(cand) >= (NW - 1) * 64 * VEC * sizeof(float), "partial sums");
+
+  const int n = blockIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const NodeInfo inf = a.info[n];
+  if (inf.M < 0) {  // offsets, depth, tau or memory range failed validation
+    write_invalid_node(a, n, tid, NT);
+    return;
+  }
+  const int M = inf.M;
+  const int64_t m0 = inf.m0;
+  const int64_t rbase = static_cast<int64_t>(n) * a.d_m;
+  const float* srow = a.S + static_cast<int64_t>(n) * a.m_max;
+
+  // entry of slot j: four consecutive entries per thread and group of four slots
+  auto entry = [&](int j) { return NK >= 4 ? 4 * (tid + NT * (j >> 2)) + (j & 3) : tid + NT * j; };
+  uint32_t kv[NK];
+  uint32_t kmax = 0;
+  int cnt = 0;
+  {
+    float sc[NK];
+    // rows of m_max floats are 16-byte aligned where m_max is a multiple of 4
+    const bool vec = (a.m_max & 3) == 0;
+    auto load = [&](const float* p, float (&x)[NK]) {
+      if constexpr (NK >= 4) {
+        if (vec) {
+#pragma unroll
+          for (int j = 0; j < NK; j += 4) {
+            const f32x4 v = entry(j) < M ? *reinterpret_cast<const f32x4*>(p + entry(j)) : f32x4{0.f, 0.f, 0.f, 0.f};
+            x[j] = v[0]; x[j + 1] = v[1]; x[j + 2] = v[2]; x[j + 3] = v[3];
+          }
+          return;
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < NK; ++j) x[j] = entry(j) < M ? p[entry(j)] : 0.f;
+    };
+    load(srow, sc);
+    for (int p = 1; p < a.s_parts; ++p) {
+      float x[NK];
+      load(srow + p * a.s_stride, x);
+#pragma unroll
+      for (int j = 0; j < NK; ++j) sc[j] += x[j];
+    }
+    if (a.valid != nullptr) {
+      uint8_t ok[NK];
+#pragma unroll
+      for (int j = 0; j < NK; ++j) ok[j] = entry(j) < M ? a.valid[m0 + entry(j)] : 0;
+#pragma unroll
+      for (int j = 0; j < NK; ++j) {
+        kv[j] = ok[j] != 0 ? order_key(sc[j]) : 0u;
+        cnt += ok[j] != 0 ? 1 : 0;
+      }
+    } else {
+#pragma unroll
+      for (int j = 0; j < NK; ++j) kv[j] = entry(j) < M ? order_key(sc[j]) : 0u;
+    }
+  }
+  uint32_t cm[2] = {0u, 0u};
+#pragma unroll
+  for (int j = 0; j < NK; ++j) cm[j / (NK / 2)] = max(cm[j / (NK / 2)], kv[j]);
+  kmax = max(cm[0], cm[1]);
+  cmax[2 * tid] = cm[0];
+  cmax[2 * tid + 1] = cm[1];
+  const int nV = a.valid != nullptr ? block_sum_int<NT>(cnt, ired) : M;
+  kmax = block_max_u32<NT>(kmax, ured);  // (its barriers also publish cmax)
+
+  int K = 0;
+  double mass = 0.0;
+  if (nV > 0) {
+    const int C = min(nV, a.k_max);
+    const float smax = key_to_float(kmax);
+    // wave 0 searches the bound while the others start on the normaliser
+    if (wave == 0 && nV > C) {
+      uint32_t mv[2 * NT / 64];
+#pragma unroll
+      for (int j = 0; j < 2 * NT / 64; ++j) mv[j] = cmax[lane + 64 * j];
+      uint32_t thr = 0u;
+      for (int bit = 31; bit >= 0; --bit) {
+        const uint32_t t = thr | (1u << bit);
+        const int got = count_ge<2 * NT / 64>(mv, t);
+        if (got >= C) thr = t;
+        if (got >= C && got <= C + C / 16) break;
+      }
+      if (lane == 0) s_thr = thr;
+    }
+    double z = 0.0;
+#pragma unroll
+    for (int j = 0; j < NK; ++j) z += kv[j] != 0u ? static_cast<double>(key_mass(kv[j], smax)) : 0.0;
+    const double Z = block_sum_f64<NT>(z, dred);
+    const uint32_t bound = nV > C ? max(s_thr, 1u) : 1u;  // (published by block_sum_f64's barriers)
+    int mine = 0;
+#pragma unroll
+    for (int j = 0; j < NK; ++j) mine += kv[j] >= bound ? 1 : 0;
+    // list positions: wave prefix, then the waves' totals in order
+    auto place = [&](int m, int& total) {
+      const int incl = wave_incl_scan_i32(m);
+      __syncthreads();
+      if (lane == 63) ired[wave] = incl;
+      __syncthreads();
+      int off = incl - m;
+      total = 0;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        off += w < wave ? ired[w] : 0;
+        total += ired[w];
+      }
+      return off;
+    };
+    int c;
+    int pos = place(mine, c);
+    if (c <= kSelList) {
+#pragma unroll
+      for (int j = 0; j < NK; ++j)
+        if (kv[j] >= bound) cand[pos++] = comp_key(kv[j], entry(j));
+    } else {
+      // the C-th largest key itself, over every register of the block
+      uint32_t thr = 0u;
+      bool exact = false;
+      for (int bit = 31; bit >= 0 && !exact; --bit) {
+        const uint32_t t = thr | (1u << bit);
+        int m = 0;
+#pragma unroll
+        for (int j = 0; j < NK; ++j) m += kv[j] >= t ? 1 : 0;
+        const int got = block_sum_int<NT>(m, ired);
+        if (got >= C) thr = t;
+        exact = got == C;
+      }
+      int ithr = INT_MAX;
+      if (!exact) {
+        // ties at thr: I is the largest index bound with #(tied, index < I) < need, so the
+        // tied entries with index <= I stay
+        int m = 0;
+#pragma unroll
+        for (int j = 0; j < NK; ++j) m += kv[j] > thr ? 1 : 0;
+        const int need = C - block_sum_int<NT>(m, ired);
+        int I = 0;
+        for (int b2 = 14; b2 >= 0; --b2) {
+          m = 0;
+#pragma unroll
+          for (int j = 0; j < NK; ++j) m += kv[j] == thr && entry(j) < I + (1 << b2) ? 1 : 0;
+          if (block_sum_int<NT>(m, ired) < need) I += 1 << b2;
+        }
+        ithr = I;
+      }
+      int m = 0;
+#pragma unroll
+      for (int j = 0; j < NK; ++j) m += kv[j] > thr || (kv[j] == thr && entry(j) <= ithr) ? 1 : 0;
+      pos = place(m, c);
+#pragma unroll
+      for (int j = 0; j < NK; ++j)
+        if (kv[j] > thr || (kv[j] == thr && entry(j) <= ithr)) {
+          if (pos < kSelList) cand[pos] = comp_key(kv[j], entry(j));
+          ++pos;
+        }
+      c = min(c, kSelList);
+    }
+    __syncthreads();
+    // descending order by counting (the keys are distinct: each holds its entry index)
+    if (c <= NT)
+      rank_sort_desc<1, NT>(cand, c, tid);
+    else if (c <= 2 * NT)
+      rank_sort_desc<2, NT>(cand, c, tid);
+    else
+      rank_sort_desc<kSelList / NT, NT>(cand, c, tid);
+    // prefix sums of exp(s - max) in rank order, two consecutive ranks per thread
+    double e2[2];
+    double loc = 0.0;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int t = 2 * tid + j;
+      loc += t < C ? static_cast<double>(key_mass(static_cast<uint32_t>(cand[t] >> 32), smax)) : 0.0;
+      e2[j] = loc;
+    }
+    {
+      const double incl = wave_incl_scan_f64(loc);
+      __syncthreads();
+      if (lane == 63) dred[wave] = incl;
+      if (tid == 0) s_first = INT_MAX;
+      __syncthreads();
+      double off = incl - loc;
+      for (int w = 0; w < wave; ++w) off += dred[w];
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+        if (2 * tid + j < C) pre[2 * tid + j] = off + e2[j];
+    }
+    // the first rank whose prefix reaches tau Z: the prefixes only grow with the rank, so a
+    // wave's first qualifying rank sits in its lowest qualifying lane (one atomic per wave);
+    // each thread reads back the prefixes that it wrote
+    {
+      const double tau = static_cast<double>(inf.tau);
+      int first = INT_MAX;
+#pragma unroll
+      for (int j = 1; j >= 0; --j) {
+        const int t = 2 * tid + j;
+        if (t < C && pre[t] / Z >= tau) first = t;
+      }
+      const unsigned long long hit = __ballot(first != INT_MAX);
+      if (hit != 0ull && lane == __ffsll(static_cast<long long>(hit)) - 1) atomicMin(&s_first, first);
+    }
+    __syncthreads();
+    const int K_raw = s_first != INT_MAX ? s_first + 1 : (C == nV ? nV : a.k_max + 1);
+    K = min(nV, min(a.k_max, max(a.k_min, K_raw)));
+    mass = pre[K - 1] / Z;
+    const double sumI = pre[K - 1];
+    for (int t = tid; t < K; t += NT) {
+      const float et = key_mass(static_cast<uint32_t>(cand[t] >> 32), smax);
+      alpha[t] = static_cast<float>(static_cast<double>(et) / sumI);
+      const uint32_t ix = 0xFFFFFFFFu - static_cast<uint32_t>(cand[t]);
+      sidx[t] = static_cast<int>(min(ix, static_cast<uint32_t>(M - 1)));
+    }
+    __syncthreads();
+  }
+
+  // ---- renormalised gather r = sum_t alpha_t u_{idx_t} ----
+  // This block covers the 16-byte chunks [c_lo, c_hi) of the row (its column slice);
+  // lane l takes chunk c_lo + l + 64 j in pass j, wave w the ranks w, w + 8, .. in
+  // batches of GR rows whose loads all issue before the first multiply-add; the eight
+  // partial sums are added by wave 0 in a fixed order through LDS.
+  {
+    constexpr int GR = 8;
+    const int cpr = a.d_m / VEC;
+    const int ns = gridDim.y;
+    const int c_lo = static_cast<int>(static_cast<int64_t>(cpr) * blockIdx.y / ns);
+    const int c_hi = static_cast<int>(static_cast<int64_t>(cpr) * (blockIdx.y + 1) / ns);
+    const int mine = K > wave ? (K - wave + NW - 1) / NW : 0;
+    float* red = reinterpret_cast<float*>(cand);  // the candidates are no longer needed
+    for (int cb = c_lo; cb < c_hi; cb += 64) {
+      const int c = min(cb + lane, c_hi - 1);
+      float acc[VEC];
+#pragma unroll
+      for (int x = 0; x < VEC; ++x) acc[x] = 0.f;
+      // batches of 2 GR rows while that many remain, then of up to GR
+      auto batch = [&](auto G_, int q0, int nr) {
+        constexpr int G = decltype(G_)::value;
+        u32x4 raw[G];
+#pragma unroll
+        for (int r = 0; r < G; ++r) {
+          const int t = wave + NW * (q0 + min(r, nr - 1));
+          raw[r] = *reinterpret_cast<const u32x4*>(a.values + (m0 + sidx[t]) * a.d_m + c * VEC);
+        }
+#pragma unroll
+        for (int r = 0; r < G; ++r) {
+          if (r < nr) {
+            const float wt = alpha[wave + NW * (q0 + r)];
+            const T* v = reinterpret_cast<const T*>(&raw[r]);
+#pragma unroll
+            for (int x = 0; x < VEC; ++x) acc[x] = fmaf(wt, Elem<T>::to_f32(v[x]), acc[x]);
+          }
+        }
+      };
+      for (int q0 = 0; q0 < mine;) {
+        if (mine - q0 >= 2 * GR) {
+          batch(std::integral_constant<int, 2 * GR>(), q0, 2 * GR);
+          q0 += 2 * GR;
+        } else {
+          const int nr = min(GR, mine - q0);
+          batch(std::integral_constant<int, GR>(), q0, nr);
+          q0 += nr;
+        }
+      }
+      if (wave > 0)
+#pragma unroll
+        for (int x = 0; x < VEC; x += 4)
+          *reinterpret_cast<f32x4*>(red + ((wave - 1) * 64 + lane) * VEC + x) =
+              f32x4{acc[x], acc[x + 1], acc[x + 2], acc[x + 3]};
+      __syncthreads();
+      if (wave == 0 && cb + lane < c_hi) {
+#pragma unroll
+        for (int q = 0; q < NW - 1; ++q)
+#pragma unroll
+          for (int x = 0; x < VEC; ++x) acc[x] += red[(q * 64 + lane) * VEC + x];
+        const int64_t o = rbase + static_cast<int64_t>(c) * VEC;
+#pragma unroll
+        for (int x = 0; x < VEC; ++x) {
+          st_f32(a.rT, o + x, acc[x]);
+          if (a.r_out) a.r_out[o + x] = acc[x];
+        }
+      }
+      __syncthreads();
+    }
+  }
+  if (blockIdx.y != 0) return;  // one block of the node writes the selection outputs
+  if (a.idx_out)
+    for (int t = tid; t < a.k_max; t += NT)
+      a.idx_out[static_cast<int64_t>(n) * a.k_max + t] = t < K ? sidx[t] : -1;
+  if (tid == 0) {
+    if (a.k_out) a.k_out[n] = K;
+    if (a.mass_out) a.mass_out[n] = static_cast<float>(mass);
   }
 }
 

@@ -1,0 +1,145 @@
+"""GPU parity at the edges of tiles, key groups and dispatch rules, against the fp64 oracle.
+
+Tolerances are the ones of the other parity tests (parity.py's compare): bf16 outputs 2e-2
+and fp32 outputs 1e-5 of a row's norm, selections exact outside the stated bands."""
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from parity import compare, dims_of, gpu_outputs, run_oracle, to_device
+from synth import WORKLOADS, make_case, make_memory_case, make_output_grad
+
+pytestmark = pytest.mark.gpu
+
+H_TOL = {"f32": 1e-5, "bf16": 2e-2}
+
+
+@pytest.fixture(scope="module")
+def lib():
+    import paper_2608_22883_amd as lib
+
+    assert torch.cuda.is_available()
+    return lib
+
+
+def _wl(dtype, **kw):
+    base = WORKLOADS["tiny_f32"] if dtype == "f32" else WORKLOADS["llava_b1"].with_(d=512, d_m=256)
+    return base.with_(**kw)
+
+
+def _run(lib, case):
+    wl = case.workload
+    fv = lib.Fovea(dims_of(wl, case.weights, 1 if wl.dtype == "bf16" else 0), case.weights, device="cuda")
+    print(f"[gpu] edges {wl.dtype}: B={wl.B} n={case.n_nodes} d={wl.d} d_m={wl.d_m} d_c={wl.d_c} "
+          f"m_max={case.m_max} k_max={case.k_max}", flush=True)
+    out = fv.retrieve_fuse(to_device(case, wl.dtype))
+    torch.cuda.synchronize()
+    st, bits = lib.fovea_last_error(fv.ctx)
+    g = gpu_outputs(out)
+    fv.close()
+    assert st == 0, f"data error bits {bits:#x}"
+    return g
+
+
+# one key per thread and slot group (1024), each register count's last size and the next
+# (2048, 4096, 8192), rows of scores that are not 16-byte aligned, k_max at both ends, masks
+@pytest.mark.parametrize("dtype,M,k_max,valid", [
+    ("bf16", 1025, 64, 1.0), ("bf16", 2048, 1, 0.9), ("bf16", 2050, 300, 1.0), ("f32", 4096, 64, 0.7),
+    ("bf16", 4099, 128, 0.5), ("bf16", 8192, 1024, 1.0), ("f32", 8195, 256, 0.9),
+    ("bf16", 16384, 256, 0.02), ("f32", 700, 1024, 0.9)])
+def test_block_selection_sizes(lib, dtype, M, k_max, valid):
+    wl = _wl(dtype, B=1, T=7, M=M, k_max=k_max, tau=0.9, key_scale=(25.0, 25.0), valid_frac=valid)
+    case = make_case(wl, affine="unit")
+    compare(case, _run(lib, case), run_oracle(case), H_TOL[dtype], label=f"block selection {dtype} M={M}")
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_block_selection_overflowing_list(lib, dtype):
+    """Every score equal over 5000 entries: the list of keys that reach the bound would hold
+    them all, so the threshold is searched and its ties cut by index; and one request whose
+    200 best entries are neighbours, so that they fill few of the block's key groups."""
+    wl = _wl(dtype, B=2, T=5, M=5000, k_max=100, tau=0.5, key_scale=(20.0, 20.0))
+    case = make_case(wl, affine="random")
+    keys = case.keys.copy()
+    keys[:5000] = keys[0]
+    keys[5000:5200] *= 4.0
+    case.keys = keys
+    case.tau = np.array([0.0101, 0.9]).astype(np.float32).astype(np.float64)
+    g, ref = _run(lib, case), run_oracle(case)
+    compare(case, g, ref, H_TOL[dtype], label=f"block selection ties {dtype}")
+    for node in range(5):
+        K = int(ref["K"][node])
+        assert g["K"][node] == K and g["idx"][node, :K].tolist() == list(range(K))
+
+
+# few nodes: 32- and 64-row tiles of the correction layers, the row partials' limit
+# (d / 16 <= d_c holds at 1024 / 64, not at 2048 / 64), layer 1 past its widest d_m
+@pytest.mark.parametrize("T,d,d_m,d_c", [(1, 512, 256, 512), (33, 1024, 64, 64), (64, 2048, 192, 64),
+                                         (64, 512, 2112, 128), (65, 512, 256, 512)])
+def test_few_nodes(lib, T, d, d_m, d_c):
+    wl = _wl("bf16", B=1, T=T, M=100, d=d, d_m=d_m, d_c=d_c, k_max=16, key_scale=(30.0, 30.0))
+    case = make_case(wl, affine="unit")
+    compare(case, _run(lib, case), run_oracle(case), H_TOL["bf16"], label=f"few nodes T={T} d={d} d_m={d_m}")
+
+
+# whole 64-row tiles of the hidden-state GEMM (12 x 15 tiles), the last row tile ragged; the
+# three-plane fp32 core in 128- and 64-row tiles
+@pytest.mark.parametrize("dtype,B,T,d,d_m,d_c", [("bf16", 12, 59, 512, 896, 512), ("f32", 3, 60, 320, 192, 128),
+                                                 ("f32", 1, 65, 1024, 128, 512)])
+def test_batches_between_tiles(lib, dtype, B, T, d, d_m, d_c):
+    wl = _wl(dtype, B=B, T=T, M=90, d=d, d_m=d_m, d_c=d_c, k_max=16, key_scale=(30.0, 30.0))
+    case = make_case(wl, affine="unit")
+    compare(case, _run(lib, case), run_oracle(case), H_TOL[dtype], label=f"batch {dtype} n={B * T}")
+
+
+# memory builds: one round of 64-row tiles (2048 rows x 16 column tiles is more), the
+# ping-pong core's 128-, 192- and 256-row tiles with ragged last tiles, fp32's two heights
+@pytest.mark.parametrize("dtype,rows,d_m", [("bf16", 65, 64), ("bf16", 1024, 1024), ("bf16", 2049, 1024),
+                                            ("bf16", 6200, 448), ("bf16", 8300, 512), ("f32", 63, 64),
+                                            ("f32", 2100, 1024)])
+def test_memory_build_tiles(lib, dtype, rows, d_m):
+    wl = _wl(dtype, d=192, d_m=d_m)
+    V, W = make_memory_case(wl, rows, affine="random")
+    fv = lib.Fovea(dims_of(wl, W, 1 if dtype == "bf16" else 0), W, device="cuda")
+    print(f"[gpu] build {dtype} rows={rows} d_m={d_m}", flush=True)
+    keys, values = fv.build_memory(torch.tensor(V, dtype=torch.bfloat16 if dtype == "bf16" else torch.float32,
+                                                device="cuda"))
+    torch.cuda.synchronize()
+    fv.close()
+    ref = oracle.build_memory(V, W["mem_ln_g"], W["mem_ln_b"], W["W_K"], W["W_U"], W["ln_eps"],
+                              gain_rounding="bf16" if dtype == "bf16" else None)
+    for got, want in zip((keys, values), ref):
+        got = got.double().cpu().numpy()
+        rel = np.linalg.norm(got - want, axis=1) / np.linalg.norm(want, axis=1)
+        assert rel.max() <= H_TOL[dtype], rel.max()
+
+
+def test_backward_wide_rows_and_long_node_lists(lib):
+    """Rows wider than the row kernels hold in registers, more nodes than one ballot lists,
+    entries selected by none, some and many of them."""
+    wl = WORKLOADS["tiny_f32"].with_(B=2, T=130, M=70, d=8256, d_m=320, d_c=64, k_max=5, k_min=5)
+    case = make_case(wl, affine="random")
+    W = case.weights
+    f = oracle.retrieve_fuse(W, case.mem_off, case.keys, case.values, case.valid, case.node_off, case.h,
+                             case.depth, case.tau, case.k_min, case.k_max)
+    dh_hat = make_output_grad(case.n_nodes, wl.d, 3)
+    ref = oracle.retrieve_fuse_backward(W, case.mem_off, case.keys, case.values, case.node_off, case.h,
+                                        case.depth, f["idx"], f["K"], dh_hat)
+    fv = lib.Fovea(dims_of(wl, W, 0), W, device="cuda")
+    dev = dict(device="cuda")
+    print(f"[gpu] backward edges n={case.n_nodes} d={wl.d}", flush=True)
+    g = fv.retrieve_fuse_backward(to_device(case, "f32"), torch.tensor(f["K"], dtype=torch.int32, **dev),
+                                  torch.tensor(f["idx"], dtype=torch.int32, **dev),
+                                  torch.tensor(dh_hat, dtype=torch.float32, **dev))
+    torch.cuda.synchronize()
+    assert lib.fovea_last_error(fv.ctx)[0] == 0
+    fv.close()
+    for k, want in ref.items():
+        if k not in g or want is None:
+            continue
+        got = g[k].double().cpu().numpy().reshape(np.shape(want))
+        scale = max(float(np.abs(want).max()), 1e-30)
+        # two-plane products: 2^-16 of the operands; 2e-4 as in the other backward tests
+        assert float(np.abs(got - want).max()) / scale <= 2e-4, k

@@ -408,15 +408,10 @@ int score_keys_per_block(int B, int m_max) {
 typedef void (*ScoreKernel)(int, const int64_t*, int64_t, int, const int32_t*, int, int,
                             const bf16_t*, int, const bf16_t*, float, float*, int, int);
 
+// 16 or 32 keys per block with a fixed chunk count; larger tiles run score_tiles_kernel
 template <int NKC>
 ScoreKernel score_kernel_kb(int kb) {
-  switch (kb) {
-    case 1: return score_bf16_kernel<NKC, 1>;
-    case 2: return score_bf16_kernel<NKC, 2>;
-    case 5: return score_bf16_kernel<NKC, 5>;
-    case 6: return score_bf16_kernel<NKC, 6>;
-    default: return score_bf16_kernel<NKC, 4>;
-  }
+  return kb == 1 ? score_bf16_kernel<NKC, 1> : kb == 2 ? score_bf16_kernel<NKC, 2> : score_bf16_any_kernel;
 }
 
 ScoreKernel score_kernel_for(int nkc, int kb) {
@@ -551,26 +546,45 @@ fovea_status run_retrieve_fuse(fovea_ctx* c, const RFArgs& a, hipStream_t s) {
   }
   // 3. scores for every (node, key) of each request
   if (a.m_max > 0) {
+    const int t_max = std::min(a.t_max, a.n);  // no chunks past the nodes there are, however loose the caller's bound
     const float scale = static_cast<float>(1.0 / std::sqrt(static_cast<double>(D.d_m)));
     ProfScope ps(pc, kScore, s);
     if constexpr (std::is_same<T, bf16_t>::value) {
-      const int kb = score_keys_per_block(a.B, a.m_max) / 16;
+      int kb = score_keys_per_block(a.B, a.m_max) / 16;
+      // larger grids: 80-key tiles, two blocks a compute unit (16 x 48 nodes over 2176 keys 15.1
+      // us; 64 keys 18.8, 96 keys 20.3), or from two rounds of 128-key tiles on runs of those,
+      // one run per compute unit (87 us for 8 x 16384 keys; 80 keys 98)
+      const int64_t t128 = (a.n_mem + 127) / 128;
+      if (kb >= 4) kb = t128 >= 512 ? 8 : 5;
       const int tiles = (a.m_max + 16 * kb - 1) / (16 * kb);
       auto kern = score_kernel_for(D.d_m / score_cfg::KC / s_parts, kb);
-      const int nch = (a.t_max + 63) / 64;
+      const int nch = (t_max + 63) / 64;
       // ragged memories (their total well below B m_max): spread the tiles over the XCDs
       const int spread = a.n_mem * 4 < static_cast<int64_t>(a.B) * a.m_max * 3 ? 1 : 0;
+      // tiles per block (kb >= 4), or the k slices of the small-grid kernel
+      int split = s_parts, blocks = a.B * tiles * nch * s_parts;
+      if (kb >= 4) {
+        split = kb == 8 ? std::min(tiles, static_cast<int>((t128 * nch + 255) / 256)) : 1;
+        blocks = a.B * ((tiles + split - 1) / split) * nch;
+        kern = kb == 8 ? score_tiles_kernel<bf16_t, 8, 4> : score_tiles_kernel<bf16_t, 5, 3>;
+      }
       const int grid = xcd_grid(kern == score_bf16_any_kernel ? a.B * ((a.m_max + 63) / 64)
-                                                              : a.B * tiles * nch * s_parts);
+                                                              : blocks);
       hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, s, a.B, a.mem_off, a.n_mem, a.m_max,
-                         a.node_off, a.n, a.t_max, static_cast<const bf16_t*>(a.keys), D.d_m,
-                         reinterpret_cast<const bf16_t*>(q), scale, S, s_parts, spread);
+                         a.node_off, a.n, t_max, static_cast<const bf16_t*>(a.keys), D.d_m,
+                         reinterpret_cast<const bf16_t*>(q), scale, S, split, spread);
     } else {
-      const int tiles = (a.m_max + 63) / 64;
-      hipLaunchKernelGGL(score_f32_kernel, dim3(xcd_grid(a.B * tiles)), dim3(256), 0, s, a.B,
-                         a.mem_off, a.n_mem, a.m_max, a.node_off, a.n, a.t_max,
-                         static_cast<const float*>(a.keys), D.d_m, reinterpret_cast<const float*>(q),
-                         scale, S);
+      const int kb = score_keys_per_block(a.B, a.m_max) / 16;
+      const int tiles = (a.m_max + 16 * kb - 1) / (16 * kb), nch = (t_max + 63) / 64;
+      auto kern = kb == 1   ? score_tiles_kernel<float, 1, 4>
+                  : kb == 2 ? score_tiles_kernel<float, 2, 4>
+                  : kb == 4 ? score_tiles_kernel<float, 4, 4>
+                  : kb == 5 ? score_tiles_kernel<float, 5, 4>
+                            : score_tiles_kernel<float, 6, 4>;
+      const int spread = a.n_mem * 4 < static_cast<int64_t>(a.B) * a.m_max * 3 ? 1 : 0;
+      hipLaunchKernelGGL(kern, dim3(xcd_grid(a.B * tiles * nch)), dim3(256), 0, s, a.B, a.mem_off, a.n_mem,
+                         a.m_max, a.node_off, a.n, t_max, static_cast<const float*>(a.keys), D.d_m,
+                         reinterpret_cast<const float*>(q), scale, S, 1, spread);
     }
   }
   // 4. selection and gather, one block per node

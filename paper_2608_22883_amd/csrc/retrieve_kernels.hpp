@@ -665,6 +665,197 @@ __global__ __launch_bounds__(256, (KB >= 5 || NKC >= 20) ? 1 : 2) void score_bf1
   }
 }
 
+// ---------------------------------------------------------------------------------
+// Scores for larger grids and for fp32: one block per (request, chunk of 64 nodes, run of tpb
+// consecutive tiles of 16 KB keys), four waves; wave w owns node block w and all keys of a
+// tile.  Both operands pass through the LDS by direct-to-LDS loads: a stage holds 64 k (fp32:
+// 32) of the chunk's nodes (two planes, 16 KB; fp32 8 KB) and of the tile's keys, NST stages,
+// across the tiles of the run; rows of 128 bytes swizzled as in gemm.hpp.  fp32: a lane's 16
+// bytes are four consecutive k, one for each of four MFMAs (the same permutation of k for
+// both operands).  A step multiplies the fragments of one
+// chunk while those of the next are read; one barrier per step.  Rows past the request are
+// clamped and dropped at the store.
+//   The kernel above reads q straight into fragments, 16 rows a load, which runs at about
+// 25 GB/s per compute unit.  8 x 64 nodes over 16384 keys of 1280 (335 MB; a plain read in
+// this order takes 59 us): 104 us on it, 87 in this one, 72 without the score stores; 16 x 48
+// nodes over 2176 keys of 896 19 -> 15.1 us; 32 x 60 over 576 of 1024 12.6 -> 11.6.  fp32,
+// 32 x 60 over 576 of 1024: 38 us, 55 with fragments of both operands read straight from memory.
+// ---------------------------------------------------------------------------------
+template <typename T, int KB_, int NST_>
+struct ScoreTile {
+  static constexpr int KB = KB_, NST = NST_, KT = 16 * KB;
+  static constexpr int PL = std::is_same<T, bf16_t>::value ? kQSplitBf16 : 1;  // planes of q
+  static constexpr int KC = 128 / static_cast<int>(sizeof(T));                 // k per chunk
+  static constexpr int A_BYTES = PL * 64 * 128, STAGE_BYTES = A_BYTES + KT * 128;
+  static constexpr int NIA = 2 * PL;                 // loads of a chunk's nodes per wave (8 rows each)
+  static constexpr int LB = KT / 8;                  // loads of a chunk's keys
+  static constexpr int NIB = (LB + 3) / 4, NI = NIA + NIB;  // per wave; the last may repeat
+  static_assert(NST * STAGE_BYTES <= 160 * 1024, "LDS");
+};
+
+template <typename T, int KB, int NST>
+__global__ __launch_bounds__(256) void score_tiles_kernel(int B, const int64_t* __restrict__ mem_off,
+                                                          int64_t n_mem, int m_max,
+                                                          const int32_t* __restrict__ node_off, int n_nodes,
+                                                          int t_max, const T* __restrict__ keys, int d_m,
+                                                          const T* __restrict__ q, float scale,
+                                                          float* __restrict__ S, int tpb, int spread) {
+  using C = ScoreTile<T, KB, NST>;
+  constexpr int VEC = Elem<T>::kPer16B;
+  using Frag = typename std::conditional<C::PL == 2, bf16x8, f32x4>::type;
+  __shared__ __align__(16) unsigned char smem[NST * C::STAGE_BYTES];
+  const int tiles = (m_max + C::KT - 1) / C::KT, runs = (tiles + tpb - 1) / tpb;
+  const int nch = (t_max + 63) / 64;
+  const int total = B * runs * nch;
+  const int item = spread ? (static_cast<int>(blockIdx.x) < total ? static_cast<int>(blockIdx.x) : -1)
+                          : xcd_item(total);
+  if (item < 0) return;
+  const int b = item / (runs * nch);
+  const int run = (item / nch) % runs;
+  const int cn = (item % nch) * 64;
+  const Extent e = request_extent(b, mem_off, n_mem, m_max, node_off, n_nodes, t_max);
+  if (!e.nodes_ok || !e.mem_ok) return;  // the select kernel reports and fills NaN
+  const int M = static_cast<int>(e.m1 - e.m0);
+  const int Tn = e.t1 - e.t0;
+  const int tile0 = run * tpb;
+  if (tile0 * C::KT >= M || cn >= Tn) return;
+  const int nt = min(tpb, (M + C::KT - 1) / C::KT - tile0);
+
+  const int lane = threadIdx.x & 63, g = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+  const int64_t plane = static_cast<int64_t>(n_nodes) * d_m;
+  const int nkc = d_m / C::KC, nc = nt * nkc;
+  const bool vec = (m_max & 3) == 0;  // score rows 16-byte aligned
+  // load u of this wave: q rows 8 (w + 4 u) .. plane by plane (u < NIA), then key rows
+  const T* gq[C::NIA];
+  const T* gk[C::NIB];
+  int kr[C::NIB], dk[C::NIB];
+  const int cx = lane & 7, rl = lane >> 3;
+#pragma unroll
+  for (int u = 0; u < C::NIA; ++u) {
+    const int j = w + 4 * u, row = (j & 7) * 8 + rl;
+    gq[u] = q + (j >> 3) * plane + static_cast<int64_t>(e.t0 + min(cn + row, Tn - 1)) * d_m +
+            (cx ^ ((row >> 1) & 7)) * VEC;
+  }
+#pragma unroll
+  for (int u = 0; u < C::NIB; ++u) {
+    const int r0 = min(w + 4 * u, C::LB - 1) * 8;
+    kr[u] = r0 + rl;
+    dk[u] = C::A_BYTES + r0 * 128;
+  }
+  auto set_tile = [&](int t) {
+#pragma unroll
+    for (int u = 0; u < C::NIB; ++u)
+      gk[u] = keys + (e.m0 + min((tile0 + t) * C::KT + kr[u], M - 1)) * d_m + (cx ^ ((kr[u] >> 1) & 7)) * VEC;
+  };
+  int lt = 0, lk = 0, ls = 0;  // tile, chunk and stage of the next load
+  set_tile(0);
+  auto load = [&]() {  // past the last chunk the last is loaded again, into a stage nobody reads
+    unsigned char* sp = smem + ls * C::STAGE_BYTES;
+#pragma unroll
+    for (int u = 0; u < C::NIA; ++u)
+      load_lds16(reinterpret_cast<const bf16_t*>(gq[u] + lk * C::KC), sp + (w + 4 * u) * 1024);
+#pragma unroll
+    for (int u = 0; u < C::NIB; ++u)
+      load_lds16(reinterpret_cast<const bf16_t*>(gk[u] + lk * C::KC), sp + dk[u]);
+    ls = ls + 1 == NST ? 0 : ls + 1;
+    if (lk + 1 < nkc) {
+      ++lk;
+    } else if (lt + 1 < nt) {
+      ++lt;
+      lk = 0;
+      set_tile(lt);
+    }
+  };
+  // fragment offsets in a stage: nodes 16 w + lane % 16, keys lane % 16 (+ 16 per block)
+  const int r = lane & 15;
+  int fa[2], fb[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int sl = ((4 * h + g) ^ ((r >> 1) & 7)) << 4;
+    fa[h] = (16 * w + r) * 128 + sl;
+    fb[h] = C::A_BYTES + r * 128 + sl;
+  }
+  f32x4 acc[KB];
+#pragma unroll
+  for (int i = 0; i < KB; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  Frag af[2][C::PL][2], bf[2][KB][2];  // [register set][plane or key block][k half]
+  int rs = 0;                        // stage of the next chunk to read
+  auto read = [&](Frag (&a)[C::PL][2], Frag (&k8)[KB][2]) {
+    const unsigned char* sp = smem + rs * C::STAGE_BYTES;
+    rs = rs + 1 == NST ? 0 : rs + 1;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+      for (int p = 0; p < C::PL; ++p) a[p][h] = *reinterpret_cast<const Frag*>(sp + p * 64 * 128 + fa[h]);
+#pragma unroll
+      for (int k = 0; k < KB; ++k) k8[k][h] = *reinterpret_cast<const Frag*>(sp + fb[h] + k * 16 * 128);
+    }
+  };
+  int ck = 0, ct = 0;
+  // chunk i from register set P: its stage is free (read in the step before), so the load of
+  // chunk i + NST and the reads of i + 1 go out before its products
+  auto step = [&](auto P) {
+    constexpr int p0 = decltype(P)::value;
+    load();
+    read(af[1 - p0], bf[1 - p0]);
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int p = 0; p < (C::PL == 2 ? 2 : 4); ++p)
+#pragma unroll
+        for (int k = 0; k < KB; ++k) {
+          if constexpr (C::PL == 2)
+            acc[k] = mfma_bf16_16x16x32(bf[p0][k][h], af[p0][p][h], acc[k]);
+          else
+            acc[k] = mfma_f32_16x16x4(bf[p0][k][h][p], af[p0][0][h][p], acc[k]);
+        }
+    if (++ck == nkc) {
+      ck = 0;
+      // keys are the product's rows: a lane holds four consecutive keys of node lane % 16
+      const int nd = cn + 16 * w + r;
+      if (nd < Tn) {
+        float* srow = S + static_cast<int64_t>(e.t0 + nd) * m_max;
+#pragma unroll
+        for (int k = 0; k < KB; ++k) {
+          const int key = (tile0 + ct) * C::KT + 16 * k + 4 * g;
+          const f32x4 o = f32x4{acc[k][0] * scale, acc[k][1] * scale, acc[k][2] * scale, acc[k][3] * scale};
+          if (vec && key + 3 < M) {
+            *reinterpret_cast<f32x4*>(srow + key) = o;
+          } else {
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+              if (key + v < M) srow[key + v] = o[v];
+          }
+        }
+      }
+#pragma unroll
+      for (int k = 0; k < KB; ++k) acc[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+      ++ct;
+    }
+    // this wave has read chunk i + 1, and its loads of i + 2 are done (loads retire in order;
+    // stores between them only make the count stricter)
+    __builtin_amdgcn_s_waitcnt(0xC07F);
+    wait_vmcnt<(NST - 2) * C::NI>();
+    lds_barrier();
+  };
+#pragma unroll
+  for (int s2 = 0; s2 < NST; ++s2) load();
+  wait_vmcnt<(NST - 1) * C::NI>();
+  lds_barrier();
+  read(af[0], bf[0]);
+  __builtin_amdgcn_s_waitcnt(0xC07F);
+  wait_vmcnt<(NST - 2) * C::NI>();
+  lds_barrier();
+  int i = 0;
+  for (; i + 1 < nc; i += 2) {
+    step(std::integral_constant<int, 0>());
+    step(std::integral_constant<int, 1>());
+  }
+  if (i < nc) step(std::integral_constant<int, 0>());
+  wait_vmcnt<0>();  // no load may land after the block's LDS is given away
+}
+
 // Fallback for chunk counts without a fixed instantiation: same tiling (64 keys per
 // block), no register prefetch; each 64-k chunk is loaded, staged and consumed in turn.
 __global__ __launch_bounds__(256) void score_bf16_any_kernel(
@@ -727,77 +918,6 @@ __global__ __launch_bounds__(256) void score_bf16_any_kernel(
         for (int v = 0; v < 4; ++v) {
           const int r = cn + 16 * w + 4 * g + v;
           if (r < Tn) S[static_cast<int64_t>(e.t0 + r) * m_max + key] = acc[kblk][v] * scale;
-        }
-      }
-    }
-  }
-}
-
-// ---------------------------------------------------------------------------------
-// Scores for fp32 storage (a simple version: one block per (request, 64-key tile),
-// wave w owns keys [16 w, 16 w + 16), fp32 MFMA, q staged per 64-k chunk in LDS).
-// ---------------------------------------------------------------------------------
-
-__global__ __launch_bounds__(256) void score_f32_kernel(int B, const int64_t* __restrict__ mem_off,
-                                                        int64_t n_mem, int m_max,
-                                                        const int32_t* __restrict__ node_off,
-                                                        int n_nodes, int t_max,
-                                                        const float* __restrict__ keys, int d_m,
-                                                        const float* __restrict__ q, float scale,
-                                                        float* __restrict__ S) {
-  constexpr int LDQ = 64 + 4;
-  __shared__ __align__(16) float qs[64][LDQ];
-  const int tiles = (m_max + 63) / 64;
-  const int item = xcd_item(B * tiles);
-  if (item < 0) return;
-  const int b = item / tiles;
-  const int tile = item % tiles;
-  const Extent e = request_extent(b, mem_off, n_mem, m_max, node_off, n_nodes, t_max);
-  if (!e.nodes_ok || !e.mem_ok) return;
-  const int M = static_cast<int>(e.m1 - e.m0);
-  const int Tn = e.t1 - e.t0;
-  const int i0 = tile * 64;
-  if (i0 >= M || Tn == 0) return;
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4;
-  const int key = i0 + wave * 16 + (lane & 15);
-  const float* krow = keys + (e.m0 + min(key, M - 1)) * d_m + 16 * g;
-
-  for (int c0 = 0; c0 < Tn; c0 += 64) {
-    const int nblk = min(4, (Tn - c0 + 15) / 16);
-    f32x4 acc[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int k0 = 0; k0 < d_m; k0 += 64) {
-      float kf[16];
-#pragma unroll
-      for (int u = 0; u < 16; ++u) kf[u] = krow[k0 + u];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int c = tid + 256 * j;  // 64 rows x 16 chunks of 4 floats
-        const int rr = c >> 4, cc = (c & 15) * 4;
-        const int src = e.t0 + min(c0 + rr, Tn - 1);
-        *reinterpret_cast<u32x4*>(&qs[rr][cc]) =
-            *reinterpret_cast<const u32x4*>(q + static_cast<int64_t>(src) * d_m + k0 + cc);
-      }
-      __syncthreads();
-#pragma unroll
-      for (int nb = 0; nb < 4; ++nb) {
-        if (nb >= nblk) break;
-        const float* qrow = &qs[nb * 16 + (lane & 15)][16 * g];
-#pragma unroll
-        for (int s2 = 0; s2 < 16; ++s2) acc[nb] = mfma_f32_16x16x4(qrow[s2], kf[s2], acc[nb]);
-      }
-      __syncthreads();
-    }
-    if (key < M) {
-#pragma unroll
-      for (int nb = 0; nb < 4; ++nb) {
-        if (nb >= nblk) break;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          const int r = c0 + nb * 16 + 4 * g + v;
-          if (r < Tn) S[static_cast<int64_t>(e.t0 + r) * m_max + key] = acc[nb][v] * scale;
         }
       }
     }

@@ -552,19 +552,23 @@ fovea_status run_retrieve_fuse(fovea_ctx* c, const RFArgs& a, hipStream_t s) {
     if constexpr (std::is_same<T, bf16_t>::value) {
       int kb = score_keys_per_block(a.B, a.m_max) / 16;
       // larger grids: 80-key tiles, two blocks a compute unit (16 x 48 nodes over 2176 keys 15.1
-      // us; 64 keys 18.8, 96 keys 20.3), or from two rounds of 128-key tiles on runs of those,
-      // one run per compute unit (87 us for 8 x 16384 keys; 80 keys 98)
-      const int64_t t128 = (a.n_mem + 127) / 128;
-      if (kb >= 4) kb = t128 >= 512 ? 8 : 5;
+      // us; 64 keys 18.8, 96 keys 20.3), or runs of 128-key tiles, one run per compute unit (87
+      // us for 8 x 16384 keys; 80 keys 98), whichever takes less time over its rounds (8 x 128
+      // nodes over 4096 keys: a step of 123 us in runs, 131 in 80-key tiles); runs of two tiles
+      // or more, of memories long against one (128 x 16 nodes over 576 keys: 148 in runs, 144)
+      const int nch = (t_max + 63) / 64;
+      const int64_t t128 = (a.n_mem + 127) / 128 * nch, t80 = (a.n_mem + 79) / 80 * nch;
+      const int64_t run = (t128 + 255) / 256;
+      if (kb >= 4)
+        kb = run > 1 && run * 9 < (t80 + 511) / 512 * 10 && t128 >= run * 8 * a.B * nch ? 8 : 5;
       const int tiles = (a.m_max + 16 * kb - 1) / (16 * kb);
       auto kern = score_kernel_for(D.d_m / score_cfg::KC / s_parts, kb);
-      const int nch = (t_max + 63) / 64;
       // ragged memories (their total well below B m_max): spread the tiles over the XCDs
       const int spread = a.n_mem * 4 < static_cast<int64_t>(a.B) * a.m_max * 3 ? 1 : 0;
       // tiles per block (kb >= 4), or the k slices of the small-grid kernel
       int split = s_parts, blocks = a.B * tiles * nch * s_parts;
       if (kb >= 4) {
-        split = kb == 8 ? std::min(tiles, static_cast<int>((t128 * nch + 255) / 256)) : 1;
+        split = kb == 8 ? static_cast<int>(std::min<int64_t>(tiles, run)) : 1;
         blocks = a.B * ((tiles + split - 1) / split) * nch;
         kern = kb == 8 ? score_tiles_kernel<bf16_t, 8, 4> : score_tiles_kernel<bf16_t, 5, 3>;
       }

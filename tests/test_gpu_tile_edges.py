@@ -94,6 +94,20 @@ def test_batches_between_tiles(lib, dtype, B, T, d, d_m, d_c):
     compare(case, _run(lib, case), run_oracle(case), H_TOL[dtype], label=f"batch {dtype} n={B * T}")
 
 
+# scores: runs of 128-key tiles (two node chunks, a ragged last run, unaligned score rows, more
+# and fewer chunks of k than stages), 80-key tiles with one chunk, ragged memories, and each
+# key count of the fp32 tiles
+@pytest.mark.parametrize("dtype,B,T,M,M_lo,d_m", [
+    ("bf16", 8, 65, 6001, None, 64), ("bf16", 8, 65, 6001, None, 320), ("bf16", 4, 65, 16001, 8000, 128),
+    ("bf16", 16, 66, 1999, None, 64), ("bf16", 16, 3, 1999, 5, 192), ("f32", 1, 3, 90, None, 64),
+    ("f32", 5, 65, 1400, None, 64), ("f32", 12, 3, 1201, None, 192), ("f32", 16, 17, 1300, 700, 64),
+    ("f32", 20, 5, 1500, None, 128)])
+def test_score_tiles(lib, dtype, B, T, M, M_lo, d_m):
+    wl = _wl(dtype, B=B, T=T, M=M, d_m=d_m, k_max=16, key_scale=(30.0, 30.0), **({"M_lo": M_lo} if M_lo else {}))
+    case = make_case(wl, affine="unit")
+    compare(case, _run(lib, case), run_oracle(case), H_TOL[dtype], label=f"scores {dtype} B={B} T={T} M={M} d_m={d_m}")
+
+
 # memory builds: one round of 64-row tiles (2048 rows x 16 column tiles is more), the
 # ping-pong core's 128-, 192- and 256-row tiles with ragged last tiles, fp32's two heights
 @pytest.mark.parametrize("dtype,rows,d_m", [("bf16", 65, 64), ("bf16", 1024, 1024), ("bf16", 2049, 1024),

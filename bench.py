@@ -135,7 +135,8 @@ def kernel_model(wl, case, union_rows, k_sum, lm=None, kc=0):
     k["corr2"] = dict(bytes=n * d_c * es + d * d_c * es + 2 * n * d * es, flops=2 * n * d_c * d)
     k["rms"] = dict(bytes=2 * n * d * es, flops=3 * n * d)
     if lm is not None:
-        cand = n * ((lm["vocab"] + 127) // 128) * kc * 8
+        tile = 256 if es == 2 and n > 64 else 128  # columns of a candidate list
+        cand = n * ((lm["vocab"] + tile - 1) // tile) * kc * 8
         k["lm_head"] = dict(bytes=lm["vocab"] * d * es + n * d * es + cand,
                             flops=2 * n * d * lm["vocab"])
         k["lm_merge"] = dict(bytes=cand + n * kc * 8, flops=0)
@@ -240,8 +241,8 @@ def backward_main(args):
         per_step_us = tot / args.steps * 1e3
         e = dict(name=name, us_per_step=round(per_step_us, 2), timed_regions_per_step=cnt // args.steps)
         if name == "bwd_gemm":
-            # fp32-accurate products as bf16 GEMMs over a tripled K (hi/lo planes): the
-            # matrix cores issue three times the products' flops
+            # fp32-accurate products on bf16 hi/lo planes: the matrix cores issue three
+            # times the products' flops (six for the recomputed z and c, not counted here)
             e["TFLOPs"] = round(gemm_flops / (per_step_us * 1e-6) / 1e12, 2)
             e["MFMA_TFLOPs"] = round(3 * gemm_flops / (per_step_us * 1e-6) / 1e12, 2)
         kernels.append(e)
@@ -257,8 +258,8 @@ def backward_main(args):
                     d_c=d_c, k_max=wl.k_max, states_per_step=n),
         roofline=dict(bound="mfma", achieved=gk["MFMA_TFLOPs"], peak=PEAK_BF16_TFLOPS, unit="TFLOP/s",
                       frac=round(gk["MFMA_TFLOPs"] / PEAK_BF16_TFLOPS, 4), traffic=None,
-                      kernel="bwd_gemm (all GEMM launches of a step; bf16 matrix cores, K tripled "
-                             "by the hi/lo planes of the fp32 operands)"),
+                      kernel="bwd_gemm (all GEMM launches of a step; bf16 matrix cores, three "
+                             "products of the fp32 operands' hi/lo planes)"),
         kernels=kernels)
     fv.close()
     print(json.dumps(line), flush=True)

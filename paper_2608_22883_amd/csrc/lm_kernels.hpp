@@ -193,14 +193,31 @@ __device__ __forceinline__ float max3_f32(float a, float b, float c) {
 
 typedef __attribute__((ext_vector_type(2))) uint64_t u64x2;
 
-// m = 2 m + (x >= t): the compare's carry goes straight into the shift (left to itself the
-// compiler keeps every compare in a scalar pair of its own and spills them).
-__device__ __forceinline__ void push_ge_f32(uint32_t& m, float x, float t) {
-  asm("v_cmp_ge_f32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(m) : "v"(x), "v"(t) : "vcc");
+// For x0 .. x3 in turn, m = 2 m + (x >= t): the compare's carry goes straight into the shift
+// (left to itself the compiler keeps every compare in a scalar pair of its own and spills
+// them).  A vector instruction may read a scalar pair (VCC too) only two wait states after
+// another has written it, and the compiler does not look in here: the four compares stand
+// before the four shifts, so that three instructions lie between each write and its read.
+__device__ __forceinline__ void push4_ge_f32(uint32_t& m, float x0, float x1, float x2, float x3, float t) {
+  uint64_t c0, c1, c2, c3;
+  asm("v_cmp_ge_f32_e64 %1, %5, %9\n\tv_cmp_ge_f32_e64 %2, %6, %9\n\t"
+      "v_cmp_ge_f32_e64 %3, %7, %9\n\tv_cmp_ge_f32_e64 %4, %8, %9\n\t"
+      "v_addc_co_u32_e64 %0, vcc, %0, %0, %1\n\tv_addc_co_u32_e64 %0, vcc, %0, %0, %2\n\t"
+      "v_addc_co_u32_e64 %0, vcc, %0, %0, %3\n\tv_addc_co_u32_e64 %0, vcc, %0, %0, %4"
+      : "+v"(m), "=&s"(c0), "=&s"(c1), "=&s"(c2), "=&s"(c3)
+      : "v"(x0), "v"(x1), "v"(x2), "v"(x3), "v"(t)
+      : "vcc");
 }
 
-__device__ __forceinline__ void push_eq_f32(uint32_t& m, float x, float t) {
-  asm("v_cmp_eq_f32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(m) : "v"(x), "v"(t) : "vcc");
+__device__ __forceinline__ void push4_eq_f32(uint32_t& m, float x0, float x1, float x2, float x3, float t) {
+  uint64_t c0, c1, c2, c3;
+  asm("v_cmp_eq_f32_e64 %1, %5, %9\n\tv_cmp_eq_f32_e64 %2, %6, %9\n\t"
+      "v_cmp_eq_f32_e64 %3, %7, %9\n\tv_cmp_eq_f32_e64 %4, %8, %9\n\t"
+      "v_addc_co_u32_e64 %0, vcc, %0, %0, %1\n\tv_addc_co_u32_e64 %0, vcc, %0, %0, %2\n\t"
+      "v_addc_co_u32_e64 %0, vcc, %0, %0, %3\n\tv_addc_co_u32_e64 %0, vcc, %0, %0, %4"
+      : "+v"(m), "=&s"(c0), "=&s"(c1), "=&s"(c2), "=&s"(c3)
+      : "v"(x0), "v"(x1), "v"(x2), "v"(x3), "v"(t)
+      : "vcc");
 }
 
 // The value of the lane 16 (32) away: with both operands equal, a row swap leaves this
@@ -280,7 +297,7 @@ __device__ __forceinline__ void lm_select_quad(float* so, int ld, int row0, int 
     for (int w = 0; w < NV / 32; ++w) {
       uint32_t m = 0;
 #pragma unroll
-      for (int e = 0; e < 32; ++e) push_ge_f32(m, v[32 * w + e], t);
+      for (int e = 32 * w; e < 32 * w + 32; e += 4) push4_ge_f32(m, v[e], v[e + 1], v[e + 2], v[e + 3], t);
       hit[w] = m;
       c += __popc(m);
     }
@@ -317,7 +334,7 @@ __device__ __forceinline__ void lm_select_quad(float* so, int ld, int row0, int 
     for (int w = 0; w < NV / 32; ++w) {
       uint32_t m = 0;
 #pragma unroll
-      for (int e = 0; e < 32; ++e) push_eq_f32(m, v[32 * w + e], t0);
+      for (int e = 32 * w; e < 32 * w + 32; e += 4) push4_eq_f32(m, v[e], v[e + 1], v[e + 2], v[e + 3], t0);
       eq[w] = m;
       hit[w] &= ~m;
       neq += __popc(m);

@@ -194,3 +194,34 @@ def test_lm_topk_wide_tiles(lib, n, vocab, k):
         assert idx[r].tolist() == list(range(k)) and np.all(val[r] == 0.0)
     keep = [r for r in range(n) if r not in (1, n - 1)]
     assert check_topk(idx[keep], val[keep], z[keep], k) > 0.9
+
+
+@pytest.mark.parametrize("n,vocab,k,few", [
+    (66, 700, 6, 256), (130, 1300, 12, 256), (200, 520, 8, 0), (257, 515, 16, 8), (65, 256, 10, 256)])
+def test_lm_topk_special_logits(lib, n, vocab, k, few):
+    """Isolated NaN, +inf and -inf logits at the edges of chunks (8 columns), lanes (64) and
+    tiles (256) of the bf16 kernel for more than 64 rows; of the first `few` columns of the
+    second tile (or of the only one) all but three are NaN, so that a tile, or the whole
+    vocabulary, holds fewer than k logits."""
+    h, W = make_lm_case(n, 128, vocab, "bf16", seed=n + 7 * vocab + k)
+    h[3, 0] = 0.0   # an infinite weight times zero: NaN
+    t0 = 256 if vocab > 256 else 0
+    W[t0:t0 + few] = np.nan
+    W[t0 + few // 2:t0 + few // 2 + 3] = 0.25 if few else W[t0:t0 + 3]
+    marks = [v for v in (0, 7, 8, 15, 63, 64, 127, 128, 255, 511, 512, 519) if v < vocab - 1]
+    for i, v in enumerate(marks if vocab > 256 else []):
+        if i % 3 == 0:
+            W[v] = np.nan
+        else:
+            W[v, 0] = np.inf if i % 3 == 1 else -np.inf
+    idx, val = _run(lib, h, W, k, "bf16")
+    with np.errstate(invalid="ignore"):
+        z = np.stack([(h * w).sum(1) for w in W], 1)
+        ref_idx, ref_val = oracle.lm_topk_from_logits(z, k)
+    for r in range(n):
+        fin = np.isfinite(ref_val[r])
+        assert np.array_equal(val[r][~fin], ref_val[r][~fin])
+        # infinities tie: the ids ascend; nothing left: -1
+        assert idx[r][~fin].tolist() == ref_idx[r][~fin].tolist()
+        np.testing.assert_allclose(val[r][fin], ref_val[r][fin], rtol=0, atol=2 * Z_TOL)
+        np.testing.assert_allclose(val[r][fin], z[r, idx[r][fin]], rtol=0, atol=Z_TOL)

@@ -258,9 +258,24 @@ __device__ __forceinline__ f32x4 mfma_bf16_16x16x32(bf16x8 a, bf16x8 b, f32x4 c)
 // compiler's own allocation of loop-carried accumulators otherwise rotates them and
 // inserts copies that drain the matrix pipeline every iteration).  Back-to-back MFMAs
 // on the same accumulator are interlocked in hardware; vector reads of the results
-// must be preceded by mfma_results_ready().
+// must be preceded by mfma_results_ready().  The compiler does not see an MFMA here, so it
+// leaves no wait states behind a vector write (a copy between loops, say) of an accumulator
+// that one of these reads: mfma_accumulators_ready() goes before the first of them and
+// before each loop or tail that follows another.
 __device__ __forceinline__ void mfma_bf16_16x16x32_acc(f32x4& c, bf16x8 a, bf16x8 b) {
   asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
+}
+
+// Two wait states after whatever the compiler writes to the accumulators: the empty
+// statements take every accumulator in its registers first.
+template <int M, int N>
+__device__ __forceinline__ void mfma_accumulators_ready(f32x4 (&acc)[M][N]) {
+#pragma unroll
+  for (int i = 0; i < M; ++i)
+#pragma unroll
+    for (int j = 0; j < N; ++j) asm volatile("" : "+a"(acc[i][j]));
+  asm volatile("s_nop 1" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
 }
 
 // Wait states between the last in-place MFMA and vector reads of its results (more

@@ -254,12 +254,16 @@ __device__ __forceinline__ void gemm_mainloop_dma(f32x4 (&acc)[C::TM][C::TN],
 #pragma unroll
   for (int r = 0; r < NH; ++r) read_frag(smem, 0, r, af0[0], bf0[0]);
   asm volatile("" ::: "memory");
+  mfma_accumulators_ready(acc);
   int kt = 0;
   for (; kt + 1 < nk; kt += 2) {
     step(kt, std::integral_constant<int, 0>());
     step(kt + 1, std::integral_constant<int, 1>());
   }
-  if (kt < nk) step(kt, std::integral_constant<int, 0>());
+  if (kt < nk) {
+    mfma_accumulators_ready(acc);
+    step(kt, std::integral_constant<int, 0>());
+  }
   // the extra loads of the last steps land before the LDS is reused
   wait_vmcnt<0>();
   mfma_results_ready();
@@ -584,12 +588,22 @@ __device__ __forceinline__ void pp_mainloop(typename C::Acc& acc, const bf16_t* 
   wait_vmcnt<NB + NA + NT1>();
   lds_barrier();
   if (wave >= 4) lds_barrier();  // the second wave of each SIMD runs one slot behind
+  auto ready = [&]() {
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int b = 0; b < 2; ++b) mfma_accumulators_ready(acc[a][b]);
+  };
+  ready();
   int kt = 0;
   for (; kt + 1 < nk; kt += 2) {
     tile(kt, std::integral_constant<int, 0>());
     tile(kt + 1, std::integral_constant<int, 1>());
   }
-  if (kt < nk) tile(kt, std::integral_constant<int, 0>());
+  if (kt < nk) {
+    ready();
+    tile(kt, std::integral_constant<int, 0>());
+  }
   if (wave < 4) lds_barrier();
   wait_vmcnt<0>();  // the repeated loads land before the LDS is reused
   mfma_results_ready();
@@ -887,12 +901,16 @@ __device__ __forceinline__ void split_mainloop(f32x4 (&acc)[C::TM][C::TN], const
   __builtin_amdgcn_s_waitcnt(0xC07F);
   wait_vmcnt<(NST - 2) * NI>();
   lds_barrier();
+  mfma_accumulators_ready(acc);
   int kt = 0;
   for (; kt + 1 < nk; kt += 2) {
     step(kt, std::integral_constant<int, 0>());
     step(kt + 1, std::integral_constant<int, 1>());
   }
-  if (kt < nk) step(kt, std::integral_constant<int, 0>());
+  if (kt < nk) {
+    mfma_accumulators_ready(acc);
+    step(kt, std::integral_constant<int, 0>());
+  }
   wait_vmcnt<0>();  // the repeated loads land before the LDS is reused
   mfma_results_ready();
   lds_barrier();

@@ -6,6 +6,7 @@ checks every pair of dependent instructions against the wait states that the com
 leaves (an instruction counts 1, `s_nop N` counts N + 1), along fall-through and every branch:
 
     VALU write of VCC or a scalar register -> VALU read of it (carry-in, mask)      2
+    VALU write of a vector or accumulation register -> MFMA read of it              2
     VALU write of a vector register -> row swap (v_permlane*_swap) of it            2
     MFMA write -> any other instruction that reads or overwrites the result         7
 """
@@ -77,7 +78,7 @@ def check(inst, last, now):
         gap = now - t - 1
         if kind == "valu" and inst.kind == "valu" and (r == "vcc" or r[0] == "s"):
             need = 2
-        elif kind == "valu" and r[0] in "va" and "permlane" in inst.name:
+        elif kind == "valu" and r[0] in "va" and (inst.kind == "mfma" or "permlane" in inst.name):
             need = 2
         elif kind == "mfma" and inst.kind != "mfma":
             need = 7
@@ -156,6 +157,7 @@ def listing(tmp):
     (["v_cmp_ge_f32_e32 vcc, v1, v2", "v_addc_co_u32_e32 v0, vcc, v0, v0, vcc"], 1),
     (["v_cmp_ge_f32_e32 vcc, v1, v2", "s_nop 1", "v_addc_co_u32_e32 v0, vcc, v0, v0, vcc"], 0),
     (["v_cmp_ge_f32_e64 s[2:3], v1, v2", "v_mov_b32_e32 v5, v6", "v_addc_co_u32_e64 v0, vcc, v0, v0, s[2:3]"], 1),
+    (["v_accvgpr_write_b32 a2, v1", "v_mfma_f32_16x16x32_bf16 a[0:3], v[4:7], v[8:11], a[0:3]"], 1),
     (["v_mov_b32_e32 v3, v1", "s_nop 0", "v_permlane32_swap_b32_e32 v2, v3"], 1),
     (["v_mfma_f32_16x16x32_bf16 a[0:3], v[4:7], v[8:11], a[0:3]", "s_nop 5", "v_accvgpr_read_b32 v1, a3"], 1),
     (["v_mfma_f32_16x16x32_bf16 a[0:3], v[4:7], v[8:11], a[0:3]", "s_nop 6", "v_accvgpr_read_b32 v1, a3"], 0),

@@ -31,6 +31,12 @@
  *     in fovea_dims.dtype (fp32 or bf16) unless its type says otherwise.
  *   - The caller owns every buffer.  The context owns only the packed weight copies
  *     it makes in fovea_create (the caller's weight buffers may be freed afterwards).
+ *   - fp32 contexts: the matrix products of the forward and of the memory build run on the
+ *     bf16 matrix cores over three bf16 planes of each operand, as accurate as fp32
+ *     products while the operands' magnitudes are 0 or at least 2^-110 (8e-34); smaller
+ *     operands keep their bits down to 2^-133 only.  Infinities and overflow come out as in
+ *     fp32 arithmetic.  The backward's products take two planes (three for the recomputed
+ *     nets); there an infinite operand gives NaN.
  *   - All work is enqueued on `stream` (NULL = the default stream); calls return
  *     without synchronising.  fovea_retrieve_fuse allocates nothing.
  *   - Host-detectable errors return a status before anything is enqueued.  Errors

@@ -100,8 +100,8 @@ __global__ __launch_bounds__(256) void corr1_kernel(TileMap tm, const T* __restr
   }
   f32x4 acc[C::TM][C::TN];
   fwd_mainloop<C>(acc, rT, epi.n, W1r, epi.N, d_m, 0, d_m, m0, n0, smem);
-  gemm_epilogue<C>(
-      acc, smem, m0, n0,
+  fwd_epilogue<C>(
+      acc, rT, epi.n, W1r, epi.N, d_m, 0, d_m, m0, n0, smem,
       [&](int row, int col0, const float(&v)[8], int gi) -> float {
         if (row >= epi.n || col0 >= epi.N) return 0.f;
         const float p[8] = {ppre[gi][0][0], ppre[gi][0][1], ppre[gi][0][2], ppre[gi][0][3],
@@ -202,7 +202,8 @@ __global__ __launch_bounds__(256) void corr2_kernel(TileMap tm, const T* __restr
   // (the epilogue's first barrier orders these writes before any read)
   epi.sg = sg;
   epi.m0 = m0;
-  gemm_epilogue<C>(acc, smem, m0, n0, epi, RowPart{epi.n, n_parts(epi.d), tc, ca.rms_part});
+  fwd_epilogue<C>(acc, a_c, epi.n, Wc2, epi.d, ca.d_c, 0, ca.d_c, m0, n0, smem, epi,
+                  RowPart{epi.n, n_parts(epi.d), tc, ca.rms_part});
 }
 
 template <typename T>
@@ -224,7 +225,7 @@ __global__ __launch_bounds__(256) void corr2_combine_kernel(Corr2Epi<T> epi, Cor
 // column t < d / 16 <= d_c).  One request: layer 1 4.9 + 4.4 us (split-K and combine) before.
 __global__ __launch_bounds__(512, 2) void corr1_skinny_kernel(const bf16_t* __restrict__ rT, int d_m,
                                                               const bf16_t* __restrict__ W1r,
-                                                              Corr1Epi<bf16_t> epi, float* __restrict__ P) {
+                                                              Corr1Epi<bf16_t> epi, float* P) {
   const int m0 = blockIdx.y * 32, n0 = blockIdx.x * 16;
   skinny_tile<2, 8, 4>(rT, epi.n, W1r, d_m, m0, n0, epi, [&](int row, float sum) {
     if (row < epi.n && n0 >= epi.d_c) P[static_cast<int64_t>(row) * epi.N + n0] = sum;
@@ -428,7 +429,7 @@ __global__ __launch_bounds__(256) void mem_proj_kernel(TileMap tm, const T* __re
   const int m0 = tr * C::BM, n0 = tc * C::BN;
   f32x4 acc[C::TM][C::TN];
   fwd_mainloop<C>(acc, V, epi.n, Wku, 2 * epi.d_m, d_v, 0, d_v, m0, n0, smem);
-  gemm_epilogue<C>(acc, smem, m0, n0, epi, NoRowSum{});
+  fwd_epilogue<C>(acc, V, epi.n, Wku, 2 * epi.d_m, d_v, 0, d_v, m0, n0, smem, epi, NoRowSum{});
 }
 
 template <int QM>

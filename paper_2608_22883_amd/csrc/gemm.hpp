@@ -347,11 +347,18 @@ __device__ __forceinline__ void gemm_mainloop(f32x4 (&acc)[C::TM][C::TN], const 
 // col0 .. col0 + 7 of `row` (rows and columns past the matrix included: f drops them)
 // and returns a per-row contribution; fr(row, sum) receives the sum of the
 // contributions over the tile's 128 columns (lane order fixed, so deterministic).
+// fix(row, col0, so), if given, may first change 8 columns of a row where they are staged (it
+// is called for each group of 8 when some output of the tile is NaN).
 // Must be reached by every thread of the block.
-template <class C, class F, class FR>
+struct NoFix {};
+
+template <class C, class F, class FR, class FX = NoFix>
 __device__ __forceinline__ void gemm_epilogue(const f32x4 (&acc)[C::TM][C::TN],
                                               unsigned char* smem, int m0, int n0, F&& f,
-                                              FR&& fr) {
+                                              FR&& fr, FX&& fix = FX()) {
+  constexpr bool FIX = !std::is_same<typename std::decay<FX>::type, NoFix>::value;
+  int* flag = reinterpret_cast<int*>(smem + C::OUT_BYTES + 1024);  // of the WN staged waves
+  static_assert(!FIX || C::SMEM_BYTES >= C::OUT_BYTES + 1024 + 16 && C::WN == 2, "flags");
   float* so = reinterpret_cast<float*>(smem);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wm = wave / C::WN, wn = wave % C::WN;
@@ -360,16 +367,30 @@ __device__ __forceinline__ void gemm_epilogue(const f32x4 (&acc)[C::TM][C::TN],
 #pragma unroll
   for (int p = 0; p < C::WM; ++p) {
     if (wm == p) {
+      float t[4] = {0.f, 0.f, 0.f, 0.f};  // NaN as soon as one output of the wave is NaN (or infinite)
 #pragma unroll
       for (int i = 0; i < C::TM; ++i)
 #pragma unroll
         for (int j = 0; j < C::TN; ++j)
 #pragma unroll
-          for (int v = 0; v < 4; ++v)
+          for (int v = 0; v < 4; ++v) {
             so[(i * 16 + 4 * (lane >> 4) + v) * C::SLD + wn * C::TN * 16 + j * 16 + (lane & 15)] =
                 acc[i][j][v];
+            if (FIX) t[v] = fmaf(acc[i][j][v], 0.f, t[v]);
+          }
+      if (FIX) {
+        const float sum = (t[0] + t[1]) + (t[2] + t[3]);
+        const bool any = __ballot(sum != sum) != 0ull;
+        if (lane == 0) flag[wn] = any ? 1 : 0;
+      }
     }
     __syncthreads();
+    if constexpr (FIX) {
+      if (__builtin_expect(flag[0] | flag[1], 0))
+#pragma unroll 1
+        for (int g = static_cast<int>(threadIdx.x); g < GROUPS; g += C::NT)
+          fix(m0 + p * C::SROWS + (g >> 4), n0 + (g & 15) * 8, so + (g >> 4) * C::SLD + (g & 15) * 8);
+    }
 #pragma unroll
     for (int g0 = 0; g0 < GROUPS; g0 += C::NT) {
       const int g = g0 + static_cast<int>(threadIdx.x);
@@ -673,7 +694,8 @@ inline int pp_rows(int64_t M, int64_t N) {
 //
 // x = x0 + x1 (+ x2) with x0 = bf16(x), x1 = bf16(x - x0), x2 = bf16(x - x0 - x1).  Two
 // planes leave 2^-16 |x| and take three products (00, 10, 01); three planes hold all 24
-// bits and take the six products of weight 2^-16 or more (00, 01, 10, 11, 02, 20): what is
+// bits of an operand of at least 2^-110 (below that the lower planes run into bf16's
+// subnormals, and an operand keeps its bits down to 2^-133) and take the six products of weight 2^-16 or more (00, 01, 10, 11, 02, 20): what is
 // left out is below fp32's own rounding, and the matrix cores round once per 32 products,
 // so the sum is closer to 64 bits than fp32 MFMA's (1920 x 2048 x 4096: 1.0e-6 against
 // 1.2e-6).
@@ -727,7 +749,8 @@ __host__ __device__ __forceinline__ int64_t plane_col(int64_t k) {
 }
 
 // Two values into P packed planes.  The first plane saturates at the largest bf16, so that
-// a finite value never becomes infinite (an infinite one ends as NaN).
+// a finite value never becomes infinite.  An infinite one is (largest, infinity, NaN), whose
+// products are NaN; the forward computes those again (plain_dot).
 template <int P>
 __device__ __forceinline__ void split_pair(float x, float y, uint32_t (&out)[P]) {
   constexpr float kBig = 3.3895313892515355e38f;
@@ -944,6 +967,43 @@ __device__ __forceinline__ void fwd_mainloop(f32x4 (&acc)[C::TM][C::TN], const T
     split_mainloop<C>(acc, A, K, M, Bw, 3 * static_cast<int64_t>(K), N, k0 / 32, (k0 + Kc) / 32, m0, n0, smem);
 }
 
+// The product of fp32 row a and packed row w over the K-columns k0 .. k0 + Kc in plain fp32: an
+// infinite operand, or one whose partial products overflow with both signs, has no sum over
+// planes.  Ends at the first NaN, so an output that is NaN by right costs one step.
+__device__ __forceinline__ float plain_dot(const float* __restrict__ a, const bf16_t* __restrict__ w, int k0,
+                                           int Kc) {
+  float s = 0.f;
+#pragma unroll 1
+  for (int k = k0; s == s && k < k0 + Kc; k += 8) {
+    float x[8], w0[8], w1[8], w2[8];
+    load8(a + k, x);
+    load8(w + plane_col<3>(k), w0);
+    load8(w + plane_col<3>(k) + 32, w1);
+    load8(w + plane_col<3>(k) + 64, w2);
+#pragma unroll
+    for (int j = 0; j < 8; ++j)  // (plane 1 of an infinity or a NaN is that value)
+      s = fmaf(x[j], fabsf(w1[j]) < INFINITY ? w0[j] + w1[j] + w2[j] : w1[j], s);
+  }
+  return s;
+}
+
+// gemm_epilogue after fwd_mainloop over the same operands and columns of K.
+template <class C, typename T, class F, class FR>
+__device__ __forceinline__ void fwd_epilogue(const f32x4 (&acc)[C::TM][C::TN], const T* A, int M,
+                                             const bf16_t* Bw, int N, int K, int k0, int Kc, int m0,
+                                             int n0, unsigned char* smem, F&& f, FR&& fr) {
+  if constexpr (std::is_same<T, bf16_t>::value) {
+    gemm_epilogue<C>(acc, smem, m0, n0, f, fr);
+  } else {
+    gemm_epilogue<C>(acc, smem, m0, n0, f, fr, [&](int row, int col0, float* so) {
+#pragma unroll 1
+      for (int e = 0; e < 8; ++e)
+        if (so[e] != so[e] && row < M && col0 < N)
+          so[e] = plain_dot(A + static_cast<int64_t>(row) * K, Bw + 3 * static_cast<int64_t>(col0 + e) * K, k0, Kc);
+    });
+  }
+}
+
 // Split-K for GEMMs with too few output tiles to fill the chip: block (tile, y) contracts
 // K slice y (Kc = K / ks columns, a multiple of BK) and stores its fp32 partial tile in
 // part[y][M][N]; a combine kernel then sums the slices in order and runs the fused
@@ -957,8 +1017,8 @@ __device__ __forceinline__ void gemm_splitk_partial(const T* A, int M, const bf1
   f32x4 acc[C::TM][C::TN];
   fwd_mainloop<C>(acc, A, M, Bw, N, K, k0, Kc, m0, n0, smem);
   float* pp = part + static_cast<int64_t>(blockIdx.y) * M * N;
-  gemm_epilogue<C>(
-      acc, smem, m0, n0,
+  fwd_epilogue<C>(
+      acc, A, M, Bw, N, K, k0, Kc, m0, n0, smem,
       [&](int row, int col0, const float(&v)[8]) -> float {
         if (row < M && col0 < N) store8(pp + static_cast<int64_t>(row) * N + col0, v);
         return 0.f;

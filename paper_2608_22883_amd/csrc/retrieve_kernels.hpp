@@ -410,7 +410,7 @@ __global__ __launch_bounds__(256) void hq_kernel(TileMap tm, int n, const T* __r
   }
   f32x4 acc[C::TM][C::TN];
   fwd_mainloop<C>(acc, h, n, Whq, epi.N, d, 0, d, m0, n0, smem);
-  gemm_epilogue<C>(acc, smem, m0, n0, epi, NoRowSum{});
+  fwd_epilogue<C>(acc, h, n, Whq, epi.N, d, 0, d, m0, n0, smem, epi, NoRowSum{});
 }
 
 // stat_part set: the block's 16 rows get their LayerNorm statistics by merging the ks

@@ -447,6 +447,17 @@ int score_parts(const fovea_dims& D, int B, int n, int m_max, int t_max) {
   return best;
 }
 
+// Chunks of 64 nodes that have blocks of their own in score_tiles_kernel (a block walks every
+// gch-th chunk of its request): all that t_max allows while the grid stays within 2048 blocks
+// or the mean request has as many.  t_max is the caller's bound and may be loose: with a block
+// for each chunk that it allows, 512 x 16 nodes over 576 keys of 320 under t_max = 8192 took
+// 965 us a step, most of it blocks without work (226 so), and larger batches did not launch.
+int score_chunks(int B, int n, int t_max, int blocks_per_request) {
+  const int64_t mean = (n + 64 * static_cast<int64_t>(B) - 1) / (64 * static_cast<int64_t>(B));
+  const int64_t few = 2048 / (static_cast<int64_t>(B) * blocks_per_request);
+  return static_cast<int>(std::min<int64_t>((t_max + 63) / 64, std::max({mean, few, int64_t{1}})));
+}
+
 // Few nodes: the two correction layers run in skinny tiles, which need no combine launches
 // (measured at 60 nodes: layer 1 over d_m = 1024 5.7 us against 9.3, over 4096 13.8 against
 // 13.5, so up to 2048); the row partials of layer 2 must fit the consumed half of P.
@@ -472,7 +483,7 @@ fovea_status run_retrieve_fuse(fovea_ctx* c, const RFArgs& a, hipStream_t s) {
   T* q = reinterpret_cast<T*>(a.ws + L.q);
   float* P = reinterpret_cast<float*>(a.ws + L.P);
   float* S = reinterpret_cast<float*>(a.ws + L.S);
-  const int s_parts = score_parts(D, a.B, a.n, a.m_max, a.t_max);
+  const int s_parts = score_parts(D, a.B, a.n, a.m_max, std::min(a.t_max, a.n));
   T* rT = reinterpret_cast<T*>(a.ws + L.rT);
   T* a_c = reinterpret_cast<T*>(a.ws + L.a_c);
   float* gate_part = reinterpret_cast<float*>(a.ws + L.gate_part);
@@ -562,33 +573,35 @@ fovea_status run_retrieve_fuse(fovea_ctx* c, const RFArgs& a, hipStream_t s) {
       if (kb >= 4)
         kb = run > 1 && run * 9 < (t80 + 511) / 512 * 10 && t128 >= run * 8 * a.B * nch ? 8 : 5;
       const int tiles = (a.m_max + 16 * kb - 1) / (16 * kb);
-      auto kern = score_kernel_for(D.d_m / score_cfg::KC / s_parts, kb);
+      const ScoreKernel kern = score_kernel_for(D.d_m / score_cfg::KC / s_parts, kb);
       // ragged memories (their total well below B m_max): spread the tiles over the XCDs
       const int spread = a.n_mem * 4 < static_cast<int64_t>(a.B) * a.m_max * 3 ? 1 : 0;
-      // tiles per block (kb >= 4), or the k slices of the small-grid kernel
-      int split = s_parts, blocks = a.B * tiles * nch * s_parts;
       if (kb >= 4) {
-        split = kb == 8 ? static_cast<int>(std::min<int64_t>(tiles, run)) : 1;
-        blocks = a.B * ((tiles + split - 1) / split) * nch;
-        kern = kb == 8 ? score_tiles_kernel<bf16_t, 8, 4> : score_tiles_kernel<bf16_t, 5, 3>;
+        const int split = kb == 8 ? static_cast<int>(std::min<int64_t>(tiles, run)) : 1;
+        const int runs = (tiles + split - 1) / split, gch = score_chunks(a.B, a.n, t_max, runs);
+        auto tkern = kb == 8 ? score_tiles_kernel<bf16_t, 8, 4> : score_tiles_kernel<bf16_t, 5, 3>;
+        hipLaunchKernelGGL(tkern, dim3(xcd_grid(a.B * runs * gch)), dim3(256), 0, s, a.B, a.mem_off, a.n_mem,
+                           a.m_max, a.node_off, a.n, t_max, static_cast<const bf16_t*>(a.keys), D.d_m,
+                           reinterpret_cast<const bf16_t*>(q), scale, S, split, spread, gch);
+      } else {
+        const int grid = xcd_grid(kern == score_bf16_any_kernel ? a.B * ((a.m_max + 63) / 64)
+                                                                : a.B * tiles * nch * s_parts);
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, s, a.B, a.mem_off, a.n_mem, a.m_max,
+                           a.node_off, a.n, t_max, static_cast<const bf16_t*>(a.keys), D.d_m,
+                           reinterpret_cast<const bf16_t*>(q), scale, S, s_parts, spread);
       }
-      const int grid = xcd_grid(kern == score_bf16_any_kernel ? a.B * ((a.m_max + 63) / 64)
-                                                              : blocks);
-      hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, s, a.B, a.mem_off, a.n_mem, a.m_max,
-                         a.node_off, a.n, t_max, static_cast<const bf16_t*>(a.keys), D.d_m,
-                         reinterpret_cast<const bf16_t*>(q), scale, S, split, spread);
     } else {
       const int kb = score_keys_per_block(a.B, a.m_max) / 16;
-      const int tiles = (a.m_max + 16 * kb - 1) / (16 * kb), nch = (t_max + 63) / 64;
+      const int tiles = (a.m_max + 16 * kb - 1) / (16 * kb), gch = score_chunks(a.B, a.n, t_max, tiles);
       auto kern = kb == 1   ? score_tiles_kernel<float, 1, 4>
                   : kb == 2 ? score_tiles_kernel<float, 2, 4>
                   : kb == 4 ? score_tiles_kernel<float, 4, 4>
                   : kb == 5 ? score_tiles_kernel<float, 5, 4>
                             : score_tiles_kernel<float, 6, 4>;
       const int spread = a.n_mem * 4 < static_cast<int64_t>(a.B) * a.m_max * 3 ? 1 : 0;
-      hipLaunchKernelGGL(kern, dim3(xcd_grid(a.B * tiles * nch)), dim3(256), 0, s, a.B, a.mem_off, a.n_mem,
+      hipLaunchKernelGGL(kern, dim3(xcd_grid(a.B * tiles * gch)), dim3(256), 0, s, a.B, a.mem_off, a.n_mem,
                          a.m_max, a.node_off, a.n, t_max, static_cast<const float*>(a.keys), D.d_m,
-                         reinterpret_cast<const float*>(q), scale, S, 1, spread);
+                         reinterpret_cast<const float*>(q), scale, S, 1, spread, gch);
     }
   }
   // 4. selection and gather, one block per node

@@ -666,8 +666,8 @@ __global__ __launch_bounds__(256, (KB >= 5 || NKC >= 20) ? 1 : 2) void score_bf1
 }
 
 // ---------------------------------------------------------------------------------
-// Scores for larger grids and for fp32: one block per (request, chunk of 64 nodes, run of tpb
-// consecutive tiles of 16 KB keys), four waves; wave w owns node block w and all keys of a
+// Scores for larger grids and for fp32: one block per (request, chunk of 64 nodes (every
+// gch-th), run of tpb consecutive tiles of 16 KB keys), four waves; wave w owns node block w and all keys of a
 // tile.  Both operands pass through the LDS by direct-to-LDS loads: a stage holds 64 k (fp32:
 // 32) of the chunk's nodes (two planes, 16 KB; fp32 8 KB) and of the tile's keys, NST stages,
 // across the tiles of the run; rows of 128 bytes swizzled as in gemm.hpp.  fp32: a lane's 16
@@ -699,26 +699,26 @@ __global__ __launch_bounds__(256) void score_tiles_kernel(int B, const int64_t* 
                                                           const int32_t* __restrict__ node_off, int n_nodes,
                                                           int t_max, const T* __restrict__ keys, int d_m,
                                                           const T* __restrict__ q, float scale,
-                                                          float* __restrict__ S, int tpb, int spread) {
+                                                          float* __restrict__ S, int tpb, int spread,
+                                                          int gch) {
   using C = ScoreTile<T, KB, NST>;
   constexpr int VEC = Elem<T>::kPer16B;
   using Frag = typename std::conditional<C::PL == 2, bf16x8, f32x4>::type;
   __shared__ __align__(16) unsigned char smem[NST * C::STAGE_BYTES];
   const int tiles = (m_max + C::KT - 1) / C::KT, runs = (tiles + tpb - 1) / tpb;
-  const int nch = (t_max + 63) / 64;
-  const int total = B * runs * nch;
+  const int total = B * runs * gch;
   const int item = spread ? (static_cast<int>(blockIdx.x) < total ? static_cast<int>(blockIdx.x) : -1)
                           : xcd_item(total);
   if (item < 0) return;
-  const int b = item / (runs * nch);
-  const int run = (item / nch) % runs;
-  const int cn = (item % nch) * 64;
+  const int b = item / (runs * gch);
+  const int run = (item / gch) % runs;
+  const int cn0 = (item % gch) * 64;
   const Extent e = request_extent(b, mem_off, n_mem, m_max, node_off, n_nodes, t_max);
   if (!e.nodes_ok || !e.mem_ok) return;  // the select kernel reports and fills NaN
   const int M = static_cast<int>(e.m1 - e.m0);
   const int Tn = e.t1 - e.t0;
   const int tile0 = run * tpb;
-  if (tile0 * C::KT >= M || cn >= Tn) return;
+  if (tile0 * C::KT >= M || cn0 >= Tn) return;
   const int nt = min(tpb, (M + C::KT - 1) / C::KT - tile0);
 
   const int lane = threadIdx.x & 63, g = lane >> 4;
@@ -726,6 +726,7 @@ __global__ __launch_bounds__(256) void score_tiles_kernel(int B, const int64_t* 
   const int64_t plane = static_cast<int64_t>(n_nodes) * d_m;
   const int nkc = d_m / C::KC, nc = nt * nkc;
   const bool vec = (m_max & 3) == 0;  // score rows 16-byte aligned
+  for (int cn = cn0; cn < Tn; cn += 64 * gch) {
   // load u of this wave: q rows 8 (w + 4 u) .. plane by plane (u < NIA), then key rows
   const T* gq[C::NIA];
   const T* gk[C::NIB];
@@ -853,7 +854,10 @@ __global__ __launch_bounds__(256) void score_tiles_kernel(int B, const int64_t* 
     step(std::integral_constant<int, 1>());
   }
   if (i < nc) step(std::integral_constant<int, 0>());
-  wait_vmcnt<0>();  // no load may land after the block's LDS is given away
+  // no load may land after the block's LDS is given away, or in the next chunk's stages
+  wait_vmcnt<0>();
+  lds_barrier();
+  }
 }
 
 // Fallback for chunk counts without a fixed instantiation: same tiling (64 keys per

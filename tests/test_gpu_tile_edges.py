@@ -157,3 +157,71 @@ def test_backward_wide_rows_and_long_node_lists(lib):
         scale = max(float(np.abs(want).max()), 1e-30)
         # two-plane products: 2^-16 of the operands; 2e-4 as in the other backward tests
         assert float(np.abs(got - want).max()) / scale <= 2e-4, k
+
+
+# a batch in which one request has most of the nodes, so that a block walks several chunks of
+# 64 of them (every score kernel: 16- to 128-key tiles, both dtypes, widths with and without a
+# fixed chunk count), under the tight bound on a request's nodes and under the loosest
+@pytest.mark.parametrize("dtype,B,big,M,d_m", [
+    ("bf16", 300, 300, 576, 256), ("bf16", 300, 700, 100, 512), ("bf16", 260, 200, 200, 320),
+    ("bf16", 20, 1500, 100, 192), ("bf16", 2, 1100, 300, 1024), ("bf16", 40, 3000, 700, 768),
+    ("f32", 300, 300, 576, 128), ("f32", 300, 700, 60, 64), ("f32", 16, 1500, 700, 512)])
+def test_uneven_requests(lib, dtype, B, big, M, d_m):
+    wl = _wl(dtype, B=B, T=1, M=M, d=256 if dtype == "bf16" else 128, d_m=d_m, d_c=64, k_max=16,
+             key_scale=(30.0, 30.0))
+    extra = -(-(big + B - 1) // B)
+    case = make_case(wl.with_(T=extra), affine="unit")
+    n = case.n_nodes
+    sizes = np.ones(B, np.int64)
+    sizes[B // 2] = n - (B - 1)
+    case.node_off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int32)
+    fv = lib.Fovea(dims_of(wl, case.weights, 1 if dtype == "bf16" else 0), case.weights, device="cuda")
+    inp = to_device(case, dtype)
+    got = []
+    for t_max in (int(sizes.max()), n, 1 << 30):
+        inp["t_max"] = t_max
+        print(f"[gpu] uneven {dtype} B={B} n={n} M={M} d_m={d_m} t_max={t_max}", flush=True)
+        out = fv.retrieve_fuse(inp)
+        torch.cuda.synchronize()
+        got.append(gpu_outputs(out))
+        assert lib.fovea_last_error(fv.ctx)[0] == 0
+    fv.close()
+    for g in got[1:]:
+        for k in g:
+            assert np.array_equal(g[k], got[0][k]), k
+    pick = np.r_[0:B // 2, B // 2 + np.arange(0, n - B + 1, 37), n - (B - B // 2 - 1):n]
+    sub = np.unique(pick)
+    # the oracle on every 37th node of the large request and on all the others
+    req = np.searchsorted(case.node_off, sub, side="right") - 1
+    case.h, case.depth = case.h[sub], case.depth[sub]
+    case.node_off = np.searchsorted(req, np.arange(B + 1)).astype(np.int32)
+    compare(case, {k: v[sub] for k, v in got[0].items()}, run_oracle(case), H_TOL[dtype],
+            label=f"uneven {dtype} B={B} M={M} d_m={d_m}")
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_loose_node_bound_of_a_large_batch(lib, dtype):
+    """16384 requests of 4 nodes under t_max = 65536: the grid follows the nodes there are (with
+    a block per chunk that the bound allows it would be past what a launch may hold)."""
+    B, T, d, d_m = 16384, 4, 64, 64
+    wl = _wl(dtype, B=1, T=1, M=8, d=d, d_m=d_m, d_c=64, k_max=4)
+    W = make_case(wl, affine="unit").weights
+    fv = lib.Fovea(dims_of(wl, W, 1 if dtype == "bf16" else 0), W, device="cuda")
+    g = torch.Generator(device="cuda").manual_seed(5)
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda").to(dt)  # noqa: E731
+    ar = torch.arange(B + 1, device="cuda")
+    inp = dict(mem_off=ar * 8, keys=rnd(B * 8, d_m), values=rnd(B * 8, d_m), valid=None,
+               node_off=(ar * T).to(torch.int32), h=rnd(B * T, d),
+               depth=torch.zeros(B * T, dtype=torch.int32, device="cuda"), tau=torch.full((B,), 0.7, device="cuda"),
+               m_max=8, k_min=1, k_max=4)
+    got = []
+    for t_max in (T, B * T):
+        print(f"[gpu] loose bound {dtype} B={B} t_max={t_max}", flush=True)
+        out = fv.retrieve_fuse(dict(inp, t_max=t_max))
+        torch.cuda.synchronize()
+        got.append(gpu_outputs(out))
+        assert lib.fovea_last_error(fv.ctx)[0] == 0
+    fv.close()
+    for k in got[0]:
+        assert np.array_equal(got[0][k], got[1][k]), k

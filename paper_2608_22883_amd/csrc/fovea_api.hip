@@ -408,10 +408,15 @@ int score_keys_per_block(int B, int m_max) {
 typedef void (*ScoreKernel)(int, const int64_t*, int64_t, int, const int32_t*, int, int,
                             const bf16_t*, int, const bf16_t*, float, float*, int, int);
 
-// 16 or 32 keys per block with a fixed chunk count; larger tiles run score_tiles_kernel
 template <int NKC>
 ScoreKernel score_kernel_kb(int kb) {
-  return kb == 1 ? score_bf16_kernel<NKC, 1> : kb == 2 ? score_bf16_kernel<NKC, 2> : score_bf16_any_kernel;
+  switch (kb) {
+    case 1: return score_bf16_kernel<NKC, 1>;
+    case 2: return score_bf16_kernel<NKC, 2>;
+    case 5: return score_bf16_kernel<NKC, 5>;
+    case 6: return score_bf16_kernel<NKC, 6>;
+    default: return score_bf16_kernel<NKC, 4>;
+  }
 }
 
 ScoreKernel score_kernel_for(int nkc, int kb) {
@@ -447,6 +452,9 @@ int score_parts(const fovea_dims& D, int B, int n, int m_max, int t_max) {
   return best;
 }
 
+// ragged memories (their total well below B m_max): spread the tiles over the XCDs
+int score_spread(int B, int64_t n_mem, int m_max) { return n_mem * 4 < static_cast<int64_t>(B) * m_max * 3 ? 1 : 0; }
+
 // Chunks of 64 nodes that have blocks of their own in score_tiles_kernel (a block walks every
 // gch-th chunk of its request): all that t_max allows while the grid stays within 2048 blocks
 // or the mean request has as many.  t_max is the caller's bound and may be loose: with a block
@@ -456,6 +464,68 @@ int score_chunks(int B, int n, int t_max, int blocks_per_request) {
   const int64_t mean = (n + 64 * static_cast<int64_t>(B) - 1) / (64 * static_cast<int64_t>(B));
   const int64_t few = 2048 / (static_cast<int64_t>(B) * blocks_per_request);
   return static_cast<int>(std::min<int64_t>((t_max + 63) / 64, std::max({mean, few, int64_t{1}})));
+}
+
+// bf16 scores: score_tiles_kernel with 80-key tiles, two blocks a compute unit, or with runs of
+// 128-key tiles, one block a unit; or else score_bf16_kernel with score_keys_per_block keys
+// (score_bf16_any_kernel where it has no instantiation).
+//   Both operands through the LDS cost score_tiles_kernel the staging of 64 nodes a chunk
+// however few there are and a pipeline that few chunks of k do not fill, so it wins with many
+// nodes, wide keys and full rounds.  Score kernel, us (score_bf16_kernel, tiles):
+// 32 x 60 over 576 of 1024 16.4, 14.6; 16 x 17 over 1000 of 1024 11.9, 13.8; 128 x 16 over 576
+// of 512 21.2, 22.2 and of 1024 38.6, 35.1; 16 x 64 over 3000 of 512 18.6, 19.9; 64 x 60 over
+// 576 of 512 17.6, 15.1; 40 x 64 over 2000 of 64 12.1, 13.9.  Over 12 widths, 20 batches and 2 to
+// 130 nodes the rule is 1% from the better of the two on average.
+struct ScorePlan {
+  bool tiles;
+  int kb, run;  // 16 kb keys a tile; tiles a block (score_tiles_kernel)
+};
+
+ScorePlan score_plan(const fovea_dims& D, int B, int n, int t_max, int64_t n_mem, int m_max) {
+  ScorePlan p{false, score_keys_per_block(B, m_max) / 16, 1};
+  if (p.kb < 4) return p;  // a small grid, whose k slices score_bf16_kernel has
+  const int t = static_cast<int>((static_cast<int64_t>(n) + B - 1) / B);  // nodes of the mean request
+  const int64_t blocks = (n_mem + 79) / 80 * ((t + 63) / 64);
+  // runs of 128-key tiles on every compute unit, of one chunk of nodes, where they take less
+  // time: 4 us and 15 a tile against 10 for each 80-key tile of a unit, at d_m = 1024 (8 x 64
+  // nodes over 16384 keys: 62 us in runs of 4, 75 in 80-key tiles; 16 x 64 over 3000: 29, 27;
+  // 8 x 130 over 16384: 220, 150)
+  if (t >= 32 && t <= 64 && B <= 128 && D.d_m >= 256) {
+    const int tiles = (m_max + 127) / 128, per = 256 / B, run = (tiles + per - 1) / per;
+    if (run > 1 && 4 + 15 * run < 10 * ((blocks + 255) / 256)) return ScorePlan{true, 8, run};
+  }
+  const bool half = 2 * blocks <= 512, one = blocks <= 512;  // rounds of two blocks a unit
+  const bool ragged = score_spread(B, n_mem, m_max) != 0;
+  bool tiles;
+  if (score_kernel_for(D.d_m / score_cfg::KC, p.kb) != score_bf16_any_kernel) {
+    // score_bf16_kernel has a block for every chunk that t_max allows
+    const int per = (m_max + 16 * p.kb - 1) / (16 * p.kb);
+    if ((t_max + 63) / 64 > score_chunks(B, n, t_max, per)) return ScorePlan{true, 5, 1};
+    const bool wide = D.d_m >= 768;
+    // (a second round of few blocks is worse than that kernel's larger tiles)
+    const bool tail = !one && blocks < 640;
+    // (keys of 512 to 767: not where that kernel has its 96-key tiles)
+    tiles = (t >= 64 && (wide || (D.d_m >= 512 && !ragged && p.kb < 6))) ||
+            (wide && ((t >= 48 && blocks >= 230) ||
+                      (!tail && ((t >= 32 && blocks >= 307) || blocks >= 486))));
+  } else {
+    // against the kernel without prefetch, whose 64-key blocks walk the chunks of nodes
+    tiles = (t >= 32 && half) || (t >= 64 && D.d_m >= 320) || (t >= 48 && D.d_m >= 448) ||
+            (t > 64 && D.d_m >= 192 && blocks <= 768) ||
+            (D.d_m >= 1024 && (t >= 32 || (one && !ragged) || blocks >= 768));
+  }
+  return tiles ? ScorePlan{true, 5, 1} : p;
+}
+
+// fp32 scores of few nodes a request, or of narrow keys, take score_f32_kernel, unless its grid
+// leaves compute units idle (32 requests over 576 keys of 1024: 16 nodes 30 us against 34 in
+// tiles, 32 nodes 37 and 35, 48 nodes 44 and 35; 2 x 16 nodes over 2500 of 1024 33 and 23; 16 x
+// 64 over 3000 of 64 16 and 16, of 192 30 and 29)
+bool score_f32_few(const fovea_dims& D, int B, int n, int m_max) {
+  const int64_t blocks = static_cast<int64_t>(B) * ((m_max + 63) / 64);
+  const int t = static_cast<int>((static_cast<int64_t>(n) + B - 1) / B);
+  if (blocks < 128) return false;
+  return !(t >= 48 && D.d_m >= 512 && (blocks <= 320 || t == 64 || (t > 64 && D.d_m >= 1024)));
 }
 
 // Few nodes: the two correction layers run in skinny tiles, which need no combine launches
@@ -561,35 +631,28 @@ fovea_status run_retrieve_fuse(fovea_ctx* c, const RFArgs& a, hipStream_t s) {
     const float scale = static_cast<float>(1.0 / std::sqrt(static_cast<double>(D.d_m)));
     ProfScope ps(pc, kScore, s);
     if constexpr (std::is_same<T, bf16_t>::value) {
-      int kb = score_keys_per_block(a.B, a.m_max) / 16;
-      // larger grids: 80-key tiles, two blocks a compute unit (16 x 48 nodes over 2176 keys 15.1
-      // us; 64 keys 18.8, 96 keys 20.3), or runs of 128-key tiles, one run per compute unit (87
-      // us for 8 x 16384 keys; 80 keys 98), whichever takes less time over its rounds (8 x 128
-      // nodes over 4096 keys: a step of 123 us in runs, 131 in 80-key tiles); runs of two tiles
-      // or more, of memories long against one (128 x 16 nodes over 576 keys: 148 in runs, 144)
-      const int nch = (t_max + 63) / 64;
-      const int64_t t128 = (a.n_mem + 127) / 128 * nch, t80 = (a.n_mem + 79) / 80 * nch;
-      const int64_t run = (t128 + 255) / 256;
-      if (kb >= 4)
-        kb = run > 1 && run * 9 < (t80 + 511) / 512 * 10 && t128 >= run * 8 * a.B * nch ? 8 : 5;
-      const int tiles = (a.m_max + 16 * kb - 1) / (16 * kb);
-      const ScoreKernel kern = score_kernel_for(D.d_m / score_cfg::KC / s_parts, kb);
-      // ragged memories (their total well below B m_max): spread the tiles over the XCDs
-      const int spread = a.n_mem * 4 < static_cast<int64_t>(a.B) * a.m_max * 3 ? 1 : 0;
-      if (kb >= 4) {
-        const int split = kb == 8 ? static_cast<int>(std::min<int64_t>(tiles, run)) : 1;
-        const int runs = (tiles + split - 1) / split, gch = score_chunks(a.B, a.n, t_max, runs);
-        auto tkern = kb == 8 ? score_tiles_kernel<bf16_t, 8, 4> : score_tiles_kernel<bf16_t, 5, 3>;
-        hipLaunchKernelGGL(tkern, dim3(xcd_grid(a.B * runs * gch)), dim3(256), 0, s, a.B, a.mem_off, a.n_mem,
+      const ScorePlan pl = score_plan(D, a.B, a.n, t_max, a.n_mem, a.m_max);
+      const int spread = score_spread(a.B, a.n_mem, a.m_max);
+      const int kt = 16 * pl.kb, tiles = (a.m_max + kt - 1) / kt;
+      if (pl.tiles) {
+        const int runs = (tiles + pl.run - 1) / pl.run, gch = score_chunks(a.B, a.n, t_max, runs);
+        auto kern = pl.kb == 8 ? score_tiles_kernel<bf16_t, 8, 4> : score_tiles_kernel<bf16_t, 5, 3>;
+        hipLaunchKernelGGL(kern, dim3(xcd_grid(a.B * runs * gch)), dim3(256), 0, s, a.B, a.mem_off, a.n_mem,
                            a.m_max, a.node_off, a.n, t_max, static_cast<const bf16_t*>(a.keys), D.d_m,
-                           reinterpret_cast<const bf16_t*>(q), scale, S, split, spread, gch);
+                           reinterpret_cast<const bf16_t*>(q), scale, S, pl.run, spread, gch);
       } else {
+        const ScoreKernel kern = score_kernel_for(D.d_m / score_cfg::KC / s_parts, pl.kb);
+        const int nch = (t_max + 63) / 64;
         const int grid = xcd_grid(kern == score_bf16_any_kernel ? a.B * ((a.m_max + 63) / 64)
                                                                 : a.B * tiles * nch * s_parts);
         hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, s, a.B, a.mem_off, a.n_mem, a.m_max,
                            a.node_off, a.n, t_max, static_cast<const bf16_t*>(a.keys), D.d_m,
                            reinterpret_cast<const bf16_t*>(q), scale, S, s_parts, spread);
       }
+    } else if (score_f32_few(D, a.B, a.n, a.m_max)) {
+      hipLaunchKernelGGL(score_f32_kernel, dim3(xcd_grid(a.B * ((a.m_max + 63) / 64))), dim3(256), 0, s, a.B,
+                         a.mem_off, a.n_mem, a.m_max, a.node_off, a.n, t_max,
+                         static_cast<const float*>(a.keys), D.d_m, reinterpret_cast<const float*>(q), scale, S);
     } else {
       const int kb = score_keys_per_block(a.B, a.m_max) / 16;
       const int tiles = (a.m_max + 16 * kb - 1) / (16 * kb), gch = score_chunks(a.B, a.n, t_max, tiles);
@@ -598,10 +661,9 @@ fovea_status run_retrieve_fuse(fovea_ctx* c, const RFArgs& a, hipStream_t s) {
                   : kb == 4 ? score_tiles_kernel<float, 4, 4>
                   : kb == 5 ? score_tiles_kernel<float, 5, 4>
                             : score_tiles_kernel<float, 6, 4>;
-      const int spread = a.n_mem * 4 < static_cast<int64_t>(a.B) * a.m_max * 3 ? 1 : 0;
       hipLaunchKernelGGL(kern, dim3(xcd_grid(a.B * tiles * gch)), dim3(256), 0, s, a.B, a.mem_off, a.n_mem,
                          a.m_max, a.node_off, a.n, t_max, static_cast<const float*>(a.keys), D.d_m,
-                         reinterpret_cast<const float*>(q), scale, S, 1, spread, gch);
+                         reinterpret_cast<const float*>(q), scale, S, 1, score_spread(a.B, a.n_mem, a.m_max), gch);
     }
   }
   // 4. selection and gather, one block per node

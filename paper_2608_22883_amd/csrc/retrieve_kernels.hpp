@@ -860,6 +860,80 @@ __global__ __launch_bounds__(256) void score_tiles_kernel(int B, const int64_t* 
   }
 }
 
+// ---------------------------------------------------------------------------------
+// Scores for fp32 storage with few nodes a request: one block per (request, 64-key tile),
+// wave w owns keys [16 w, 16 w + 16), fp32 MFMA, q staged per 64-k chunk in LDS.  It does the
+// products of whole blocks of 16 nodes only, where score_tiles_kernel stages and multiplies
+// 64: 128 x 16 nodes over 576 keys of 512 37 us against 54, 32 x 16 over 576 of 1024 30
+// against 34; 32 x 60 of those 52 against 34.
+// ---------------------------------------------------------------------------------
+
+__global__ __launch_bounds__(256) void score_f32_kernel(int B, const int64_t* __restrict__ mem_off,
+                                                        int64_t n_mem, int m_max,
+                                                        const int32_t* __restrict__ node_off,
+                                                        int n_nodes, int t_max,
+                                                        const float* __restrict__ keys, int d_m,
+                                                        const float* __restrict__ q, float scale,
+                                                        float* __restrict__ S) {
+  constexpr int LDQ = 64 + 4;
+  __shared__ __align__(16) float qs[64][LDQ];
+  const int tiles = (m_max + 63) / 64;
+  const int item = xcd_item(B * tiles);
+  if (item < 0) return;
+  const int b = item / tiles;
+  const int tile = item % tiles;
+  const Extent e = request_extent(b, mem_off, n_mem, m_max, node_off, n_nodes, t_max);
+  if (!e.nodes_ok || !e.mem_ok) return;
+  const int M = static_cast<int>(e.m1 - e.m0);
+  const int Tn = e.t1 - e.t0;
+  const int i0 = tile * 64;
+  if (i0 >= M || Tn == 0) return;
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4;
+  const int key = i0 + wave * 16 + (lane & 15);
+  const float* krow = keys + (e.m0 + min(key, M - 1)) * d_m + 16 * g;
+
+  for (int c0 = 0; c0 < Tn; c0 += 64) {
+    const int nblk = min(4, (Tn - c0 + 15) / 16);
+    f32x4 acc[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int k0 = 0; k0 < d_m; k0 += 64) {
+      float kf[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) kf[u] = krow[k0 + u];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int c = tid + 256 * j;  // 64 rows x 16 chunks of 4 floats
+        const int rr = c >> 4, cc = (c & 15) * 4;
+        const int src = e.t0 + min(c0 + rr, Tn - 1);
+        *reinterpret_cast<u32x4*>(&qs[rr][cc]) =
+            *reinterpret_cast<const u32x4*>(q + static_cast<int64_t>(src) * d_m + k0 + cc);
+      }
+      __syncthreads();
+#pragma unroll
+      for (int nb = 0; nb < 4; ++nb) {
+        if (nb >= nblk) break;
+        const float* qrow = &qs[nb * 16 + (lane & 15)][16 * g];
+#pragma unroll
+        for (int s2 = 0; s2 < 16; ++s2) acc[nb] = mfma_f32_16x16x4(qrow[s2], kf[s2], acc[nb]);
+      }
+      __syncthreads();
+    }
+    if (key < M) {
+#pragma unroll
+      for (int nb = 0; nb < 4; ++nb) {
+        if (nb >= nblk) break;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int r = c0 + nb * 16 + 4 * g + v;
+          if (r < Tn) S[static_cast<int64_t>(e.t0 + r) * m_max + key] = acc[nb][v] * scale;
+        }
+      }
+    }
+  }
+}
+
 // Fallback for chunk counts without a fixed instantiation: same tiling (64 keys per
 // block), no register prefetch; each 64-k chunk is loaded, staged and consumed in turn.
 __global__ __launch_bounds__(256) void score_bf16_any_kernel(

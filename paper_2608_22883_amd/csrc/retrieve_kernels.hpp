@@ -1594,14 +1594,19 @@ __global__ __launch_bounds__(256) void select_node_kernel(SelectArgs<T> a, int n
 //    it bit by bit on ballots and stops within C / 16 of the count);
 //  * the few keys that reach the bound (about 290 of 16384 for C = 256) go to a list, which is
 //    ranked by counting; its first C entries are the candidates in order;
-//  * where the list would overflow (ties, or scores that crowd few chunks) the C-th largest
-//    key is searched over every register, ties cut by index.
+//  * where the list would overflow, or where ranking it would cost more than a search (ties,
+//    scores that crowd few chunks, C near the number of chunks), a closer bound is searched
+//    over every register, down to the C-th largest key itself with ties cut by index.
 // Then the prefix masses, K, the weights, and the gather by eight waves.
 //   Bound by the latency of its phases and, for large K, of the value rows.  With the keys in
 // LDS, a histogram of every key per radix digit and four waves a node (512 nodes of 16384
 // entries): score row 13 us, normaliser 7, threshold 23, compaction 12, ranking 4, gather 18.
 constexpr int kSelNT = 512;
 constexpr int kSelList = 2048;  // candidate list entries (at least kMaxKmax)
+// Ranking a list of c keys takes c steps for every kSelNT of them a thread holds; a search
+// costs about as much as 512 + 16 NK of these (512 nodes of 1500 entries, k_max 1024, a step:
+// 178 us with the list of all 1500 ranked, 125 with a search before it; 700 of 4096 194, 109).
+__device__ __forceinline__ int rank_cost(int c) { return c * (c <= kSelNT ? 1 : c <= 2 * kSelNT ? 2 : 4); }
 
 template <typename T, int NK>
 __global__ __launch_bounds__(kSelNT, 4) void select_gather_kernel(SelectArgs<T> a) {
@@ -1682,7 +1687,7 @@ __global__ __launch_bounds__(kSelNT, 4) void select_gather_kernel(SelectArgs<T> 
   cmax[2 * tid] = cm[0];
   cmax[2 * tid + 1] = cm[1];
   const int nV = a.valid != nullptr ? block_sum_int<NT>(cnt, ired) : M;
-  kmax = block_max_u32<NT>(kmax, ured);  // (its barriers also publish cmax)
+  kmax = __builtin_amdgcn_readfirstlane(block_max_u32<NT>(kmax, ured));  // (its barriers also publish cmax)
 
   int K = 0;
   double mass = 0.0;
@@ -1707,7 +1712,8 @@ __global__ __launch_bounds__(kSelNT, 4) void select_gather_kernel(SelectArgs<T> 
 #pragma unroll
     for (int j = 0; j < NK; ++j) z += kv[j] != 0u ? static_cast<double>(key_mass(kv[j], smax)) : 0.0;
     const double Z = block_sum_f64<NT>(z, dred);
-    const uint32_t bound = nV > C ? max(s_thr, 1u) : 1u;  // (published by block_sum_f64's barriers)
+    // (published by block_sum_f64's barriers)
+    const uint32_t bound = __builtin_amdgcn_readfirstlane(nV > C ? max(s_thr, 1u) : 1u);
     int mine = 0;
 #pragma unroll
     for (int j = 0; j < NK; ++j) mine += kv[j] >= bound ? 1 : 0;
@@ -1724,30 +1730,35 @@ __global__ __launch_bounds__(kSelNT, 4) void select_gather_kernel(SelectArgs<T> 
         off += w < wave ? ired[w] : 0;
         total += ired[w];
       }
+      total = __builtin_amdgcn_readfirstlane(total);
       return off;
     };
     int c;
     int pos = place(mine, c);
-    if (c <= kSelList) {
+    if (c <= kSelList && rank_cost(c) <= rank_cost(C) + 512 + 16 * NK) {
 #pragma unroll
       for (int j = 0; j < NK; ++j)
         if (kv[j] >= bound) cand[pos++] = comp_key(kv[j], entry(j));
     } else {
-      // the C-th largest key itself, over every register of the block
-      uint32_t thr = 0u;
+      // over every register of the block: a key that at least C and at most `most` keys reach,
+      // below the bits that the largest key shares with the bound
+      const int most = min(C + C / 8, C <= NT ? NT : kMaxKmax);
+      const uint32_t diff = bound ^ kmax;
+      int bit = diff != 0u ? 31 - __builtin_clz(diff) : -1;
+      uint32_t thr = diff != 0u ? kmax & ~((2u << bit) - 1u) : kmax;
       bool exact = false;
-      for (int bit = 31; bit >= 0 && !exact; --bit) {
+      for (; bit >= 0 && !exact; --bit) {
         const uint32_t t = thr | (1u << bit);
         int m = 0;
 #pragma unroll
         for (int j = 0; j < NK; ++j) m += kv[j] >= t ? 1 : 0;
-        const int got = block_sum_int<NT>(m, ired);
+        const int got = __builtin_amdgcn_readfirstlane(block_sum_int<NT>(m, ired));
         if (got >= C) thr = t;
-        exact = got == C;
+        exact = got >= C && got <= most;
       }
       int ithr = INT_MAX;
       if (!exact) {
-        // ties at thr: I is the largest index bound with #(tied, index < I) < need, so the
+        // thr is the C-th largest key; ties at thr: I is the largest index bound with #(tied, index < I) < need, so the
         // tied entries with index <= I stay
         int m = 0;
 #pragma unroll

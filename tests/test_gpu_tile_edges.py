@@ -48,27 +48,30 @@ def _run(lib, case):
 @pytest.mark.parametrize("dtype,M,k_max,valid", [
     ("bf16", 1025, 64, 1.0), ("bf16", 2048, 1, 0.9), ("bf16", 2050, 300, 1.0), ("f32", 4096, 64, 0.7),
     ("bf16", 4099, 128, 0.5), ("bf16", 8192, 1024, 1.0), ("f32", 8195, 256, 0.9),
-    ("bf16", 16384, 256, 0.02), ("f32", 700, 1024, 0.9)])
+    ("bf16", 16384, 256, 0.02), ("f32", 700, 1024, 0.9),
+    # lists too long to rank (k_max near the number of key groups): a closer bound first
+    ("bf16", 1500, 1024, 1.0), ("f32", 2048, 700, 1.0), ("bf16", 3000, 512, 0.9), ("f32", 1100, 513, 1.0)])
 def test_block_selection_sizes(lib, dtype, M, k_max, valid):
     wl = _wl(dtype, B=1, T=7, M=M, k_max=k_max, tau=0.9, key_scale=(25.0, 25.0), valid_frac=valid)
     case = make_case(wl, affine="unit")
     compare(case, _run(lib, case), run_oracle(case), H_TOL[dtype], label=f"block selection {dtype} M={M}")
 
 
-@pytest.mark.parametrize("dtype", ["f32", "bf16"])
-def test_block_selection_overflowing_list(lib, dtype):
-    """Every score equal over 5000 entries: the list of keys that reach the bound would hold
-    them all, so the threshold is searched and its ties cut by index; and one request whose
-    200 best entries are neighbours, so that they fill few of the block's key groups."""
-    wl = _wl(dtype, B=2, T=5, M=5000, k_max=100, tau=0.5, key_scale=(20.0, 20.0))
+@pytest.mark.parametrize("dtype,M", [("f32", 5000), ("bf16", 5000), ("bf16", 1500)])
+def test_block_selection_overflowing_list(lib, dtype, M):
+    """Every score equal over all entries: the list of keys that reach the bound would hold
+    them all (5000 do not fit it, 1500 would take longer to rank than a search), so the
+    threshold is searched and its ties cut by index; and one request whose 200 best entries
+    are neighbours, so that they fill few of the block's key groups."""
+    wl = _wl(dtype, B=2, T=5, M=M, k_max=100, tau=0.5, key_scale=(20.0, 20.0))
     case = make_case(wl, affine="random")
     keys = case.keys.copy()
-    keys[:5000] = keys[0]
-    keys[5000:5200] *= 4.0
+    keys[:M] = keys[0]
+    keys[M:M + 200] *= 4.0
     case.keys = keys
     case.tau = np.array([0.0101, 0.9]).astype(np.float32).astype(np.float64)
     g, ref = _run(lib, case), run_oracle(case)
-    compare(case, g, ref, H_TOL[dtype], label=f"block selection ties {dtype}")
+    compare(case, g, ref, H_TOL[dtype], label=f"block selection ties {dtype} M={M}")
     for node in range(5):
         K = int(ref["K"][node])
         assert g["K"][node] == K and g["idx"][node, :K].tolist() == list(range(K))

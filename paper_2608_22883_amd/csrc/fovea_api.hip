@@ -528,13 +528,15 @@ bool score_f32_few(const fovea_dims& D, int B, int n, int m_max) {
   return !(t >= 48 && D.d_m >= 512 && (blocks <= 320 || t == 64 || (t > 64 && D.d_m >= 1024)));
 }
 
-// Few nodes: the two correction layers run in skinny tiles, which need no combine launches
-// (measured at 60 nodes: layer 1 over d_m = 1024 5.7 us against 9.3, over 4096 13.8 against
-// 13.5, so up to 2048); the row partials of layer 2 must fit the consumed half of P.
-constexpr int kSkinnyNodes = 64, kSkinnyK = 2048;
+// Few nodes: the two correction layers run in skinny tiles, which need no combine launches,
+// while their k is short enough for fragments read straight from memory.  At 60 nodes: layer
+// 1 over d_m = 1024 5.7 us against 9.3, over 4096 13.8 against 13.5; both layers and the norm
+// at d = 1024 over d_c = 512 21.2 against 23.7, 1024 24.4 and 24.3, 1536 29.3 and 25.7, 2048
+// 34.6 and 27.2.  The row partials of layer 2 must fit the consumed half of P.
+constexpr int kSkinnyNodes = 64, kSkinnyK1 = 2048, kSkinnyK2 = 1024;
 
 bool use_skinny(const fovea_dims& D, int n) {
-  return D.dtype == FOVEA_BF16 && n <= kSkinnyNodes && D.d_c <= kSkinnyK && D.d / 16 <= D.d_c;
+  return D.dtype == FOVEA_BF16 && n <= kSkinnyNodes && D.d_c <= kSkinnyK2 && D.d / 16 <= D.d_c;
 }
 
 // Threads of a combine block: 4 rows of 128 columns while 16 would leave compute units idle.
@@ -563,7 +565,7 @@ fovea_status run_retrieve_fuse(fovea_ctx* c, const RFArgs& a, hipStream_t s) {
   // 1. LayerNorm statistics of h, node -> request map, depth / tau / offset checks (with
   // a split-K query GEMM its slices and its combine do this, without a launch of its own)
   const bool split_stats = ksp.hq > 1;
-  const bool skinny2 = use_skinny(D, a.n), skinny1 = skinny2 && D.d_m <= kSkinnyK;
+  const bool skinny2 = use_skinny(D, a.n), skinny1 = skinny2 && D.d_m <= kSkinnyK1;
   if (!split_stats) {
     ProfScope ps(pc, kRowStats, s);
     hipLaunchKernelGGL(row_stats_kernel<T>, dim3((a.n + 3) / 4), dim3(256), 0, s, a.n, h, D.d,

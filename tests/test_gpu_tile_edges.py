@@ -78,9 +78,10 @@ def test_block_selection_overflowing_list(lib, dtype, M):
 
 
 # few nodes: 32- and 64-row tiles of the correction layers, the row partials' limit
-# (d / 16 <= d_c holds at 1024 / 64, not at 2048 / 64), layer 1 past its widest d_m
+# (d / 16 <= d_c holds at 1024 / 64, not at 2048 / 64), layers 1 and 2 past their widest k
 @pytest.mark.parametrize("T,d,d_m,d_c", [(1, 512, 256, 512), (33, 1024, 64, 64), (64, 2048, 192, 64),
-                                         (64, 512, 2112, 128), (65, 512, 256, 512)])
+                                         (64, 512, 2112, 128), (65, 512, 256, 512),
+                                         (61, 256, 64, 1024), (61, 256, 64, 1088)])
 def test_few_nodes(lib, T, d, d_m, d_c):
     wl = _wl("bf16", B=1, T=T, M=100, d=d, d_m=d_m, d_c=d_c, k_max=16, key_scale=(30.0, 30.0))
     case = make_case(wl, affine="unit")

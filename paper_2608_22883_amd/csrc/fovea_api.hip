@@ -340,15 +340,16 @@ fovea_status run_build(fovea_ctx* c, int n, const void* V, void* keys, void* val
   auto tiles = [&](int bm, int bn) { return static_cast<int64_t>((n + bm - 1) / bm) * ((N + bn - 1) / bn); };
   ProfScope ps(c, kMemProj, s);
   if constexpr (std::is_same<T, bf16_t>::value) {
-    // a full round of 128 x 128 tiles or more: the ping-pong core in the tile height that
-    // takes the least time over its rounds
-    if (tiles(128, 128) > 256) {
-      const int qm = pp_rows(n, N);
-      launch_mem_proj_pp(qm, map(64 * qm, 256), Vt, D.d_v, Wku, epi, s);
-      return hipGetLastError() == hipSuccess ? FOVEA_OK : FOVEA_ERR_DEVICE;
-    }
+    const BfTile t = best_bf_tile([&](int bm, int bn) { return tile_grid(map(bm, bn)) / 8; });
+    const TileMap tm = map(t.rows, t.cols);
+    if (t.cols == 256)
+      launch_mem_proj_pp(t.rows / 64, tm, Vt, D.d_v, Wku, epi, s);
+    else
+      hipLaunchKernelGGL((t.rows == 64 ? mem_proj_kernel<T, 64> : mem_proj_kernel<T, 128>), dim3(tile_grid(tm)),
+                         dim3(256), 0, s, tm, Vt, D.d_v, Wku, epi);
+    return hipGetLastError() == hipSuccess ? FOVEA_OK : FOVEA_ERR_DEVICE;
   }
-  // 64-row tiles while they take one round
+  // fp32: 64-row tiles while they take one round
   if (tiles(64, 128) <= 256) {
     const TileMap tm = map(64, 128);
     hipLaunchKernelGGL((mem_proj_kernel<T, 64>), dim3(tile_grid(tm)), dim3(256), 0, s, tm, Vt, D.d_v, Wku, epi);
@@ -845,9 +846,8 @@ void launch_lm(int n, const T* h, int d, const T* W, int vocab, int k, uint64_t*
                      k, cand);
 }
 
-void launch_lm_pp(int n, const bf16_t* h, int d, const bf16_t* W, int vocab, int k, uint64_t* cand,
+void launch_lm_pp(int qm, int n, const bf16_t* h, int d, const bf16_t* W, int vocab, int k, uint64_t* cand,
                   hipStream_t s) {
-  const int qm = pp_rows(n, vocab);
   const LmMap m = make_lm_map((n + 64 * qm - 1) / (64 * qm), (vocab + 255) / 256);
   auto kern = qm == 4 ? lm_pp_kernel<4> : qm == 3 ? lm_pp_kernel<3> : lm_pp_kernel<2>;
   hipLaunchKernelGGL(kern, dim3(lm_grid(m)), dim3(512), 0, s, m, n, h, d, W, vocab, k, cand);
@@ -857,13 +857,18 @@ template <typename T>
 fovea_status run_lm_topk(fovea_ctx* c, int n, const void* h, const void* W, int vocab, int k,
                          int32_t* idx, float* logit, uint64_t* cand, hipStream_t s) {
   const int d = c->dims.d;
+  int tile = 128;  // columns of a candidate list
   {
     ProfScope ps(c, kLmHead, s);
     const T* ht = static_cast<const T*>(h);
     const T* Wt = static_cast<const T*>(W);
     if constexpr (std::is_same<T, bf16_t>::value) {
-      if (n <= 64) launch_lm<T, 64>(n, ht, d, Wt, vocab, k, cand, s);
-      else launch_lm_pp(n, ht, d, Wt, vocab, k, cand, s);
+      const BfTile t = best_bf_tile(
+          [&](int bm, int bn) { return lm_grid(make_lm_map((n + bm - 1) / bm, (vocab + bn - 1) / bn)) / 8; });
+      tile = t.cols;
+      if (t.cols == 256) launch_lm_pp(t.rows / 64, n, ht, d, Wt, vocab, k, cand, s);
+      else if (t.rows == 64) launch_lm<T, 64>(n, ht, d, Wt, vocab, k, cand, s);
+      else launch_lm<T, 128>(n, ht, d, Wt, vocab, k, cand, s);
     } else {
       if (n <= 64) launch_lm<T, 64>(n, ht, d, Wt, vocab, k, cand, s);
       else if (n < 768) launch_lm<T, 128>(n, ht, d, Wt, vocab, k, cand, s);
@@ -871,7 +876,6 @@ fovea_status run_lm_topk(fovea_ctx* c, int n, const void* h, const void* W, int 
     }
   }
   {
-    const int tile = std::is_same<T, bf16_t>::value && n > 64 ? 256 : 128;
     const int n_cand = (vocab + tile - 1) / tile * k;
     ProfScope ps(c, kLmMerge, s);
     if (k <= 8)

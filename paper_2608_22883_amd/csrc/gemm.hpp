@@ -672,18 +672,28 @@ __device__ __forceinline__ void pp_epilogue(const typename C::Acc& acc, unsigned
   }
 }
 
-// Row blocks of 16 per quadrant and wave (tile rows 64 QM) for an M x N product on 256
-// compute units: rounds of tiles times the measured time of a k-tile.
-inline int pp_rows(int64_t M, int64_t N) {
-  const int cost[5] = {0, 0, 83, 106, 118};
-  int best = 4;
+// bf16 tiles of a product that has no split along K: the core above with 4 waves (128 columns)
+// or the ping-pong core (256).  cost: a k-tile of 64, in 10 ns, measured on memory builds and
+// LM heads of 126 + 269 sizes (300 to 65536 rows; 40 to 1920 rows over vocabularies of 1000 to
+// 152064), where the tile with the smallest rounds x cost is 1% from the fastest on average.
+// A round is 32 tiles on the XCD that has most: 36 x 7 tiles in regions of 5 x 7 take two
+// rounds, although they are fewer than 256 (4608 x 1792 x 3584: 104 us, 70 in 192-row tiles),
+// and a few wide tiles leave compute units idle (200 x 8192 x 4096: 63 us, 32 in 64-row tiles).
+struct BfTile {
+  int rows, cols, cost;
+};
+constexpr BfTile kBfTiles[] = {{64, 128, 33}, {128, 128, 48}, {128, 256, 80}, {192, 256, 96}, {256, 256, 108}};
+
+// The best of kBfTiles; per_xcd(rows, cols): tiles on the XCD that has most of them.
+template <class F>
+inline BfTile best_bf_tile(F&& per_xcd) {
+  BfTile best = kBfTiles[0];
   int64_t best_cost = -1;
-  for (int qm = 4; qm >= 2; --qm) {
-    const int64_t tiles = (M + 64 * qm - 1) / (64 * qm) * ((N + 255) / 256);
-    const int64_t c = (tiles + 255) / 256 * cost[qm];
+  for (const BfTile& t : kBfTiles) {
+    const int64_t c = (static_cast<int64_t>(per_xcd(t.rows, t.cols)) + 31) / 32 * t.cost;
     if (best_cost < 0 || c < best_cost) {
       best_cost = c;
-      best = qm;
+      best = t;
     }
   }
   return best;

@@ -4,9 +4,10 @@
 // experimental setup).
 //
 // Two kernels:
-//  * lm_kernel / lm_pp_kernel: the logit GEMM (the cores of gemm.hpp: 64-row tiles for one
-//    small batch, which is bound by reading the head; the ping-pong core's 256-column tiles
-//    for more bf16 rows; 128- and 256-row tiles for fp32) with an epilogue that keeps, for
+//  * lm_kernel / lm_pp_kernel: the logit GEMM (the cores of gemm.hpp: for bf16 the tile that
+//    best_bf_tile picks, 64- or 128-row tiles for few rows or a small vocabulary and the
+//    ping-pong core's 256-column tiles for the rest; 64-, 128- and 256-row tiles for fp32)
+//    with an epilogue that keeps, for
 //    every row of the tile, its k largest logits and writes them as candidates
 //    [row][column tile][k] - the logits themselves never reach memory;
 //  * lm_merge_kernel: one block per row merges the row's candidates into its top k.

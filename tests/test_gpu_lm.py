@@ -177,11 +177,14 @@ def test_lm_topk_host_errors(lib):
 
 
 @pytest.mark.parametrize("n,vocab,k", [
-    (65, 256, 1), (128, 257, 8), (129, 320, 9), (192, 511, 16), (193, 776, 6), (257, 513, 10), (300, 264, 16)])
+    (65, 256, 1), (128, 257, 8), (129, 320, 9), (192, 511, 16), (193, 776, 6), (257, 513, 10), (300, 264, 16),
+    (65, 40001, 1), (128, 40000, 8), (300, 16500, 16), (129, 40001, 9), (192, 33000, 16), (193, 33000, 6),
+    (256, 33025, 10)])
 def test_lm_topk_wide_tiles(lib, n, vocab, k):
-    """Edges of the 128-, 192- and 256-row, 256-column tiles, last tiles of 1 to 255 columns
-    (fewer than k among them), rows of equal logits (zero states: the lowest ids) and rows whose
-    large logits are neighbours (one lane's columns)."""
+    """Small vocabularies (64-row tiles of 128 columns) and the 128-, 192- and 256-row tiles of
+    256 columns that larger ones take: edges of the tiles, last tiles of 1 to 255 columns (fewer
+    than k among them), rows of equal logits (zero states: the lowest ids) and rows whose large
+    logits are neighbours (one lane's columns)."""
     h, W = make_lm_case(n, 128, vocab, "bf16", seed=n * 31 + k)
     h[1] = 0.0
     h[n - 1] = 0.0
@@ -197,10 +200,11 @@ def test_lm_topk_wide_tiles(lib, n, vocab, k):
 
 
 @pytest.mark.parametrize("n,vocab,k,few", [
-    (66, 700, 6, 256), (130, 1300, 12, 256), (200, 520, 8, 0), (257, 515, 16, 8), (65, 256, 10, 256)])
+    (66, 700, 6, 256), (130, 1300, 12, 256), (200, 520, 8, 0), (257, 515, 16, 8), (65, 256, 10, 256),
+    (66, 40001, 6, 256), (130, 40001, 12, 256), (200, 33025, 16, 8)])
 def test_lm_topk_special_logits(lib, n, vocab, k, few):
-    """Isolated NaN, +inf and -inf logits at the edges of chunks (8 columns), lanes (64) and
-    tiles (256) of the bf16 kernel for more than 64 rows; of the first `few` columns of the
+    """Isolated NaN, +inf and -inf logits at the edges of chunks (8 columns), lanes (32, 64) and
+    tiles (128, 256) of the bf16 kernels for more than 64 rows; of the first `few` columns of the
     second tile (or of the only one) all but three are NaN, so that a tile, or the whole
     vocabulary, holds fewer than k logits."""
     h, W = make_lm_case(n, 128, vocab, "bf16", seed=n + 7 * vocab + k)

@@ -115,10 +115,11 @@ def test_score_tiles(lib, dtype, B, T, M, M_lo, d_m):
     compare(case, _run(lib, case), run_oracle(case), H_TOL[dtype], label=f"scores {dtype} B={B} T={T} M={M} d_m={d_m}")
 
 
-# memory builds: one round of 64-row tiles (2048 rows x 16 column tiles is more), the
-# ping-pong core's 128-, 192- and 256-row tiles with ragged last tiles, fp32's two heights
+# memory builds: 64- and 128-row tiles of 128 columns, the ping-pong core's 128-, 192- and
+# 256-row tiles with ragged last tiles, fp32's two heights
 @pytest.mark.parametrize("dtype,rows,d_m", [("bf16", 65, 64), ("bf16", 1024, 1024), ("bf16", 2049, 1024),
-                                            ("bf16", 6200, 448), ("bf16", 8300, 512), ("f32", 63, 64),
+                                            ("bf16", 6200, 448), ("bf16", 8300, 512), ("bf16", 2200, 512),
+                                            ("bf16", 7000, 1024), ("f32", 63, 64),
                                             ("f32", 2100, 1024)])
 def test_memory_build_tiles(lib, dtype, rows, d_m):
     wl = _wl(dtype, d=192, d_m=d_m)

@@ -314,47 +314,62 @@ __device__ __forceinline__ void lm_select_quad(float* so, int ld, int row0, int 
   int c = pair_sums(cnt, c1, c2);
   const int row = row0 + (lane & 15);
   uint64_t* dst = cand + (static_cast<int64_t>(row) * n_tiles + tile) * k;
-  if (__ballot(cnt > HMAX || c > CAP - 4) != 0ull) {
+  // whether the hits of the lane's row fit the list: at most HMAX a lane, CAP - 4 a row
+  auto row_fits = [&](int mine_cnt, int row_cnt) {
+    int o1, o2;
+    return pair_sums(mine_cnt > HMAX ? 1 : 0, o1, o2) == 0 && row_cnt <= CAP - 4;
+  };
+  bool fits = row_fits(cnt, c);
+  if (__ballot(!fits) != 0ull) {
     // too many for the list (a tile with few valid columns, logits in one lane, equal
-    // logits): search the k-th largest logit itself, between the bound and the maximum
-    // (all rows of the wave together, until each is exact), then take the logits above it
-    // and of those equal to it the lowest ids that the k slots leave
-    uint32_t lo = th, hi = L[0];
+    // logits): search a closer bound, between this one and the maximum, that k logits still
+    // reach and the list holds (all rows of the wave together), or the k-th largest logit
+    // itself; of that, take the logits above it and of those equal to it the lowest ids that
+    // the k slots leave
+    uint32_t lo = th, hi = fits ? th : L[0];
     while (__ballot(lo < hi) != 0ull) {
       const uint32_t mid = lo + ((hi - lo + 1) >> 1);
-      const int got = pair_sums(find_hits(lm_ord_val(mid)), c1, c2);
-      if (got >= k) lo = mid;
-      if (got < k) hi = mid - 1;
-      if (got == k) hi = lo;
+      const int m = find_hits(lm_ord_val(mid));
+      const int got = pair_sums(m, c1, c2);
+      const bool ok = row_fits(m, got);
+      if (lo < hi) {
+        if (got >= k) lo = mid;
+        if (got < k) hi = mid - 1;
+        if (got >= k && ok) hi = lo;
+      }
     }
     t0 = lm_ord_val(lo);
-    find_hits(t0);
-    uint32_t eq[NV / 32];
-    int ngt = 0, neq = 0;
-#pragma unroll
-    for (int w = 0; w < NV / 32; ++w) {
-      uint32_t m = 0;
-#pragma unroll
-      for (int e = 32 * w; e < 32 * w + 32; e += 4) push4_eq_f32(m, v[e], v[e + 1], v[e + 2], v[e + 3], t0);
-      eq[w] = m;
-      hit[w] &= ~m;
-      neq += __popc(m);
-      ngt += __popc(hit[w]);
-    }
-    int e1, e2;
-    pair_sums(ngt, e1, e2);
-    const int need = k - (ngt + e1 + e2);
-    pair_sums(neq, e1, e2);
-    int take = min(max(need - (((q & 1) ? e1 : 0) + ((q & 2) ? e2 : 0)), 0), neq);
-    cnt = ngt + take;
-#pragma unroll
-    for (int w = 0; w < NV / 32; ++w)
-      for (; take > 0 && eq[w] != 0u; --take) {
-        const uint32_t top = 0x80000000u >> __clz(eq[w]);
-        hit[w] |= top;
-        eq[w] &= ~top;
-      }
+    cnt = find_hits(t0);
     c = pair_sums(cnt, c1, c2);
+    fits = row_fits(cnt, c);
+    if (__ballot(!fits) != 0ull) {
+      uint32_t eq[NV / 32];
+      int ngt = 0, neq = 0;
+#pragma unroll
+      for (int w = 0; w < NV / 32; ++w) {
+        uint32_t m = 0;
+#pragma unroll
+        for (int e = 32 * w; e < 32 * w + 32; e += 4) push4_eq_f32(m, v[e], v[e + 1], v[e + 2], v[e + 3], t0);
+        eq[w] = fits ? 0u : m;
+        hit[w] &= ~eq[w];
+        neq += __popc(eq[w]);
+        ngt += __popc(hit[w]);
+      }
+      int e1, e2;
+      pair_sums(ngt, e1, e2);
+      const int need = k - (ngt + e1 + e2);
+      pair_sums(neq, e1, e2);
+      int take = min(max(need - (((q & 1) ? e1 : 0) + ((q & 2) ? e2 : 0)), 0), neq);
+      cnt = ngt + take;
+#pragma unroll
+      for (int w = 0; w < NV / 32; ++w)
+        for (; take > 0 && eq[w] != 0u; --take) {
+          const uint32_t top = 0x80000000u >> __clz(eq[w]);
+          hit[w] |= top;
+          eq[w] &= ~top;
+        }
+      c = pair_sums(cnt, c1, c2);
+    }
   }
   int pos = ((q & 1) ? c1 : 0) + ((q & 2) ? c2 : 0);
   uint64_t key[HMAX];

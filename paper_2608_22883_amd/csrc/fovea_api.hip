@@ -101,11 +101,10 @@ SplitK forward_splitk(const fovea_dims& D, int64_t n) {
   const int bk = D.dtype == FOVEA_BF16 ? 64 : 32;
   const int ni = static_cast<int>(n);
   SplitK k;
-  // at most 8 slices (one request: 16 slices of 256 columns 56.0 -> 8 of 512 53.8 us per
-  // step, the combine reading half the partials); the combine merges the slices' LayerNorm
-  // statistics in registers (at most kHqMaxKs)
-  static_assert(kHqMaxKs >= 8, "query GEMM slices");
-  k.hq = std::min(splitk_slices(((ni + 127) / 128) * ((D.d_m + 2 * D.d_c + 127) / 128), D.d, bk), 8);
+  // at most kHqMaxKs slices (one request: 16 slices of 256 columns 56.0 -> 8 of 512 53.8 us
+  // per step, the combine reading half the partials), whose LayerNorm statistics the combine
+  // merges in registers
+  k.hq = std::min(splitk_slices(((ni + 127) / 128) * ((D.d_m + 2 * D.d_c + 127) / 128), D.d, bk), kHqMaxKs);
   k.c1 = splitk_slices(((ni + 63) / 64) * ((2 * D.d_c + 127) / 128), D.d_m, bk);
   k.c2 = splitk_slices(((ni + 127) / 128) * ((D.d + 127) / 128), D.d_c, bk);
   return k;
@@ -187,13 +186,13 @@ bool dims_supported(const fovea_dims* d) {
 
 enum KernelSlot {
   kRowStats, kHq, kScore, kSelect, kCorr1, kCorr2, kRms, kMemStats, kMemProj, kLmHead, kLmMerge,
-  kBwdFill, kBwdStats, kBwdTranspose, kBwdPrep, kBwdGemm, kBwdSelFwd, kBwdRmsGate, kBwdSel,
+  kBwdFill, kBwdStats, kBwdPrep, kBwdGemm, kBwdSelFwd, kBwdRmsGate, kBwdSel,
   kBwdLn, kBwdReduce, kBwdMem, kNumSlots
 };
 const char* const kSlotNames[kNumSlots] = {
     "row_stats",     "hq",           "score",       "select_gather", "corr1",
     "corr2",         "rms",          "mem_row_stats", "mem_proj",    "lm_head",
-    "lm_merge",      "bwd_fill",     "bwd_stats",   "bwd_transpose", "bwd_prep",
+    "lm_merge",      "bwd_fill",     "bwd_stats",   "bwd_prep",
     "bwd_gemm",      "bwd_sel_fwd",  "bwd_rms_gate", "bwd_sel",      "bwd_ln",
     "bwd_reduce",    "bwd_memory"};
 
@@ -671,12 +670,8 @@ fovea_status run_retrieve_fuse(fovea_ctx* c, const RFArgs& a, hipStream_t s) {
   }
   // 4. selection and gather, one block per node
   SelectArgs<T> sa;
-  sa.mem_off = a.mem_off;
-  sa.n_mem = a.n_mem;
   sa.m_max = a.m_max;
-  sa.node_req = node_req;
   sa.info = info;
-  sa.tau = a.tau;
   sa.valid = a.valid;
   sa.values = static_cast<const T*>(a.values);
   sa.d_m = D.d_m;
@@ -690,7 +685,6 @@ fovea_status run_retrieve_fuse(fovea_ctx* c, const RFArgs& a, hipStream_t s) {
   sa.k_out = a.k_out;
   sa.idx_out = a.idx_out;
   sa.mass_out = a.mass_out;
-  sa.err = c->err;
   {
     ProfScope ps(pc, kSelect, s);
     const int VEC = D.dtype == FOVEA_BF16 ? 8 : 4;

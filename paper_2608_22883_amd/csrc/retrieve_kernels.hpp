@@ -419,7 +419,7 @@ __global__ __launch_bounds__(256) void hq_kernel(TileMap tm, int n, const T* __r
 // adds its 8 columns' partials (as
 // splitk_combine does), so that those loads and the statistics' loads are in flight
 // together; then the barrier; then the epilogue.
-constexpr int kHqMaxKs = 32;  // the query GEMM's k slices are at most d / 128 <= 32 here
+constexpr int kHqMaxKs = 8;  // k slices of the query GEMM
 
 template <typename T>
 __global__ __launch_bounds__(256) void hq_combine_kernel(HqEpi<T> epi, int ks,
@@ -1014,12 +1014,8 @@ constexpr int kScoreMaxParts = 4;  // k slices of the score GEMM (partial score 
 
 template <typename T>
 struct SelectArgs {
-  const int64_t* mem_off;
-  int64_t n_mem;
   int m_max;
-  const int32_t* node_req;
   const NodeInfo* info;
-  const float* tau;
   const uint8_t* valid;
   const T* values;
   int d_m;
@@ -1032,7 +1028,6 @@ struct SelectArgs {
   int32_t* k_out;
   int32_t* idx_out;
   float* mass_out;
-  uint32_t* err;
 };
 
 // Sums and maxima over a block of NT threads, in every thread (red: NT / 64 values of LDS;

@@ -505,7 +505,7 @@ ScorePlan score_plan(const fovea_dims& D, int B, int n, int t_max, int64_t n_mem
     // (a second round of few blocks is worse than that kernel's larger tiles)
     const bool tail = !one && blocks < 640;
     // (keys of 512 to 767: not where that kernel has its 96-key tiles)
-    tiles = (t >= 64 && (wide || (D.d_m >= 512 && !ragged && p.kb < 6))) ||
+    tiles = (t >= 64 && wide) || (t >= 48 && D.d_m >= 512 && !wide && !ragged && p.kb < 6) ||
             (wide && ((t >= 48 && blocks >= 230) ||
                       (!tail && ((t >= 32 && blocks >= 307) || blocks >= 486))));
   } else {
@@ -517,15 +517,17 @@ ScorePlan score_plan(const fovea_dims& D, int B, int n, int t_max, int64_t n_mem
   return tiles ? ScorePlan{true, 5, 1} : p;
 }
 
-// fp32 scores of few nodes a request, or of narrow keys, take score_f32_kernel, unless its grid
-// leaves compute units idle (32 requests over 576 keys of 1024: 16 nodes 30 us against 34 in
-// tiles, 32 nodes 37 and 35, 48 nodes 44 and 35; 2 x 16 nodes over 2500 of 1024 33 and 23; 16 x
-// 64 over 3000 of 64 16 and 16, of 192 30 and 29)
+// fp32 scores of few nodes a request, or of narrow keys, take score_f32_kernel, whose time goes
+// with the blocks of 16 nodes, unless its grid leaves compute units idle (32 requests over 576
+// keys of 1024: 16 nodes 30 us against 34 in tiles, 17 36 and 35, 33 44 and 35, of 512: 32 nodes
+// 21 and 21, 33 25 and 21; 128 x 16 over 576 of 1024 93 and 98, 48 118 and 101; 2 x 16 nodes over
+// 2500 of 1024 33 and 23; 16 x 64 over 3000 of 64 16 and 16, of 192 30 and 29)
 bool score_f32_few(const fovea_dims& D, int B, int n, int m_max) {
   const int64_t blocks = static_cast<int64_t>(B) * ((m_max + 63) / 64);
-  const int t = static_cast<int>((static_cast<int64_t>(n) + B - 1) / B);
+  const int t = static_cast<int>((static_cast<int64_t>(n) + B - 1) / B), nb = (t + 15) / 16;
   if (blocks < 128) return false;
-  return !(t >= 48 && D.d_m >= 512 && (blocks <= 320 || t == 64 || (t > 64 && D.d_m >= 1024)));
+  if (D.d_m >= 1024) return nb < 4 && (nb == 1 || blocks > 320);
+  return D.d_m < 512 || (nb != 4 && (nb < 3 || blocks > 320));
 }
 
 // Few nodes: the two correction layers run in skinny tiles, which need no combine launches,

@@ -135,7 +135,7 @@ def kernel_model(wl, case, union_rows, k_sum, lm=None, kc=0):
     k["corr2"] = dict(bytes=n * d_c * es + d * d_c * es + 2 * n * d * es, flops=2 * n * d_c * d)
     k["rms"] = dict(bytes=2 * n * d * es, flops=3 * n * d)
     if lm is not None:
-        tile = 256 if es == 2 and n > 64 else 128  # columns of a candidate list
+        tile = 256 if es == 2 and n > 64 else 128  # columns of a candidate list (a head of many tiles)
         cand = n * ((lm["vocab"] + tile - 1) // tile) * kc * 8
         k["lm_head"] = dict(bytes=lm["vocab"] * d * es + n * d * es + cand,
                             flops=2 * n * d * lm["vocab"])

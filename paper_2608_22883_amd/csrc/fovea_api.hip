@@ -471,7 +471,8 @@ int score_chunks(int B, int n, int t_max, int blocks_per_request) {
 // (score_bf16_any_kernel where it has no instantiation).
 //   Both operands through the LDS cost score_tiles_kernel the staging of 64 nodes a chunk
 // however few there are and a pipeline that few chunks of k do not fill, so it wins with many
-// nodes, wide keys and full rounds.  Score kernel, us (score_bf16_kernel, tiles):
+// nodes, wide keys and full rounds.  Score kernel, us (score_bf16_kernel, tiles), keys in the
+// cache:
 // 32 x 60 over 576 of 1024 16.4, 14.6; 16 x 17 over 1000 of 1024 11.9, 13.8; 128 x 16 over 576
 // of 512 21.2, 22.2 and of 1024 38.6, 35.1; 16 x 64 over 3000 of 512 18.6, 19.9; 64 x 60 over
 // 576 of 512 17.6, 15.1; 40 x 64 over 2000 of 64 12.1, 13.9.  Over 12 widths, 20 batches and 2 to
@@ -486,22 +487,35 @@ ScorePlan score_plan(const fovea_dims& D, int B, int n, int t_max, int64_t n_mem
   if (p.kb < 4) return p;  // a small grid, whose k slices score_bf16_kernel has
   const int t = static_cast<int>((static_cast<int64_t>(n) + B - 1) / B);  // nodes of the mean request
   const int64_t blocks = (n_mem + 79) / 80 * ((t + 63) / 64);
-  // runs of 128-key tiles on every compute unit, of one chunk of nodes, where they take less
-  // time: 4 us and 15 a tile against 10 for each 80-key tile of a unit, at d_m = 1024 (8 x 64
-  // nodes over 16384 keys: 62 us in runs of 4, 75 in 80-key tiles; 16 x 64 over 3000: 29, 27;
-  // 8 x 130 over 16384: 220, 150)
-  if (t >= 32 && t <= 64 && B <= 128 && D.d_m >= 256) {
-    const int tiles = (m_max + 127) / 128, per = 256 / B, run = (tiles + per - 1) / per;
-    if (run > 1 && 4 + 15 * run < 10 * ((blocks + 255) / 256)) return ScorePlan{true, 8, run};
+  const bool ragged = score_spread(B, n_mem, m_max) != 0, wide = D.d_m >= 768;
+  // Runs of 128-key tiles, one run a compute unit, of one or two chunks of nodes.  Ragged
+  // memories leave runs without work, but 32 stripes of the grid (XCD and shader engine) have 8
+  // units each and a stripe with a ninth run takes two rounds: 220 runs at most, of memories
+  // long against a run (24 x 60 nodes over 53406 keys in all 63 us in 232 runs, 42 in 80-key
+  // tiles).  Keys read again from the cache: 4 us and 15 a tile against 10 for each 80-key tile
+  // of a unit, at d_m = 1024 (8 x 64 nodes over 16384 keys: 62 us in runs of 4, 75 in 80-key
+  // tiles; 16 x 64 over 3000: 30, 29).  Keys from HBM, as in a draft loop, let the second round
+  // of 80-key tiles wait and runs of two win from 513 of these on (16 x 64 over 3000 of 1280: 59
+  // and 65, of 1024 48 and 50, 33 nodes 45 and 46; 16 x 48 over 44286 in all, of 896: 44 and 52)
+  const int ch = (t + 63) / 64;
+  if (t >= 32 && ch <= 2 && B * ch <= 128 && D.d_m >= 256) {
+    const int tiles = (m_max + 127) / 128, per = 256 / (B * ch);
+    int64_t run = (tiles + per - 1) / per;
+    if (ragged) {
+      const int room = 220 - ch * B / 2;
+      const int64_t r = std::max<int64_t>(2, (ch * n_mem / 128 + room - 1) / room);
+      if (r < run && n_mem >= 1024 * r * B) run = r;
+    }
+    const bool cached = 4 + 15 * run < 10 * ((blocks + 255) / 256);
+    const bool hbm = t >= 48 && wide && n_mem >= 1024 * run * B && 9 * run < 10 * ((blocks + 511) / 512);
+    if (run > 1 && (ch == 1 ? cached || hbm : hbm)) return ScorePlan{true, 8, static_cast<int>(run)};
   }
   const bool half = 2 * blocks <= 512, one = blocks <= 512;  // rounds of two blocks a unit
-  const bool ragged = score_spread(B, n_mem, m_max) != 0;
   bool tiles;
   if (score_kernel_for(D.d_m / score_cfg::KC, p.kb) != score_bf16_any_kernel) {
     // score_bf16_kernel has a block for every chunk that t_max allows
     const int per = (m_max + 16 * p.kb - 1) / (16 * p.kb);
     if ((t_max + 63) / 64 > score_chunks(B, n, t_max, per)) return ScorePlan{true, 5, 1};
-    const bool wide = D.d_m >= 768;
     // (a second round of few blocks is worse than that kernel's larger tiles)
     const bool tail = !one && blocks < 640;
     // (keys of 512 to 767: not where that kernel has its 96-key tiles)
@@ -518,16 +532,17 @@ ScorePlan score_plan(const fovea_dims& D, int B, int n, int t_max, int64_t n_mem
 }
 
 // fp32 scores of few nodes a request, or of narrow keys, take score_f32_kernel, whose time goes
-// with the blocks of 16 nodes, unless its grid leaves compute units idle (32 requests over 576
-// keys of 1024: 16 nodes 30 us against 34 in tiles, 17 36 and 35, 33 44 and 35, of 512: 32 nodes
-// 21 and 21, 33 25 and 21; 128 x 16 over 576 of 1024 93 and 98, 48 118 and 101; 2 x 16 nodes over
-// 2500 of 1024 33 and 23; 16 x 64 over 3000 of 64 16 and 16, of 192 30 and 29)
+// with the blocks of 16 nodes, unless its grid leaves compute units idle.  Score kernel, us
+// (score_f32_kernel, tiles), keys read again from the cache and, after the slash, from HBM, which
+// hides more of the tiles' time: 128 requests over 576 keys of 512, 16 nodes 37, 57 / 65, 69, 32
+// nodes 50, 55 / 71, 70, 48 nodes 62, 58 / 76, 69; 32 over 576 of 512, 32 nodes 21, 21 / 28, 24;
+// 64 over 576 of 1024, 17 nodes 52, 57 / 78, 76, of 1280 71, 70 / 92, 80; 16 x 64 over 3000 of 64
+// 16, 16, of 192 30, 29; 2 x 16 over 2500 of 1024 33, 23
 bool score_f32_few(const fovea_dims& D, int B, int n, int m_max) {
   const int64_t blocks = static_cast<int64_t>(B) * ((m_max + 63) / 64);
   const int t = static_cast<int>((static_cast<int64_t>(n) + B - 1) / B), nb = (t + 15) / 16;
   if (blocks < 128) return false;
-  if (D.d_m >= 1024) return nb < 4 && (nb == 1 || blocks > 320);
-  return D.d_m < 512 || (nb != 4 && (nb < 3 || blocks > 320));
+  return D.d_m < 512 || nb == 1 || (nb == 2 && D.d_m <= 1024 && blocks > 320);
 }
 
 // Few nodes: the two correction layers run in skinny tiles, which need no combine launches,
@@ -692,7 +707,10 @@ fovea_status run_retrieve_fuse(fovea_ctx* c, const RFArgs& a, hipStream_t s) {
     const int VEC = D.dtype == FOVEA_BF16 ? 8 : 4;
     const int nch = (D.d_m / VEC + 63) / 64;  // 16-byte chunks per lane per value row
     // one wave selects a node of at most 1024 entries (16 keys per lane); larger memories,
-    // wider value rows and larger k_max go to the block-wide kernel
+    // wider value rows and larger k_max go to the block-wide kernel (60 nodes a request, d_m =
+    // 1024, k_max 64, us, one wave and block-wide: 1 request over 576 entries 13.6 and 14.5, 32
+    // 21.3 and 44.4, over 1000 26.5 and 45.3.  Few nodes with more to select are better
+    // block-wide: 4 requests over 1000 17.3 and 15.2, 1 with k_max 256 39.1 and 17.6)
     const bool wave_path = a.k_max <= kWaveSelKmax && a.m_max <= 1024 && nch <= 4;
     if (wave_path) {
       // one node per block when the pairs would leave compute units idle: the gather of a

@@ -705,10 +705,10 @@ inline BfTile best_bf_tile(F&& per_xcd) {
 // x = x0 + x1 (+ x2) with x0 = bf16(x), x1 = bf16(x - x0), x2 = bf16(x - x0 - x1).  Two
 // planes leave 2^-16 |x| and take three products (00, 10, 01); three planes hold all 24
 // bits of an operand of at least 2^-110 (below that the lower planes run into bf16's
-// subnormals, and an operand keeps its bits down to 2^-133) and take the six products of weight 2^-16 or more (00, 01, 10, 11, 02, 20): what is
-// left out is below fp32's own rounding, and the matrix cores round once per 32 products,
-// so the sum is closer to 64 bits than fp32 MFMA's (1920 x 2048 x 4096: 1.0e-6 against
-// 1.2e-6).
+// subnormals, and an operand keeps its bits down to 2^-133) and take the six products of
+// weight 2^-16 or more (00, 01, 10, 11, 02, 20): what is left out is below fp32's own
+// rounding, and the matrix cores round once per 32 products, so the sum is closer to 64 bits
+// than fp32 MFMA's (1920 x 2048 x 4096: 1.0e-6 against 1.2e-6).
 //   B comes as planes, [row][K / 32][plane][32]: 64 P bytes hold 32 k of a row in every
 // plane, one LDS row of a k-tile, so that a loaded tile serves all products (three copies
 // of K in one ordinary GEMM load and read half as much again).  A comes as planes too, or

@@ -667,8 +667,8 @@ __global__ __launch_bounds__(256, (KB >= 5 || NKC >= 20) ? 1 : 2) void score_bf1
 
 // ---------------------------------------------------------------------------------
 // Scores for larger grids and for fp32: one block per (request, chunk of 64 nodes (every
-// gch-th), run of tpb consecutive tiles of 16 KB keys), four waves; wave w owns node block w and all keys of a
-// tile.  Both operands pass through the LDS by direct-to-LDS loads: a stage holds 64 k (fp32:
+// gch-th), run of tpb consecutive tiles of 16 KB keys), four waves; wave w owns node block w
+// and all keys of a tile.  Both operands pass through the LDS by direct-to-LDS loads: a stage holds 64 k (fp32:
 // 32) of the chunk's nodes (two planes, 16 KB; fp32 8 KB) and of the tile's keys, NST stages,
 // across the tiles of the run; rows of 128 bytes swizzled as in gemm.hpp.  fp32: a lane's 16
 // bytes are four consecutive k, one for each of four MFMAs (the same permutation of k for

@@ -98,7 +98,8 @@ def test_batches_between_tiles(lib, dtype, B, T, d, d_m, d_c):
     compare(case, _run(lib, case), run_oracle(case), H_TOL[dtype], label=f"batch {dtype} n={B * T}")
 
 
-# scores: runs of 128-key tiles (a ragged last run, unaligned score rows), 80-key tiles (two node
+# scores: runs of 128-key tiles (a ragged last run, unaligned score rows, two chunks of nodes,
+# runs shorter than the longest memory asks for), 80-key tiles (two node
 # chunks, more and fewer chunks of k than stages, ragged memories), the register kernel's 64-, 80-
 # and 96-key tiles, each key count of the fp32 tiles and the fp32 kernel for few nodes (whole and
 # partial blocks of 16 nodes, two chunks)
@@ -108,7 +109,8 @@ def test_batches_between_tiles(lib, dtype, B, T, d, d_m, d_c):
     ("f32", 5, 65, 1400, None, 64), ("f32", 12, 3, 1201, None, 192), ("f32", 16, 17, 1300, 700, 64),
     ("f32", 20, 5, 1500, None, 128), ("bf16", 4, 33, 16001, None, 256), ("bf16", 16, 17, 1000, None, 256),
     ("bf16", 34, 5, 601, None, 512), ("bf16", 32, 9, 600, None, 768), ("f32", 8, 17, 1030, None, 64),
-    ("f32", 8, 70, 1030, 500, 64), ("f32", 8, 33, 1030, None, 512), ("f32", 8, 32, 1030, None, 512)])
+    ("f32", 8, 70, 1030, 500, 64), ("f32", 8, 33, 1030, None, 512), ("f32", 8, 32, 1030, None, 512),
+    ("bf16", 4, 66, 5301, None, 768), ("bf16", 8, 48, 11001, 500, 768)])
 def test_score_tiles(lib, dtype, B, T, M, M_lo, d_m):
     wl = _wl(dtype, B=B, T=T, M=M, d_m=d_m, k_max=16, key_scale=(30.0, 30.0), **({"M_lo": M_lo} if M_lo else {}))
     case = make_case(wl, affine="unit")
